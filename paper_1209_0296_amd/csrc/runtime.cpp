@@ -103,7 +103,8 @@ bool lut32_ok(const sl_lattice* h)
     return true;
 }
 
-// Default schedule for a shape, from the schedule autotuner's timings on
+// Default schedule of one sweep per launch (or of a resident lattice) for a
+// shape, from the schedule autotuner's timings on
 // MI355X (us per sweep):
 //   - lattices of at most 16 KiB run resident in LDS (2D L = 64: 2.4);
 //   - 2D up to L = 1024: fused with 2-row strips, 1 word per lane (L = 1024:
@@ -131,7 +132,7 @@ bool lut32_ok(const sl_lattice* h)
 // shapes the whole-row kernels cannot take fall back to the window kernels.
 constexpr uint64_t kResidentAuto = 16 * 1024;
 
-sl_launch auto_launch(const sl_lattice* h)
+sl_launch row_launch(const sl_lattice* h)
 {
     const Geom g = {(uint32_t)h->params.L, (uint32_t)(h->params.L / 2), (uint32_t)h->params.dim,
                     0u, h->lay.nh};
@@ -196,6 +197,38 @@ sl_launch auto_launch(const sl_lattice* h)
     l.tile_rows = 0;
     l.tile_words = 0;
     return l;
+}
+
+// Beside that schedule, which sl_get_launch reports, the default runs several
+// sweeps per launch on LDS tiles (tile_device.hpp) where that is faster (us
+// per sweep, per-sweep launches against tiles): 2D L = 64: 2.2 against 0.81;
+// 512: 4.2 and 1.3; 1048, where rows fit no row kernel: 36 and 2.5; 4096: 14.6
+// and 12.5; 6144: 35.2 and 26.6; 8200: 77.7 and 48.4; 3D L = 64: 8.0 and 2.8;
+// 128: 8.7 and 5.9.  Not for Ising lattices of L >= 8192 whose rows fit the
+// fused kernels (8192: spin-1/2 38.8 against 45.7, spin-1 68.0 and 71.9; NE,
+// whose random numbers are drawn less often, 51.9 against 48.2), nor for 3D
+// lattices above L = 128, where the halo costs more than the launches (160:
+// 10.7 against 13.1).  Zero thresholds need the kernels with 64-bit tables.
+sl_launch auto_launch(const sl_lattice* h, TilePlan* tile)
+{
+    *tile = TilePlan{};
+    if (is_sub_lattice(h->params.model)) return sl_launch{};
+    const sl_launch l = row_launch(h);
+    const bool ising = h->params.model == SL_ISING, coupled = h->params.model == SL_NE_COUPLED;
+    if ((ising || coupled) && !lut32_ok(h)) return l;
+    if (h->params.dim == 3 ? h->params.L > 128 : ising && h->params.L >= 8192 && l.mode == SL_MODE_FUSED) return l;
+    *tile = tile_plan(args_of(h).g, h->kind, coupled);
+    return l;
+}
+
+// The resident schedule runs as one tile if the lattice and its table allow it.
+TilePlan resident_tile(const sl_lattice* h)
+{
+    const Geom g = args_of(h).g;
+    const TilePlan p = whole_plan(g);
+    TileGeom t;
+    const bool table32 = h->params.model == SL_NORTH_EAST || lut32_ok(h);
+    return table32 && tile_geom(g, p, p.k, t) ? p : TilePlan{};
 }
 
 sl_status check_launch(const sl_lattice* h, sl_launch* l)
@@ -344,6 +377,38 @@ sl_status enqueue_sweeps(sl_lattice* h, uint64_t n)
 {
     if (is_sub_lattice(h->params.model)) return sweep_ne_sub(h, n);
     SweepArgs a = args_of(h);
+    if (h->tile.k) {
+        // equal launches of at most k sweeps
+        const uint64_t launches = (n + h->tile.k - 1) / h->tile.k;
+        for (uint64_t i = 0, l = 0; l < launches; ++l) {
+            const uint32_t k = (uint32_t)((n - i + (launches - l) - 1) / (launches - l));
+            TileGeom tg;
+            hipError_t e = hipErrorInvalidValue;
+            if (tile_geom(a.g, h->tile, k, tg)) {
+                // a tile that is the whole lattice is updated in place
+                const int nxt = tile_whole(tg) ? h->cur : h->cur ^ 1;
+                uint8_t* d0 = h->base + h->lay.off_col[nxt][0];
+                uint8_t* d1 = h->base + h->lay.off_col[nxt][1];
+                a.t = (uint32_t)(h->next_t + i);
+                a.acc = slot_ptr(h, h->pending + i);
+                e = launch_tile(a, h->kind, tg, k, d0, d1, h->stream);
+                if (e == hipSuccess) {
+                    h->cur = nxt;
+                    a.col[0] = d0;
+                    a.col[1] = d1;
+                }
+            }
+            if (e != hipSuccess) {
+                h->next_t += i;
+                h->pending += i;
+                return hip_fail(e, "tile sweep launch");
+            }
+            i += k;
+        }
+        h->next_t += n;
+        h->pending += n;
+        return SL_OK;
+    }
     if (h->launch.mode == SL_MODE_RESIDENT) {
         for (uint64_t i = 0; i < n;) {
             const uint32_t k = (uint32_t)std::min<uint64_t>(n - i, kResidentChunk);
@@ -466,8 +531,7 @@ sl_status sl_create_lattice(const sl_params* params, void* device_buf, size_t by
     h->first_t = params->t0;
     h->cur = 0;
     h->table_n = build_table(params, h->table);
-    h->launch = auto_launch(h);
-    if (is_sub_lattice(params->model)) h->launch = sl_launch{};
+    h->launch = auto_launch(h, &h->tile);
     h->stage = nullptr;
     hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&h->stage),
                                  params->record_capacity * sizeof(sl_record), hipHostMallocDefault);
@@ -515,10 +579,14 @@ sl_status sl_set_launch(sl_lattice* h, const sl_launch* launch)
 {
     if (!h || !launch) return fail(SL_E_INVALID, "NULL argument");
     sl_launch l = *launch;
-    if (l.mode == SL_MODE_AUTO && !is_sub_lattice(h->params.model)) l = auto_launch(h);
+    TilePlan tile{};
+    const bool chosen = l.mode == SL_MODE_AUTO && !is_sub_lattice(h->params.model);
+    if (chosen) l = auto_launch(h, &tile);
     sl_status st = check_launch(h, &l);
     if (st != SL_OK) return st;
+    if (!chosen && l.mode == SL_MODE_RESIDENT) tile = resident_tile(h);
     h->launch = l;
+    h->tile = tile;
     return SL_OK;
 }
 

@@ -8,6 +8,7 @@
 #include "../../include/spinlat.h"
 #include "host_common.h"
 #include "spinlat_internal.h"
+#include "tile_plan.h"
 
 // Handle of one lattice: its parameters, the layout of the borrowed device
 // buffer, the stream, sweep and record counters, and the schedule.
@@ -22,6 +23,7 @@ struct sl_lattice {
     uint64_t first_t;  // t of the oldest unread record
     int cur;           // copy of the lattice holding the current state
     sl_launch launch;
+    spinlat::TilePlan tile;  // k != 0: sweeps run as tile launches (the default schedule only)
     uint64_t table[spinlat::kMaxLut];
     size_t table_n;
     sl_record* stage;  // pinned host staging for record readback (record_capacity)
@@ -34,7 +36,8 @@ constexpr uint64_t kResidentChunk = 4096;  // sweeps per resident launch at most
 
 SweepArgs args_of(const sl_lattice* h);
 unsigned long long* slot_ptr(const sl_lattice* h, uint64_t idx);  // record ring slot
-sl_launch auto_launch(const sl_lattice* h);                         // default schedule
+// Default schedule; the tile plan beside it (k = 0: none) goes to *tile.
+sl_launch auto_launch(const sl_lattice* h, TilePlan* tile);
 sl_status enqueue_observe(sl_lattice* h, uint64_t slot);            // record of the state
 sl_status enqueue_sweeps(sl_lattice* h, uint64_t n);                // n sweeps, unchecked
 

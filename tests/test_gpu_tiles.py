@@ -1,0 +1,60 @@
+"""Tile launches (several sweeps of LDS tiles per launch, the default schedule of
+small and middle lattices): bit-exact against the oracle at the sizes where a
+tile can go wrong -- the whole lattice as one tile, a dimension that a tile
+spans, ragged last tiles, halos deeper than a tile, several rounds of tiles per
+CU, 3D lattices up to the last tiled one -- with chunks that leave every
+remainder of a launch's sweeps."""
+import numpy as np
+import pytest
+
+import paper_1209_0296_amd as S
+from helpers import run_gpu, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+CHUNKS = [1, 2, 3, 12, 13, 17]
+KINDS = {
+    "half": dict(T=2.269), "half_field": dict(T=2.0, h=-0.3, J=-1.0), "one": dict(two_s=2, T=1.7, h=0.1),
+    "ne": dict(model=S.NORTH_EAST, c=0.3), "ne_half": dict(model=S.NORTH_EAST, c=0.5),
+    "ne_up": dict(model=S.NORTH_EAST, c=0.6), "coupled": dict(model=S.NE_COUPLED, c=0.5, T=3.0, h=0.1),
+}
+
+
+def _same(sp, chunks, launch=None):
+    got_s, got_r = run_gpu(sp, sum(chunks), launch=launch, chunks=chunks)
+    ref_s, ref_r = run_oracle(sp, sum(chunks))
+    np.testing.assert_array_equal(got_r, ref_r)
+    np.testing.assert_array_equal(got_s, ref_s)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("L", [8, 40, 64, 72, 136, 264, 520])
+def test_tiles_2d(L, kind):
+    _same(S.Params(L=L, seed=L + 1, record_capacity=64, **KINDS[kind]), CHUNKS)
+
+
+@pytest.mark.parametrize("kind", ["half", "one", "ne", "coupled"])
+@pytest.mark.parametrize("L", [1048, 2056])
+def test_tiles_2d_many_rounds(L, kind):
+    _same(S.Params(L=L, seed=L + 1, record_capacity=16, **KINDS[kind]), [1, 3, 5])
+
+
+@pytest.mark.parametrize("kw", [dict(T=4.5), dict(T=4.0, h=0.2), dict(two_s=2, T=3.1, h=-0.2)])
+@pytest.mark.parametrize("L", [8, 16, 24, 40, 72, 128])
+def test_tiles_3d(L, kw):
+    _same(S.Params(dim=3, L=L, seed=L + 1, record_capacity=64, **kw), [1, 2, 3, 7] if L > 40 else CHUNKS)
+
+
+def test_tiles_between_other_schedules():
+    """The two lattice copies stay in step when schedules alternate."""
+    sp = S.Params(L=256, T=2.3, seed=5, record_capacity=64)
+    ref_s, ref_r = run_oracle(sp, 24)
+    lat = S.Lattice(sp)
+    recs = [S.records_to_array(lat.measure())]
+    for mode, n in ((S.MODE_AUTO, 5), (S.MODE_FUSED, 3), (S.MODE_AUTO, 13), (S.MODE_HALF_WINDOW, 2), (S.MODE_AUTO, 1)):
+        lat.set_launch(mode)
+        lat.sweep(n)
+        recs.append(S.records_to_array(lat.measure()))
+    np.testing.assert_array_equal(np.vstack(recs), ref_r)
+    np.testing.assert_array_equal(lat.spins(), ref_s)
+    lat.close()
