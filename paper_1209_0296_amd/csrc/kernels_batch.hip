@@ -67,7 +67,7 @@ __device__ __forceinline__ void batch_walk_body(const BatchJob& J, const uint32_
     __syncthreads();
     const SweepArgs a = job_sweep_args(J, dj, colour, step);
     const RowGeom rg = *reinterpret_cast<const RowGeom*>(J.rg_words);
-    Obs o = {0, 0, 0, 0, 0};
+    Obs o = {};
     const Lanes ln = lanes_of(rg, false);
     const uint32_t item = ln.slot < rg.slots ? w.item_base + ln.wave * rg.slots + ln.slot : 0xFFFFFFFFu;
     half_item<KIND, DIM, D, false>(a, rg, item, ln, lut, xch, thr_up, thr_down, o);
@@ -82,7 +82,7 @@ __device__ __forceinline__ void batch_rows_body(const BatchJob& J, const uint32_
 {
     const SweepArgs a = job_sweep_args(J, dj, colour, step);
     const RowGeom rg = *reinterpret_cast<const RowGeom*>(J.rg_words);
-    Obs o = {0, 0, 0, 0, 0};
+    Obs o = {};
     const Lanes ln = lanes_of(rg, false);
     rows_run<KIND, DIM, D, kRagNone>(a, rg, w.item_base + ln.wave * rg.K, ln, J.table, lut, o);
     int32_t bond, mag, acc, unfl;
@@ -104,7 +104,7 @@ __device__ __forceinline__ void batch_fused_body(const BatchJob& J, const uint32
     uint8_t* const N0 = second ? J.col[0][0] : J.col[1][0];  // the other copy
     uint8_t* const N1 = second ? J.col[0][1] : J.col[1][1];
     const RowGeom rg = *reinterpret_cast<const RowGeom*>(J.rg_words);
-    Obs o = {0, 0, 0, 0, 0};
+    Obs o = {};
     const Lanes ln = lanes_of(rg, false);
     const uint32_t item = ln.slot < rg.slots ? w.item_base + ln.wave * rg.slots + ln.slot : 0xFFFFFFFFu;
     fused_item<KIND, D, false, 0>(a, rg, item, ln, lut, xch, thr_up, thr_down, a.col[0], a.col[1], N0, N1, o);

@@ -17,7 +17,7 @@ __global__ void __launch_bounds__(1024) k_row_half(SweepArgs a, RowGeom rg)
     build_row_luts<KIND, DIM>(lut, a.lut, thr_up, thr_down);
     __syncthreads();
 
-    Obs o = {0, 0, 0, 0, 0};
+    Obs o = {};
     const Lanes ln = lanes_of(rg, XW);
     const uint32_t item = row_item(rg, XW, ln);
     half_item<KIND, DIM, D, XW>(a, rg, item, ln, lut, xch, thr_up, thr_down, o);
@@ -37,7 +37,7 @@ __global__ void __launch_bounds__(1024) k_row_fused(SweepArgs a, RowGeom rg, con
     build_row_luts<KIND, 2>(lut, a.lut, thr_up, thr_down);
     __syncthreads();
 
-    Obs o = {0, 0, 0, 0, 0};
+    Obs o = {};
     const Lanes ln = lanes_of(rg, XW);
     const uint32_t item = row_item(rg, XW, ln);
     fused_item<KIND, D, XW, HT>(a, rg, item, ln, lut, xch, thr_up, thr_down, S0, S1, D0, D1, o);

@@ -16,7 +16,7 @@ template <int KIND, int DIM, int D, int RAGS>
 __global__ void __launch_bounds__(1024) k_rows_half(SweepArgs a, RowGeom rg)
 {
     __shared__ RowLuts lut;
-    Obs o = {0, 0, 0, 0, 0};
+    Obs o = {};
     const Lanes ln = lanes_of(rg, false);
     const uint32_t it0 = (remap_block() * (blockDim.x >> 6) + ln.wave) * rg.K;
     rows_run<KIND, DIM, D, RAGS>(a, rg, it0, ln, a.lut, lut, o);

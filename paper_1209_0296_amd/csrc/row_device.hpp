@@ -20,14 +20,15 @@
 // >= 1; the runtime sends other tables to the generic kernels).
 //
 // Neighbour words are "prepared" once per row and reused by the three rows
-// that read them: spin-1/2 keeps bit 2 of each byte (4 per -1 spin), so the
-// sum of prepared neighbours is 4 x (number of -1 neighbours) per byte;
+// that read them: spin-1/2 keeps bit 1 of each byte (2 per -1 spin), so the
+// sum of prepared neighbours is 2 x (number of -1 neighbours) per byte;
 // spin-1 keeps s+1; NE keeps n.  The row parity p (which side the same-row
 // neighbour sits on) is a template parameter chosen by a uniform branch.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "pair_lut.hpp"
 #include "philox.hpp"
 #include "site_update.hpp"
 #include "spinlat_internal.h"
@@ -36,7 +37,6 @@ namespace spinlat {
 
 namespace rowk {
 
-constexpr uint32_t M4 = 0x04040404u;
 
 struct RowGeom {
     uint32_t L, Lh, ncols;
@@ -177,8 +177,9 @@ __device__ __forceinline__ uint32_t edge_words(const Vec<D>& q, const RowGeom& r
 }
 
 // ---- tables ---------------------------------------------------------------
-struct RowLuts {
-    uint64_t e[3 * 2 * 13];  // spin-1 entries; spin-1/2 uses the first words as u32
+union RowLuts {
+    PairLut pair;            // spin-1/2 and coupled NE
+    uint64_t e[3 * 2 * 13];  // spin-1
 };
 
 // Kernel kind of NE lattices with the Ising coupling: the NE code paths (every
@@ -190,23 +191,10 @@ __device__ __forceinline__ void build_row_luts(RowLuts& lut, const uint64_t* tab
                                                uint64_t& thr_down)
 {
     constexpr int z = 2 * DIM;
-    // entries each kind reads: spin-1/2 tables 2 (z + 1), spin-1 6 (2z + 1), NE none
-    constexpr int n = (KIND == KIND_ISING_HALF || KIND == KIND_NE_COUPLED) ? 2 * (z + 1)
-                      : KIND == KIND_ISING_ONE                             ? 6 * (2 * z + 1)
-                                                                           : 0;
-    for (int t = threadIdx.x; t < n; t += blockDim.x) {
-        if (KIND == KIND_ISING_HALF || KIND == KIND_NE_COUPLED) {
-            if (t < 2 * (z + 1)) {
-                // entry nd + sneg*(z+1): nd neighbours at -1, sneg = (s == -1)
-                const int sneg = t / (z + 1), nd = t % (z + 1);
-                const int s = sneg ? -1 : 1;
-                const int nsum = z - 2 * nd;
-                const int di = s > 0 ? 0 : 3;
-                // thr >= 1 here: accept iff word <= thr - 1
-                reinterpret_cast<uint32_t*>(lut.e)[t] =
-                    (uint32_t)(table[di * (2 * z + 1) + nsum + z] - 1ull);
-            }
-        } else if (KIND == KIND_ISING_ONE) {
+    if constexpr (KIND == KIND_ISING_HALF || KIND == KIND_NE_COUPLED) {
+        build_pair_lut<KIND == KIND_NE_COUPLED, DIM>(lut.pair, table);
+    } else if constexpr (KIND == KIND_ISING_ONE) {
+        for (int t = threadIdx.x; t < 6 * (2 * z + 1); t += blockDim.x) {
             const int nz = t % (2 * z + 1);
             const int ch = (t / (2 * z + 1)) & 1;
             const int s = t / (2 * (2 * z + 1)) - 1;
@@ -222,10 +210,11 @@ __device__ __forceinline__ void build_row_luts(RowLuts& lut, const uint64_t* tab
 }
 
 struct Obs {
-    int32_t acc;   // spin-1/2: 7 x accepted moves; others: accepted moves
+    int32_t acc;   // accepted moves; spin-1/2: sum of s s' over the counted words
+    int32_t n;     // spin-1/2: counted words
     int32_t mag0;  // sum of s (NE: n) over colour-0 words
     int32_t mag1;  // same over colour-1 words
-    int32_t dd;    // spin-1/2: sum s' * 4 nd; spin-1: sum s' * (nsum + z); NE: bond
+    int32_t dd;    // spin-1/2: sum s' * 2 nd; spin-1: sum s' * (nsum + z); NE: bond
     int32_t unfl;  // NE: sites with the flip flag clear
 };
 
@@ -233,7 +222,7 @@ struct Obs {
 template <int KIND>
 __device__ __forceinline__ uint32_t prep(uint32_t w)
 {
-    if constexpr (KIND == KIND_ISING_HALF) return w & M4;
+    if constexpr (KIND == KIND_ISING_HALF) return w & 0x02020202u;
     else if constexpr (KIND == KIND_ISING_ONE) return (w ^ 0x80808080u) + 0x80808081u;  // s+1, no carries
     else return w & 0x01010101u;
 }
@@ -252,19 +241,11 @@ __device__ __forceinline__ int dot4(uint32_t a, uint32_t b, int c)
     return __builtin_amdgcn_sdot4((int)a, (int)b, c, false);
 }
 
-// spin-1/2: nd4 = 4 x (number of -1 neighbours) per byte
-__device__ __forceinline__ uint32_t half_word(uint32_t own, uint32_t nd4, const Words4& w,
-                                              const uint8_t* lut_bytes, int z)
+// spin-1/2: nd2 = 2 x (number of -1 neighbours) per byte
+__device__ __forceinline__ uint32_t half_word(uint32_t own, uint32_t nd2, const Words4& w, const PairLut& lut)
 {
-    const uint32_t idx4 = nd4 + (own & M4) * (uint32_t)(z + 1);
-    uint32_t flip = 0;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        const uint32_t off = (idx4 >> (8 * b)) & 0xFFu;
-        const uint32_t t = *reinterpret_cast<const uint32_t*>(lut_bytes + off);
-        flip |= (w.w[b] <= t) ? (0xFEu << (8 * b)) : 0u;
-    }
-    return own ^ flip;
+    const uint32_t idx = nd2 | (own & 0x10101010u);  // twice the table number
+    return own ^ pair_accept<4, 68>(lut, idx, w, 0xFEFEFEFEu, [] {});
 }
 
 // spin-1: S = per-byte nsum + z
@@ -293,8 +274,7 @@ __device__ __forceinline__ uint32_t one_word(uint32_t own, uint32_t S, const Wor
 
 // NE constraint on the Ising energy (Sec. 3.2 with J != 0): a site whose north
 // and east neighbours are up takes the spin-1/2 move of s = 2n - 1.  S holds
-// the number of up neighbours per byte, so the table entry nd + sneg*5 (nd
-// neighbours down, sneg = 1 - n) is 9 - S - 5n, with no borrow between bytes.
+// the number of up neighbours per byte; the table number is S + 8n.
 __device__ __forceinline__ uint32_t ne_coupled_word(uint32_t own, uint32_t north, uint32_t east, uint32_t S,
                                                     uint32_t g, uint32_t colour, uint32_t t,
                                                     const PhiloxKey& ks, const RowLuts& lut)
@@ -304,13 +284,7 @@ __device__ __forceinline__ uint32_t ne_coupled_word(uint32_t own, uint32_t north
     uint32_t f = 0;
     if (__builtin_amdgcn_ballot_w64(allowed != 0u) != 0ull) {
         const Words4 w = philox4x32_10(g, colour, t, 0u, ks);
-        const uint32_t idx = 0x09090909u - S - n * 5u;
-        const uint32_t* thr_m1 = reinterpret_cast<const uint32_t*>(lut.e);
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const uint32_t bit = 1u << (8 * b);
-            if ((allowed & bit) && w.w[b] <= thr_m1[(idx >> (8 * b)) & 0xFFu]) f |= bit;
-        }
+        f = pair_accept<8, 136>(lut.pair, (n << 3) | S, w, 0x01010101u, [] {}) & allowed;
     }
     return (own ^ f) | (f << 1);
 }
@@ -365,15 +339,17 @@ __device__ __forceinline__ Vec<D> row_update(const Vec<D>& own, const Vec<D>& sa
             if constexpr (DIM == 3) S += zm->w[d] + zp->w[d];
             if constexpr (KIND == KIND_ISING_HALF) {
                 const Words4 w = pre ? pre[d] : philox4x32_10(g, colour, t, 0u, ks);
-                out.w[d] = half_word(own.w[d], S, w, reinterpret_cast<const uint8_t*>(lut.e), z);
+                out.w[d] = half_word(own.w[d], S, w, lut.pair);
                 if (count) {
-                    uint32_t ow = out.w[d], iw = own.w[d];
+                    uint32_t ow = out.w[d];
                     if constexpr (RAG) {
-                        const uint32_t m = (uint32_t)d < uncounted ? 0u : ~0u;
-                        ow &= m;
-                        iw &= m;
+                        const bool skip = (uint32_t)d < uncounted;
+                        ow = skip ? 0u : ow;
+                        o.n += skip ? 0 : 1;
+                    } else {
+                        o.n += 1;
                     }
-                    o.acc += __builtin_popcount(iw ^ ow);
+                    o.acc = dot4(own.w[d], ow, o.acc);
                     if (colour == 0) {
                         o.mag0 = dot4(ow, 0x01010101u, o.mag0);
                     } else {
@@ -430,10 +406,10 @@ __device__ __forceinline__ void finish_obs(const Obs& o, int32_t& bond, int32_t&
 {
     constexpr int z = 2 * DIM;
     if constexpr (KIND == KIND_ISING_HALF) {
-        // sum_b s'_b nsum_b = z sum s' - 2 sum s' nd, and dd = sum s' * 4 nd
-        bond = z * o.mag1 - o.dd / 2;
+        // sum_b s'_b nsum_b = z sum s' - 2 sum s' nd, and dd = sum s' * 2 nd
+        bond = z * o.mag1 - o.dd;
         mag = o.mag0 + o.mag1;
-        acc = o.acc / 7;
+        acc = (4 * o.n - o.acc) >> 1;  // s s' = 1 - 2 (flipped)
         unfl = 0;
     } else if constexpr (KIND == KIND_ISING_ONE) {
         bond = o.dd - z * o.mag1;  // dd = sum s' (nsum + z)

@@ -109,16 +109,13 @@ bool lut32_ok(const sl_lattice* h)
 //   - lattices of at most 16 KiB run resident in LDS (2D L = 64: 2.4);
 //   - 2D up to L = 1024: fused with 2-row strips, 1 word per lane (L = 1024:
 //     4.9 against 6.1 with 2 words); L = 2048: fused, 2-row strips, 2 words;
-//   - 2D L = 4096: fused, 4-row strips, 2 words (spin-1/2: 14.6 against 17.7
-//     with 4 words); L = 8192 spin-1/2 takes 16-row strips with 2 words per
-//     lane (38.3 against 39.8 with 8-row strips and 4 words, 40.5 with 16
-//     rows and 4 words, 42.2 with 32 rows and 1 word), and from L = 16384
-//     32-row strips with 4 words (16384: 133.7 against 141.4 with 16 rows;
-//     32768: 538 against 569); spin-1 takes 16-row strips with 2 words from
-//     L = 8192 (68.3 against 80.7 with 4-row strips); NE takes 8-row strips
-//     with 1 word at L = 4096 (17.1 against 17.6 with 4 rows and 2 words)
-//     and 4-row strips with 2 words from 8192; coupled NE keeps 4-row strips
-//     with 2 words;
+//   - 2D L = 4096: fused, 4-row strips, 2 words (spin-1/2: 14.2; NE: 8-row
+//     strips, 1 word, 17.1 against 17.6); from L = 8192 16-row strips with 2
+//     words per lane (8192: spin-1/2 36.6 against 38.2 with 8 rows and 4
+//     words, 41.1 with 32 rows; spin-1 68.3 against 80.7 with 4 rows; NE 48.0
+//     against 51.8 with 4 rows; coupled NE 41.9 against 47.0 with 4 rows),
+//     spin-1/2 from L = 16384 32-row strips with 4 words (132 against 150 with
+//     16 rows and 2 words; 32768: 538 against 569 with 16 rows and 4 words);
 //   - 3D: half-sweeps by independent row groups with 4 words per lane (L =
 //     256: 18.4 against 19.2 for the walk with 4-row strips; L = 64: 7.4
 //     against 8.8 with 2 words and 9.8 with 1; L = 128: 7.7 against 10.0 with
@@ -177,7 +174,7 @@ sl_launch row_launch(const sl_lattice* h)
     } else if (h->params.model == SL_NORTH_EAST && L < 8192) {
         H = 8;
         Ds[0] = 1, Ds[1] = 2, Ds[2] = 4;
-    } else if (L < 8192 || !(half_spin || h->kind == KIND_ISING_ONE)) {
+    } else if (L < 8192) {
         H = 4;
         Ds[0] = 2, Ds[1] = 4, Ds[2] = 1;
     } else if (L >= 16384 && half_spin) {
@@ -204,11 +201,11 @@ sl_launch row_launch(const sl_lattice* h)
 // per sweep, per-sweep launches against tiles): 2D L = 64: 2.2 against 0.81;
 // 512: 4.2 and 1.3; 1048, where rows fit no row kernel: 36 and 2.5; 4096: 14.6
 // and 12.5; 6144: 35.2 and 26.6; 8200: 77.7 and 48.4; 3D L = 64: 8.0 and 2.8;
-// 128: 8.7 and 5.9.  Not for Ising lattices of L >= 8192 whose rows fit the
-// fused kernels (8192: spin-1/2 38.8 against 45.7, spin-1 68.0 and 71.9; NE,
-// whose random numbers are drawn less often, 51.9 against 48.2), nor for 3D
-// lattices above L = 128, where the halo costs more than the launches (160:
-// 10.7 against 13.1).  Zero thresholds need the kernels with 64-bit tables.
+// 128: 8.7 and 5.9.  Not for lattices of L >= 8192 whose rows fit the fused
+// kernels (8192: spin-1/2 36.6 against 45.7, spin-1 68.0 and 71.9, coupled NE
+// 41.9 and 51.5, NE 48.0 and 48.5), nor for 3D lattices above L = 128, where
+// the halo costs more than the launches (160: 10.7 against 13.1).  Zero
+// thresholds need the kernels with 64-bit tables.
 sl_launch auto_launch(const sl_lattice* h, TilePlan* tile)
 {
     *tile = TilePlan{};
@@ -216,7 +213,7 @@ sl_launch auto_launch(const sl_lattice* h, TilePlan* tile)
     const sl_launch l = row_launch(h);
     const bool ising = h->params.model == SL_ISING, coupled = h->params.model == SL_NE_COUPLED;
     if ((ising || coupled) && !lut32_ok(h)) return l;
-    if (h->params.dim == 3 ? h->params.L > 128 : ising && h->params.L >= 8192 && l.mode == SL_MODE_FUSED) return l;
+    if (h->params.dim == 3 ? h->params.L > 128 : h->params.L >= 8192 && l.mode == SL_MODE_FUSED) return l;
     *tile = tile_plan(args_of(h).g, h->kind, coupled);
     return l;
 }

@@ -25,9 +25,8 @@
 // word itself and the adjacent one.
 //
 // Acceptance: spin-1/2 and coupled NE look two sites' thresholds up at once
-// (PairLut: the table entry of a pair is two 32-bit thr - 1 words), spin-1 one
-// site's.  All thresholds must be >= 1 ("word <= thr - 1"); other tables run
-// elsewhere.
+// (pair_lut.hpp), spin-1 one site's.  All thresholds must be >= 1 ("word <=
+// thr - 1"); other tables run elsewhere.
 //
 // Records: a lane adds its sums of a sweep to one of 32 LDS slots (no lane
 // conflicts but between the two halves of a wave); every kFlush sweeps, and
@@ -36,6 +35,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "pair_lut.hpp"
 #include "philox.hpp"
 #include "site_update.hpp"
 #include "spinlat_internal.h"
@@ -49,13 +49,6 @@ constexpr int kMaxBlock = 1024;
 constexpr int kFlush = 8;           // sweeps whose sums LDS holds
 constexpr int kObsSlots = 32;
 
-// spin-1/2 and coupled NE: entry (n0, n1) of two sites' table numbers n in
-// 0 .. 15, at byte 8 n0 + 136 n1 (the 8 bytes beyond 16 entries spread the
-// rows over the LDS banks).  n = neighbours at -1 + 8 (s == -1) for spin-1/2,
-// neighbours up + 8 n for coupled NE.
-struct PairLut {
-    uint64_t e[16 * 17];
-};
 // spin-1: entry 4 (row (2z + 1) + nsum + z) bytes, row = ds_index(s' - s)
 struct OneLut {
     uint32_t e[52];
@@ -76,18 +69,7 @@ __device__ __forceinline__ void build_lut(TileLut& lut, const uint64_t* table)
     if constexpr (KIND == KIND_ISING_ONE) {
         for (int t = threadIdx.x; t < 4 * (2 * z + 1); t += blockDim.x) lut.one.e[t] = (uint32_t)(table[t] - 1ull);
     } else if constexpr (KIND == KIND_ISING_HALF || KIND == KIND_NE_COUPLED) {
-        for (int t = threadIdx.x; t < 256; t += blockDim.x) {
-            uint32_t v[2];
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int n = k ? t >> 4 : t & 15;
-                const int m = (n & 7) <= z ? (n & 7) : z;  // 0 .. z
-                const bool up = KIND == KIND_ISING_HALF ? (n >> 3) == 0 : (n >> 3) == 1;
-                const int nsum = KIND == KIND_ISING_HALF ? z - 2 * m : 2 * m - z;
-                v[k] = (uint32_t)(table[(up ? 0 : 3) * (2 * z + 1) + nsum + z] - 1ull);
-            }
-            lut.pair.e[(t & 15) + 17 * (t >> 4)] = (uint64_t)v[0] | ((uint64_t)v[1] << 32);
-        }
+        build_pair_lut<KIND == KIND_NE_COUPLED, DIM>(lut.pair, table);
     }
 }
 
@@ -96,33 +78,6 @@ __device__ __forceinline__ void build_lut(TileLut& lut, const uint64_t* table)
 __device__ __forceinline__ void loads_first(Words4& c)
 {
     asm volatile("" : "+v"(c.w[0]), "+v"(c.w[1]), "+v"(c.w[2]), "+v"(c.w[3])::"memory");
-}
-
-__device__ __forceinline__ uint32_t udot4(uint32_t a, uint32_t b, uint32_t c)
-{
-    return __builtin_amdgcn_udot4(a, b, c, false);
-}
-__device__ __forceinline__ int32_t sdot4(uint32_t a, uint32_t b, int32_t c)
-{
-    return __builtin_amdgcn_sdot4((int)a, (int)b, c, false);
-}
-
-// Byte mask (0xFF & val per accepted site) of four sites whose table numbers,
-// scaled so that byte weights W0 and W1 give the PairLut offset, are in idx.
-// `between` runs after the table reads are issued and before their results
-// are used.
-template <uint32_t W0, uint32_t W1, class F>
-__device__ __forceinline__ uint32_t pair_accept(const PairLut& lut, uint32_t idx, const Words4& w, uint32_t val,
-                                                F between)
-{
-    const uint8_t* base = reinterpret_cast<const uint8_t*>(lut.e);
-    const uint2 lo = *reinterpret_cast<const uint2*>(base + udot4(idx, W0 | (W1 << 8), 0u));
-    const uint2 hi = *reinterpret_cast<const uint2*>(base + udot4(idx, (W0 << 16) | (W1 << 24), 0u));
-    between();
-    const bool a0 = w.w[0] <= lo.x, a1 = w.w[1] <= lo.y, a2 = w.w[2] <= hi.x, a3 = w.w[3] <= hi.y;
-    const uint32_t f0 = a0 ? val & 0xFFu : 0u, f1 = a1 ? val & 0xFF00u : 0u;
-    const uint32_t f2 = a2 ? val & 0xFF0000u : 0u, f3 = a3 ? val & 0xFF000000u : 0u;
-    return (f0 | f1 | f2) | f3;
 }
 
 // Prepared form of a word (see above).
