@@ -70,7 +70,11 @@ __device__ __forceinline__ void batch_walk_body(const BatchJob& J, const uint32_
     Obs o = {};
     const Lanes ln = lanes_of(rg, false);
     const uint32_t item = ln.slot < rg.slots ? w.item_base + ln.wave * rg.slots + ln.slot : 0xFFFFFFFFu;
-    half_item<KIND, DIM, D, false>(a, rg, item, ln, lut, xch, thr_up, thr_down, o);
+    bool zero = false;
+    if constexpr (KIND == KIND_ISING_ONE) zero = thr_up != 0;
+    if constexpr (KIND == KIND_ISING_ONE)
+        if (zero) half_item<KIND_ISING_ONE_ZERO, DIM, D, false>(a, rg, item, ln, lut, xch, thr_up, thr_down, o);
+    if (!zero) half_item<KIND, DIM, D, false>(a, rg, item, ln, lut, xch, thr_up, thr_down, o);
     int32_t bond, mag, acc, unfl;
     finish_obs<KIND, DIM>(o, bond, mag, acc, unfl);
     block_accumulate(bond, mag, acc, unfl, J.acc + (uint64_t)(dj[1] + step) * kSlotWords);
@@ -78,16 +82,16 @@ __device__ __forceinline__ void batch_walk_body(const BatchJob& J, const uint32_
 
 template <int KIND, int DIM, int D>
 __device__ __forceinline__ void batch_rows_body(const BatchJob& J, const uint32_t* dj, const BatchWG w, uint32_t colour,
-                                                uint32_t step, RowLuts& lut)
+                                                uint32_t step, RowLuts& lut, LanePart& part)
 {
     const SweepArgs a = job_sweep_args(J, dj, colour, step);
     const RowGeom rg = *reinterpret_cast<const RowGeom*>(J.rg_words);
     Obs o = {};
     const Lanes ln = lanes_of(rg, false);
-    rows_run<KIND, DIM, D, kRagNone>(a, rg, w.item_base + ln.wave * rg.K, ln, J.table, lut, o);
-    int32_t bond, mag, acc, unfl;
-    finish_obs<KIND, DIM>(o, bond, mag, acc, unfl);
-    block_accumulate(bond, mag, acc, unfl, J.acc + (uint64_t)(dj[1] + step) * kSlotWords);
+    rows_run<KIND, DIM, D, kRagNone>(a, rg, w.item_base + ln.wave * rg.K, ln, J.table, lut, part, o);
+    int32_t v[kQ];
+    finish_obs<KIND, DIM>(o, v[0], v[1], v[2], v[3]);
+    lane_accumulate<rows_quantities<KIND>()>(v, part, J.acc + (uint64_t)(dj[1] + step) * kSlotWords);
 }
 
 // 2D jobs with two copies: the whole sweep, reading copy cur and writing the
@@ -107,7 +111,14 @@ __device__ __forceinline__ void batch_fused_body(const BatchJob& J, const uint32
     Obs o = {};
     const Lanes ln = lanes_of(rg, false);
     const uint32_t item = ln.slot < rg.slots ? w.item_base + ln.wave * rg.slots + ln.slot : 0xFFFFFFFFu;
-    fused_item<KIND, D, false, 0>(a, rg, item, ln, lut, xch, thr_up, thr_down, a.col[0], a.col[1], N0, N1, o);
+    bool zero = false;
+    if constexpr (KIND == KIND_ISING_ONE) zero = thr_up != 0;
+    if constexpr (KIND == KIND_ISING_ONE)
+        if (zero)
+            fused_item<KIND_ISING_ONE_ZERO, D, false, 0>(a, rg, item, ln, lut, xch, thr_up, thr_down, a.col[0],
+                                                         a.col[1], N0, N1, o);
+    if (!zero)
+        fused_item<KIND, D, false, 0>(a, rg, item, ln, lut, xch, thr_up, thr_down, a.col[0], a.col[1], N0, N1, o);
     int32_t bond, mag, acc, unfl;
     finish_obs<KIND, 2>(o, bond, mag, acc, unfl);
     block_accumulate(bond, mag, acc, unfl, J.acc + (uint64_t)(dj[1] + step) * kSlotWords);
@@ -129,8 +140,13 @@ __device__ __forceinline__ void batch_window_body(const BatchJob& J, const uint3
     block_accumulate(o.bond, o.mag, o.acc, o.unfl, J.acc + (uint64_t)(dj[1] + step) * kSlotWords);
 }
 
+struct RowsLds {
+    RowLuts lut;
+    LanePart part;
+};
 union BatchLds {
     RowLuts row;
+    RowsLds rows;
     streamk::Luts win;
 };
 
@@ -151,9 +167,9 @@ __device__ __forceinline__ void dispatch(uint32_t v, const BatchJob& J, const ui
             if (v == kBvWindow) batch_window_body<KIND, DIM>(J, dj, w, colour, step, lds.win);
         }
     } else if constexpr (FAM == kFamRows || FAM == kFamRowsOne) {
-        if (v == kBvRowsD4) batch_rows_body<KIND, DIM, 4>(J, dj, w, colour, step, lds.row);
-        else if (v == kBvRowsD2) batch_rows_body<KIND, DIM, 2>(J, dj, w, colour, step, lds.row);
-        else if (v == kBvRowsD1) batch_rows_body<KIND, DIM, 1>(J, dj, w, colour, step, lds.row);
+        if (v == kBvRowsD4) batch_rows_body<KIND, DIM, 4>(J, dj, w, colour, step, lds.rows.lut, lds.rows.part);
+        else if (v == kBvRowsD2) batch_rows_body<KIND, DIM, 2>(J, dj, w, colour, step, lds.rows.lut, lds.rows.part);
+        else if (v == kBvRowsD1) batch_rows_body<KIND, DIM, 1>(J, dj, w, colour, step, lds.rows.lut, lds.rows.part);
     } else if constexpr (DIM == 2) {
         if (v == kBvFusedD2) batch_fused_body<KIND, 2>(J, dj, w, step, lds.row, xch);
         else if (v == kBvFusedD1) batch_fused_body<KIND, 1>(J, dj, w, step, lds.row, xch);

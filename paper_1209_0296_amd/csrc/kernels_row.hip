@@ -20,7 +20,11 @@ __global__ void __launch_bounds__(1024) k_row_half(SweepArgs a, RowGeom rg)
     Obs o = {};
     const Lanes ln = lanes_of(rg, XW);
     const uint32_t item = row_item(rg, XW, ln);
-    half_item<KIND, DIM, D, XW>(a, rg, item, ln, lut, xch, thr_up, thr_down, o);
+    bool zero = false;
+    if constexpr (KIND == KIND_ISING_ONE) zero = thr_up != 0;  // tables with a zero threshold
+    if constexpr (KIND == KIND_ISING_ONE)
+        if (zero) half_item<KIND_ISING_ONE_ZERO, DIM, D, XW>(a, rg, item, ln, lut, xch, thr_up, thr_down, o);
+    if (!zero) half_item<KIND, DIM, D, XW>(a, rg, item, ln, lut, xch, thr_up, thr_down, o);
     int32_t bond, mag, acc, unfl;
     finish_obs<KIND, DIM>(o, bond, mag, acc, unfl);
     block_accumulate(bond, mag, acc, unfl, a.acc);
@@ -40,7 +44,12 @@ __global__ void __launch_bounds__(1024) k_row_fused(SweepArgs a, RowGeom rg, con
     Obs o = {};
     const Lanes ln = lanes_of(rg, XW);
     const uint32_t item = row_item(rg, XW, ln);
-    fused_item<KIND, D, XW, HT>(a, rg, item, ln, lut, xch, thr_up, thr_down, S0, S1, D0, D1, o);
+    bool zero = false;
+    if constexpr (KIND == KIND_ISING_ONE) zero = thr_up != 0;  // tables with a zero threshold
+    if constexpr (KIND == KIND_ISING_ONE)
+        if (zero)
+            fused_item<KIND_ISING_ONE_ZERO, D, XW, 0>(a, rg, item, ln, lut, xch, thr_up, thr_down, S0, S1, D0, D1, o);
+    if (!zero) fused_item<KIND, D, XW, HT>(a, rg, item, ln, lut, xch, thr_up, thr_down, S0, S1, D0, D1, o);
     int32_t bond, mag, acc, unfl;
     finish_obs<KIND, 2>(o, bond, mag, acc, unfl);
     block_accumulate(bond, mag, acc, unfl, a.acc);

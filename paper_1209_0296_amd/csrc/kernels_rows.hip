@@ -13,16 +13,18 @@ namespace {
 // parities; rg.nitems those of the launch.  rg.K row sets per wave; the block
 // has blockDim.x / 64 waves.
 template <int KIND, int DIM, int D, int RAGS>
-__global__ void __launch_bounds__(1024) k_rows_half(SweepArgs a, RowGeom rg)
+__global__ void __launch_bounds__(1024, KIND == KIND_ISING_HALF && RAGS == kRagNone ? 8 : 4)
+    k_rows_half(SweepArgs a, RowGeom rg)
 {
     __shared__ RowLuts lut;
+    __shared__ LanePart part;
     Obs o = {};
     const Lanes ln = lanes_of(rg, false);
-    const uint32_t it0 = (remap_block() * (blockDim.x >> 6) + ln.wave) * rg.K;
-    rows_run<KIND, DIM, D, RAGS>(a, rg, it0, ln, a.lut, lut, o);
-    int32_t bond, mag, acc, unfl;
-    finish_obs<KIND, DIM>(o, bond, mag, acc, unfl);
-    block_accumulate(bond, mag, acc, unfl, a.acc);
+    const uint32_t it0 = (xcd_item(blockIdx.x, gridDim.x) * (blockDim.x >> 6) + ln.wave) * rg.K;
+    rows_run<KIND, DIM, D, RAGS>(a, rg, it0, ln, a.lut, lut, part, o);
+    int32_t v[kQ];
+    finish_obs<KIND, DIM>(o, v[0], v[1], v[2], v[3]);
+    lane_accumulate<rows_quantities<KIND>()>(v, part, a.acc);
 }
 
 // Ragged rows get kernels of their own, so that the others carry no code for

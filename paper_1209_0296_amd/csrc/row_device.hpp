@@ -28,7 +28,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "pair_lut.hpp"
+#include "accept.hpp"
+#include "block_order.hpp"
 #include "philox.hpp"
 #include "site_update.hpp"
 #include "spinlat_internal.h"
@@ -65,14 +66,6 @@ __device__ __forceinline__ uint32_t wrapr(int y, uint32_t L)
 __device__ __forceinline__ uint32_t wrap1(int y, uint32_t L)
 {
     return (uint32_t)(y < 0 ? y + (int)L : (y >= (int)L ? y - (int)L : y));
-}
-
-__device__ __forceinline__ uint32_t remap_block()
-{
-    const uint32_t nb = gridDim.x;
-    uint32_t b = blockIdx.x;
-    if ((nb & 7u) == 0) b = (b & 7u) * (nb >> 3) + (b >> 3);
-    return b;
 }
 
 template <int D>
@@ -176,41 +169,37 @@ __device__ __forceinline__ uint32_t edge_words(const Vec<D>& q, const RowGeom& r
     return 0u;
 }
 
+// Spin-1 with zero thresholds in the table (very low temperature).
+constexpr int KIND_ISING_ONE_ZERO = 4;
+constexpr bool spin_one(int kind) { return kind == KIND_ISING_ONE || kind == KIND_ISING_ONE_ZERO; }
+
 // ---- tables ---------------------------------------------------------------
 union RowLuts {
     PairLut pair;            // spin-1/2 and coupled NE
-    uint64_t e[3 * 2 * 13];  // spin-1
+    OneLut one;              // spin-1
 };
 
 // Kernel kind of NE lattices with the Ising coupling: the NE code paths (every
 // kind other than the two Ising ones), with the spin-1/2 table and move.
 constexpr int KIND_NE_COUPLED = 3;
 
+// Tables in LDS (the caller's barrier follows) and the two NE thresholds.  For
+// spin-1, thr_up tells whether the table has a zero threshold (the runtime
+// sends other kinds' tables with one elsewhere).
 template <int KIND, int DIM>
 __device__ __forceinline__ void build_row_luts(RowLuts& lut, const uint64_t* table, uint64_t& thr_up,
                                                uint64_t& thr_down)
 {
-    constexpr int z = 2 * DIM;
-    if constexpr (KIND == KIND_ISING_HALF || KIND == KIND_NE_COUPLED) {
-        build_pair_lut<KIND == KIND_NE_COUPLED, DIM>(lut.pair, table);
-    } else if constexpr (KIND == KIND_ISING_ONE) {
-        for (int t = threadIdx.x; t < 6 * (2 * z + 1); t += blockDim.x) {
-            const int nz = t % (2 * z + 1);
-            const int ch = (t / (2 * z + 1)) & 1;
-            const int s = t / (2 * (2 * z + 1)) - 1;
-            const int av = (s == -1) ? 0 : -1;
-            const int bv = (s == 1) ? 0 : 1;
-            const int sp = ch ? bv : av;
-            const uint64_t thr = table[ds_index(sp - s) * (2 * z + 1) + nz];
-            lut.e[t] = thr | ((uint64_t)(uint32_t)(sp + 1) << 40);
-        }
-    }
     thr_up = table[0];
     thr_down = table[1];
+    if constexpr (KIND == KIND_ISING_HALF || KIND == KIND_NE_COUPLED)
+        build_pair_lut<KIND == KIND_NE_COUPLED, DIM>(lut.pair, table);
+    else if constexpr (KIND == KIND_ISING_ONE)
+        thr_up = build_one_lut<DIM>(lut.one, table) ? 1u : 0u;
 }
 
 struct Obs {
-    int32_t acc;   // accepted moves; spin-1/2: sum of s s' over the counted words
+    int32_t acc;   // accepted moves; spin-1/2: sum of s s' over the counted words; spin-1: 8 x accepted
     int32_t n;     // spin-1/2: counted words
     int32_t mag0;  // sum of s (NE: n) over colour-0 words
     int32_t mag1;  // same over colour-1 words
@@ -223,7 +212,7 @@ template <int KIND>
 __device__ __forceinline__ uint32_t prep(uint32_t w)
 {
     if constexpr (KIND == KIND_ISING_HALF) return w & 0x02020202u;
-    else if constexpr (KIND == KIND_ISING_ONE) return (w ^ 0x80808080u) + 0x80808081u;  // s+1, no carries
+    else if constexpr (spin_one(KIND)) return (w ^ 0x80808080u) + 0x80808081u;  // s+1, no carries
     else return w & 0x01010101u;
 }
 
@@ -246,30 +235,6 @@ __device__ __forceinline__ uint32_t half_word(uint32_t own, uint32_t nd2, const 
 {
     const uint32_t idx = nd2 | (own & 0x10101010u);  // twice the table number
     return own ^ pair_accept<4, 68>(lut, idx, w, 0xFEFEFEFEu, [] {});
-}
-
-// spin-1: S = per-byte nsum + z
-template <int DIM>
-__device__ __forceinline__ uint32_t one_word(uint32_t own, uint32_t S, const Words4& wa, const Words4& wb,
-                                             const RowLuts& lut, int& nacc)
-{
-    constexpr int z = 2 * DIM;
-    const uint32_t ob = prep<KIND_ISING_ONE>(own);
-    uint32_t out = 0;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        const Words4& w = b < 2 ? wa : wb;
-        const uint32_t ua = w.w[(b & 1) * 2];
-        const uint32_t up = w.w[(b & 1) * 2 + 1];
-        const uint32_t s1 = (ob >> (8 * b)) & 0xFFu;
-        const uint32_t nz = (S >> (8 * b)) & 0xFFu;
-        const uint64_t ent = lut.e[(s1 * 2 + (up >> 31)) * (2 * z + 1) + nz];
-        const bool acc = (uint64_t)ua < (ent & 0x1FFFFFFFFull);
-        const uint32_t n1 = acc ? (uint32_t)(ent >> 40) : s1;
-        nacc += acc ? 1 : 0;
-        out |= ((n1 - 1u) & 0xFFu) << (8 * b);
-    }
-    return out;
 }
 
 // NE constraint on the Ising energy (Sec. 3.2 with J != 0): a site whose north
@@ -328,13 +293,13 @@ __device__ __forceinline__ Vec<D> row_update(const Vec<D>& own, const Vec<D>& sa
                                              uint32_t uncounted = 0)
 {
     // pre: the words' Philox outputs (spin-1: two per word), when the caller drew them
-    static_assert(!RAG || KIND == KIND_ISING_HALF || KIND == KIND_ISING_ONE, "ragged rows: Ising kinds");
+    static_assert(!RAG || KIND == KIND_ISING_HALF || spin_one(KIND), "ragged rows: Ising kinds");
     constexpr int z = 2 * DIM;
     Vec<D> out;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
         const uint32_t g = g0 + d;
-        if constexpr (KIND == KIND_ISING_HALF || KIND == KIND_ISING_ONE) {
+        if constexpr (KIND == KIND_ISING_HALF || spin_one(KIND)) {
             uint32_t S = same.w[d] + side[d] + up.w[d] + down.w[d];
             if constexpr (DIM == 3) S += zm->w[d] + zp->w[d];
             if constexpr (KIND == KIND_ISING_HALF) {
@@ -360,16 +325,17 @@ __device__ __forceinline__ Vec<D> row_update(const Vec<D>& own, const Vec<D>& sa
             } else {
                 const Words4 wa = pre ? pre[2 * d] : philox4x32_10(2 * g, colour, t, 0u, ks);
                 const Words4 wb = pre ? pre[2 * d + 1] : philox4x32_10(2 * g + 1, colour, t, 0u, ks);
-                int nacc = 0;
-                out.w[d] = one_word<DIM>(own.w[d], S, wa, wb, lut, nacc);
+                uint32_t f;
+                out.w[d] = spin_of(one_move<DIM, KIND == KIND_ISING_ONE_ZERO>(
+                    prep<KIND>(own.w[d]), S, wa, wb, lut.one, f, [] {}));
                 if (count) {
                     uint32_t ow = out.w[d];
                     if constexpr (RAG) {
                         const uint32_t m = (uint32_t)d < uncounted ? 0u : ~0u;
                         ow &= m;
-                        nacc &= (int)m;
+                        f &= m;
                     }
-                    o.acc += nacc;
+                    o.acc += __builtin_popcount(f);
                     if (colour == 0) {
                         o.mag0 = dot4(ow, 0x01010101u, o.mag0);
                     } else {
@@ -411,10 +377,10 @@ __device__ __forceinline__ void finish_obs(const Obs& o, int32_t& bond, int32_t&
         mag = o.mag0 + o.mag1;
         acc = (4 * o.n - o.acc) >> 1;  // s s' = 1 - 2 (flipped)
         unfl = 0;
-    } else if constexpr (KIND == KIND_ISING_ONE) {
+    } else if constexpr (spin_one(KIND)) {
         bond = o.dd - z * o.mag1;  // dd = sum s' (nsum + z)
         mag = o.mag0 + o.mag1;
-        acc = o.acc;
+        acc = o.acc >> 3;
         unfl = 0;
     } else {
         bond = o.dd;
@@ -451,7 +417,7 @@ __device__ __forceinline__ Lanes lanes_of(const RowGeom& rg, bool xw)
 // Item (strip, plane) of this lane, or >= nitems if idle.
 __device__ __forceinline__ uint32_t row_item(const RowGeom& rg, bool xw, const Lanes& ln)
 {
-    const uint32_t b = remap_block();
+    const uint32_t b = xcd_item(blockIdx.x, gridDim.x);
     if (xw) return b;
     if (ln.slot >= rg.slots) return 0xFFFFFFFFu;
     return (b * (blockDim.x >> 6) + ln.wave) * rg.slots + ln.slot;

@@ -18,8 +18,9 @@
 // after the other, so every lane updates four words per launch whatever the
 // row width.  (Measured and dropped: waves that load the next row set while
 // updating the current one were slower at every depth, and so was issuing the
-// first set's loads before the threshold table is built: the loaded words
-// live across the table build and the registers cut the waves per SIMD.)
+// first set's loads before the threshold table is built, although the kernel
+// keeps 8 waves per SIMD with it: 3D L = 256 16.9 us per sweep against 16.1,
+// 512 92 against 87.)
 #pragma once
 #include "row_device.hpp"
 
@@ -48,6 +49,13 @@ __device__ __forceinline__ RowsAt rows_at(const RowGeom& rg, uint32_t it, uint32
     return r;
 }
 
+// Byte offset of this lane's words in its plane: 32 bits, beside a
+// wave-uniform plane base, so that a load's address is one register.
+__device__ __forceinline__ uint32_t plane_offset(const RowGeom& rg, const RowsAt& at, const Lanes& ln)
+{
+    return at.y * rg.Lh + 4u * ln.col0;
+}
+
 template <int DIM, int D>
 __device__ __forceinline__ void rows_load(RowsIn<DIM, D>& in, const SweepArgs& a, const RowGeom& rg, const RowsAt& at,
                                           const Lanes& ln)
@@ -55,20 +63,18 @@ __device__ __forceinline__ void rows_load(RowsIn<DIM, D>& in, const SweepArgs& a
     if (!at.ok) return;
     const uint32_t L = rg.L, z = at.z, y = at.y;
     const uint32_t c = a.colour;
-    const uint8_t* O = colour_array(a, c ^ 1u);
-    const uint64_t rowb = rg.Lh;
-    // one byte offset for the row, the neighbour rows as signed steps from it
-    // (the periodic wrap as a select); the plane steps are wave-uniform
-    const int64_t base = (int64_t)(((uint64_t)z * L + y) * rowb + 4ull * ln.col0);
-    const int64_t ystep = (int64_t)rowb, ywrap = (int64_t)(L - 1) * (int64_t)rowb;
-    in.own = ldv<D>(colour_array(a, c), (uint64_t)base);
-    in.o0 = ldv<D>(O, (uint64_t)base);
-    in.om = ldv<D>(O, (uint64_t)(base + (y == 0 ? ywrap : -ystep)));
-    in.op = ldv<D>(O, (uint64_t)(base + (y + 1 == L ? -ywrap : ystep)));
+    const uint64_t planeb = (uint64_t)L * rg.Lh;
+    const uint8_t* O = colour_array(a, c ^ 1u) + z * planeb;
+    const uint32_t off = plane_offset(rg, at, ln);
+    const uint32_t wrap = (L - 1) * rg.Lh;
+    in.own = ldv<D>(colour_array(a, c) + z * planeb, off);
+    in.o0 = ldv<D>(O, off);
+    in.om = ldv<D>(O, y == 0 ? off + wrap : off - rg.Lh);
+    in.op = ldv<D>(O, y + 1 == L ? off - wrap : off + rg.Lh);
     if constexpr (DIM == 3) {
-        const int64_t zstep = (int64_t)L * ystep, zwrap = (int64_t)(L - 1) * zstep;
-        in.zm = ldv<D>(O, (uint64_t)(base + (z == 0 ? zwrap : -zstep)));
-        in.zp = ldv<D>(O, (uint64_t)(base + (z + 1 == L ? -zwrap : zstep)));
+        const int64_t zwrap = (int64_t)(L - 1) * (int64_t)planeb;
+        in.zm = ldv<D>(O + (z == 0 ? zwrap : -(int64_t)planeb), off);
+        in.zp = ldv<D>(O + (z + 1 == L ? -zwrap : (int64_t)planeb), off);
     }
 }
 
@@ -79,8 +85,8 @@ __device__ __forceinline__ void rows_update(const RowsIn<DIM, D>& in, const Swee
                                             const RowLuts& lut, uint64_t thr_up, uint64_t thr_down, Obs& o,
                                             const Words4* pre)
 {
-    const uint64_t row = (uint64_t)at.z * rg.L + at.y;
-    const uint64_t cb = 4ull * ln.col0;
+    const uint32_t off = plane_offset(rg, at, ln);
+    const uint64_t planeb = (uint64_t)rg.L * rg.Lh;
     const Vec<D> q0 = prepv<KIND, D>(in.o0);
     uint32_t last, first;
     const uint32_t uncounted = edge_words<D, P, RAG>(q0, rg, ln, last, first);
@@ -94,10 +100,17 @@ __device__ __forceinline__ void rows_update(const RowsIn<DIM, D>& in, const Swee
         qzm = prepv<KIND, D>(in.zm);
         qzp = prepv<KIND, D>(in.zp);
     }
-    const uint32_t g0 = (uint32_t)(row * rg.ncols + ln.col0);
+    const uint32_t g0 = at.z * (uint32_t)(planeb >> 2) + (off >> 2);
     const Vec<D> nw = row_update<KIND, DIM, D, P, RAG>(in.own, q0, side, qm, qp, &qzm, &qzp, g0, a.colour, a.t, ks,
                                                        lut, thr_up, thr_down, true, o, pre, uncounted);
-    stv<D>(colour_array(a, a.colour), row * rg.Lh + cb, nw);
+    stv<D>(colour_array(a, a.colour) + at.z * planeb, off, nw);
+}
+
+// Record quantities of a kind (Ising lattices have no persistence).
+template <int KIND>
+constexpr int rows_quantities()
+{
+    return KIND == KIND_ISING_HALF || spin_one(KIND) ? 3 : kQ;
 }
 
 // Ragged-row handling of a kernel: none, or every row (rg.rag != 0).  Each
@@ -115,11 +128,11 @@ __device__ __forceinline__ void rows_step(const RowsIn<DIM, D>& in, const SweepA
     // are drawn here, before the first use of the loaded rows, while the loads
     // are still in flight (the scheduling barrier keeps that order).  Spin-1
     // with four words per lane would hold 32 words and spill: it draws late.
-    constexpr bool kPre = KIND == KIND_ISING_HALF || (KIND == KIND_ISING_ONE && D <= 2);
-    constexpr int kCalls = KIND == KIND_ISING_ONE ? 2 : 1;  // Philox calls per word
+    constexpr bool kPre = KIND == KIND_ISING_HALF || (spin_one(KIND) && D <= 2);
+    constexpr int kCalls = spin_one(KIND) ? 2 : 1;  // Philox calls per word
     Words4 pre[kPre ? kCalls * D : 1];
     if constexpr (kPre) {
-        const uint32_t g0 = (uint32_t)(((uint64_t)at.z * rg.L + at.y) * rg.ncols + ln.col0);
+        const uint32_t g0 = at.z * (rg.L * rg.ncols) + (plane_offset(rg, at, ln) >> 2);
 #pragma unroll
         for (int i = 0; i < kCalls * D; ++i) pre[i] = philox4x32_10(kCalls * g0 + i, a.colour, a.t, 0u, ks);
         __builtin_amdgcn_sched_barrier(0);
@@ -128,7 +141,7 @@ __device__ __forceinline__ void rows_step(const RowsIn<DIM, D>& in, const SweepA
     // the row parity is uniform across the wave: every row of a row set has
     // the parity of rem & 1
     const bool p1 = ((at.y + at.z + a.colour) & 1u) != 0;
-    constexpr bool kRag = D > 1 && (KIND == KIND_ISING_HALF || KIND == KIND_ISING_ONE) && RAGS == kRagAll;
+    constexpr bool kRag = D > 1 && (KIND == KIND_ISING_HALF || spin_one(KIND)) && RAGS == kRagAll;
     if constexpr (kRag) {
         if (!p1) rows_update<KIND, DIM, D, 0, kRag>(in, a, rg, at, ln, ks, lut, thr_up, thr_down, o, pw);
         else rows_update<KIND, DIM, D, 1, kRag>(in, a, rg, at, ln, ks, lut, thr_up, thr_down, o, pw);
@@ -152,15 +165,10 @@ inline bool make_rows_geom(const Geom& g, int D, int waves, RowGeom& rg, bool ra
     return true;
 }
 
-// Row sets it0 .. it0 + K - 1 of one wave (it0 wave-uniform, K = 4 / D).  Every thread of
-// the block calls this: the table build inside ends in a workgroup barrier.
 template <int KIND, int DIM, int D, int RAGS>
-__device__ __forceinline__ void rows_run(const SweepArgs& a, const RowGeom& rg, uint32_t it0, const Lanes& ln,
-                                         const uint64_t* table, RowLuts& lut, Obs& o)
+__device__ __forceinline__ void rows_sets(const SweepArgs& a, const RowGeom& rg, uint32_t it0, const Lanes& ln,
+                                          const RowLuts& lut, uint64_t thr_up, uint64_t thr_down, Obs& o)
 {
-    uint64_t thr_up, thr_down;
-    build_row_luts<KIND, DIM>(lut, table, thr_up, thr_down);
-    lds_barrier();
     const PhiloxKey ks = philox_schedule(a.key0, a.key1);
     constexpr uint32_t K = 4 / D;  // rg.K
     if constexpr (D == 1) {
@@ -185,6 +193,26 @@ __device__ __forceinline__ void rows_run(const SweepArgs& a, const RowGeom& rg, 
             rows_step<KIND, DIM, D, RAGS>(in, a, rg, at, ln, ks, lut, thr_up, thr_down, o);
         }
     }
+}
+
+// Row sets it0 .. it0 + K - 1 of one wave (it0 wave-uniform, K = 4 / D).  Every thread of
+// the block calls this: the table build inside ends in a workgroup barrier,
+// which also publishes the cleared `part` of the workgroup reduction.
+template <int KIND, int DIM, int D, int RAGS>
+__device__ __forceinline__ void rows_run(const SweepArgs& a, const RowGeom& rg, uint32_t it0, const Lanes& ln,
+                                         const uint64_t* table, RowLuts& lut, LanePart& part, Obs& o)
+{
+    uint64_t thr_up, thr_down;
+    clear_part(part);
+    build_row_luts<KIND, DIM>(lut, table, thr_up, thr_down);
+    lds_barrier();
+    if constexpr (KIND == KIND_ISING_ONE) {
+        if (thr_up) {  // a zero threshold
+            rows_sets<KIND_ISING_ONE_ZERO, DIM, D, RAGS>(a, rg, it0, ln, lut, thr_up, thr_down, o);
+            return;
+        }
+    }
+    rows_sets<KIND, DIM, D, RAGS>(a, rg, it0, ln, lut, thr_up, thr_down, o);
 }
 
 }  // namespace rowk

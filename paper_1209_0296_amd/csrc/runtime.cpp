@@ -112,20 +112,18 @@ bool lut32_ok(const sl_lattice* h)
 //   - 2D L = 4096: fused, 4-row strips, 2 words (spin-1/2: 14.2; NE: 8-row
 //     strips, 1 word, 17.1 against 17.6); from L = 8192 16-row strips with 2
 //     words per lane (8192: spin-1/2 36.6 against 38.2 with 8 rows and 4
-//     words, 41.1 with 32 rows; spin-1 68.3 against 80.7 with 4 rows; NE 48.0
-//     against 51.8 with 4 rows; coupled NE 41.9 against 47.0 with 4 rows),
-//     spin-1/2 from L = 16384 32-row strips with 4 words (132 against 150 with
-//     16 rows and 2 words; 32768: 538 against 569 with 16 rows and 4 words);
-//   - 3D: half-sweeps by independent row groups with 4 words per lane (L =
-//     256: 18.4 against 19.2 for the walk with 4-row strips; L = 64: 7.4
-//     against 8.8 with 2 words and 9.8 with 1; L = 128: 7.7 against 10.0 with
-//     1), also when 4 does not divide the row (Ising rows may be ragged: L =
-//     136: 8.7 against 13.0 with 1 word; L = 200: 13.1 against 22.1; spin-1
-//     at 200: 18.2 against 25.6); spin-1/2 takes blocks of 8 waves from L =
-//     256 (17.3 against 17.6 with 4), else 4 (L = 128: 7.7 against 8.6;
-//     spin-1 at 256: 24.7 against 24.9).
-// A fused 3D sweep would recompute a halo in two directions, so 3D uses
-// half-sweeps.  Other widths are tried in order when a row does not fit, and
+//     words, 41.1 with 32 rows; NE 48.0 against 51.8 with 4 rows; coupled NE
+//     41.9 against 47.0 with 4 rows), spin-1 8-row strips (62.3 against 63.8
+//     with 16 rows), Ising from L = 16384 32-row strips with 4 words (spin-1/2
+//     132 against 150 with 16 rows and 2 words, 32768: 538 against 569 with 16
+//     rows and 4 words; spin-1 213 against 238);
+//   - 3D: half-sweeps by independent row groups with 4 words per lane (fewest
+//     waves; L = 128: 7.7 against 10.0 with 1), also when 4 does not divide the
+//     row (Ising rows may be ragged: L = 136: 8.7 against 13.0 with 1 word);
+//     blocks of 4 waves, spin-1/2 16 at L = 256, where two of them fill a CU
+//     (16.1 against 16.4 with 8 and 17.0 with 4), and 8 above (512: 81 against
+//     87 with 4 or 16); spin-1 at 256: 22.1 with 4, 22.3 with 8.
+// Other widths are tried in order when a row does not fit, and
 // shapes the whole-row kernels cannot take fall back to the window kernels.
 constexpr uint64_t kResidentAuto = 16 * 1024;
 
@@ -149,7 +147,7 @@ sl_launch row_launch(const sl_lattice* h)
     sl_launch l{};
     if (h->params.dim == 3) {
         const int Ds[3] = {4, 2, 1};
-        const int waves = L >= 256 && half_spin ? 8 : 4;
+        const int waves = L >= 256 && half_spin ? (L == 256 ? 16 : 8) : 4;
         for (int D : Ds)
             if (rows_supported(g, h->kind, waves, D, lut32_ok(h))) {
                 l.mode = SL_MODE_HALF_ROWS;
@@ -177,8 +175,11 @@ sl_launch row_launch(const sl_lattice* h)
     } else if (L < 8192) {
         H = 4;
         Ds[0] = 2, Ds[1] = 4, Ds[2] = 1;
-    } else if (L >= 16384 && half_spin) {
+    } else if (L >= 16384 && (half_spin || h->kind == KIND_ISING_ONE)) {
         H = 32;
+    } else if (h->kind == KIND_ISING_ONE) {
+        H = 8;
+        Ds[0] = 2, Ds[1] = 4, Ds[2] = 1;
     } else {
         H = 16;
         Ds[0] = 2, Ds[1] = 4, Ds[2] = 1;
@@ -203,18 +204,28 @@ sl_launch row_launch(const sl_lattice* h)
 // and 12.5; 6144: 35.2 and 26.6; 8200: 77.7 and 48.4; 3D L = 64: 8.0 and 2.8;
 // 128: 8.7 and 5.9.  Not for lattices of L >= 8192 whose rows fit the fused
 // kernels (8192: spin-1/2 36.6 against 45.7, spin-1 68.0 and 71.9, coupled NE
-// 41.9 and 51.5, NE 48.0 and 48.5), nor for 3D lattices above L = 128, where
-// the halo costs more than the launches (160: 10.7 against 13.1).  Zero
-// thresholds need the kernels with 64-bit tables.
-sl_launch auto_launch(const sl_lattice* h, TilePlan* tile)
+// 41.9 and 51.5, NE 48.0 and 48.5).  3D lattices above L = 128, where a tile's
+// halo costs more than the launches, walk along z with both colours per launch
+// (plane_device.hpp; spin-1/2 L = 136: 9.8 against 6.8; 232: 19.6 and 14.8;
+// 264: 23.4 and 18.1; spin-1 200: 17.4 and 16.0), but not L = 256, whose rows
+// fill the row groups' waves (spin-1/2 16.1 against 16.9, spin-1 22.1 and
+// 24.8), nor from L = 512 (81 against 82).  Zero thresholds need the kernels
+// with 64-bit tables.
+sl_launch auto_launch(const sl_lattice* h, TilePlan* tile, PlaneGeom* plane)
 {
     *tile = TilePlan{};
+    *plane = PlaneGeom{};
     if (is_sub_lattice(h->params.model)) return sl_launch{};
     const sl_launch l = row_launch(h);
     const bool ising = h->params.model == SL_ISING, coupled = h->params.model == SL_NE_COUPLED;
     if ((ising || coupled) && !lut32_ok(h)) return l;
-    if (h->params.dim == 3 ? h->params.L > 128 : h->params.L >= 8192 && l.mode == SL_MODE_FUSED) return l;
-    *tile = tile_plan(args_of(h).g, h->kind, coupled);
+    const Geom g = args_of(h).g;
+    if (h->params.dim == 3 && h->params.L > 128) {
+        if (h->params.L < 512 && h->params.L != 256 && !plane_plan(g, h->kind, *plane)) *plane = PlaneGeom{};
+        return l;
+    }
+    if (h->params.L >= 8192 && l.mode == SL_MODE_FUSED) return l;
+    *tile = tile_plan(g, h->kind, coupled);
     return l;
 }
 
@@ -406,6 +417,27 @@ sl_status enqueue_sweeps(sl_lattice* h, uint64_t n)
         h->pending += n;
         return SL_OK;
     }
+    if (h->plane.L) {
+        for (uint64_t i = 0; i < n; ++i) {
+            const int nxt = h->cur ^ 1;
+            uint8_t* d0 = h->base + h->lay.off_col[nxt][0];
+            uint8_t* d1 = h->base + h->lay.off_col[nxt][1];
+            a.t = (uint32_t)(h->next_t + i);
+            a.acc = slot_ptr(h, h->pending + i);
+            const hipError_t e = launch_plane(a, h->kind, h->plane, d0, d1, h->stream);
+            if (e != hipSuccess) {
+                h->next_t += i;
+                h->pending += i;
+                return hip_fail(e, "plane walk launch");
+            }
+            h->cur = nxt;
+            a.col[0] = d0;
+            a.col[1] = d1;
+        }
+        h->next_t += n;
+        h->pending += n;
+        return SL_OK;
+    }
     if (h->launch.mode == SL_MODE_RESIDENT) {
         for (uint64_t i = 0; i < n;) {
             const uint32_t k = (uint32_t)std::min<uint64_t>(n - i, kResidentChunk);
@@ -528,7 +560,7 @@ sl_status sl_create_lattice(const sl_params* params, void* device_buf, size_t by
     h->first_t = params->t0;
     h->cur = 0;
     h->table_n = build_table(params, h->table);
-    h->launch = auto_launch(h, &h->tile);
+    h->launch = auto_launch(h, &h->tile, &h->plane);
     h->stage = nullptr;
     hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&h->stage),
                                  params->record_capacity * sizeof(sl_record), hipHostMallocDefault);
@@ -577,13 +609,15 @@ sl_status sl_set_launch(sl_lattice* h, const sl_launch* launch)
     if (!h || !launch) return fail(SL_E_INVALID, "NULL argument");
     sl_launch l = *launch;
     TilePlan tile{};
+    PlaneGeom plane{};
     const bool chosen = l.mode == SL_MODE_AUTO && !is_sub_lattice(h->params.model);
-    if (chosen) l = auto_launch(h, &tile);
+    if (chosen) l = auto_launch(h, &tile, &plane);
     sl_status st = check_launch(h, &l);
     if (st != SL_OK) return st;
     if (!chosen && l.mode == SL_MODE_RESIDENT) tile = resident_tile(h);
     h->launch = l;
     h->tile = tile;
+    h->plane = plane;
     return SL_OK;
 }
 

@@ -7,6 +7,7 @@
 
 #include "../../include/spinlat.h"
 #include "host_common.h"
+#include "plane_plan.h"
 #include "spinlat_internal.h"
 #include "tile_plan.h"
 
@@ -24,6 +25,7 @@ struct sl_lattice {
     int cur;           // copy of the lattice holding the current state
     sl_launch launch;
     spinlat::TilePlan tile;  // k != 0: sweeps run as tile launches (the default schedule only)
+    spinlat::PlaneGeom plane;  // L != 0: 3D sweeps run as walks along z (the default schedule only)
     uint64_t table[spinlat::kMaxLut];
     size_t table_n;
     sl_record* stage;  // pinned host staging for record readback (record_capacity)
@@ -37,7 +39,7 @@ constexpr uint64_t kResidentChunk = 4096;  // sweeps per resident launch at most
 SweepArgs args_of(const sl_lattice* h);
 unsigned long long* slot_ptr(const sl_lattice* h, uint64_t idx);  // record ring slot
 // Default schedule; the tile plan beside it (k = 0: none) goes to *tile.
-sl_launch auto_launch(const sl_lattice* h, TilePlan* tile);
+sl_launch auto_launch(const sl_lattice* h, TilePlan* tile, PlaneGeom* plane);
 sl_status enqueue_observe(sl_lattice* h, uint64_t slot);            // record of the state
 sl_status enqueue_sweeps(sl_lattice* h, uint64_t n);                // n sweeps, unchecked
 

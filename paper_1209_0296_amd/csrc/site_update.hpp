@@ -103,4 +103,34 @@ __device__ __forceinline__ void block_accumulate(int32_t v0, int32_t v1, int32_t
     }
 }
 
+// The same sums for workgroups whose waves do little else: a lane adds its
+// values to the slot of its number in LDS (no two lanes of a wave share one),
+// and only the first kQ waves, one quantity each, reduce across lanes.  The
+// wave sums of block_accumulate are about 60 instructions in every wave, 15
+// for each of the four words that a lane of a 3D row group updates.
+struct LanePart {
+    int32_t v[kQ][64];
+};
+
+// Before a workgroup barrier that precedes lane_accumulate.
+__device__ __forceinline__ void clear_part(LanePart& part)
+{
+    for (uint32_t e = threadIdx.x; e < kQ * 64; e += blockDim.x) (&part.v[0][0])[e] = 0;
+}
+
+// NQ: quantities that are not always 0 (Ising: 3).
+template <int NQ>
+__device__ __forceinline__ void lane_accumulate(const int32_t (&v)[kQ], LanePart& part, unsigned long long* acc)
+{
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) atomicAdd(&part.v[q][lane], v[q]);
+    lds_barrier();
+    for (uint32_t q = wave; q < (uint32_t)NQ; q += nw) {
+        const int32_t sum = wave_sum(part.v[q][lane]);
+        if (lane == 0 && sum != 0)
+            atomicAdd(&acc[(blockIdx.x % kSub) * kSubStride + q], (unsigned long long)(int64_t)sum);
+    }
+}
+
 }  // namespace spinlat

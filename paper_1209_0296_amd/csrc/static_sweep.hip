@@ -101,7 +101,7 @@ sl_status sl_sweep_static(const sl_params* params, uint64_t n, int8_t* spins_out
     h.first_t = p.t0;
     h.cur = 0;
     h.table_n = build_table(&p, h.table);
-    h.launch = auto_launch(&h, &h.tile);
+    h.launch = auto_launch(&h, &h.tile, &h.plane);
     h.stage = nullptr;
 
     TableArg tab{};

@@ -25,7 +25,7 @@
 // word itself and the adjacent one.
 //
 // Acceptance: spin-1/2 and coupled NE look two sites' thresholds up at once
-// (pair_lut.hpp), spin-1 one site's.  All thresholds must be >= 1 ("word <=
+// (accept.hpp), spin-1 one site's.  All thresholds must be >= 1 ("word <=
 // thr - 1"); other tables run elsewhere.
 //
 // Records: a lane adds its sums of a sweep to one of 32 LDS slots (no lane
@@ -35,7 +35,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "pair_lut.hpp"
+#include "accept.hpp"
 #include "philox.hpp"
 #include "site_update.hpp"
 #include "spinlat_internal.h"
@@ -49,10 +49,6 @@ constexpr int kMaxBlock = 1024;
 constexpr int kFlush = 8;           // sweeps whose sums LDS holds
 constexpr int kObsSlots = 32;
 
-// spin-1: entry 4 (row (2z + 1) + nsum + z) bytes, row = ds_index(s' - s)
-struct OneLut {
-    uint32_t e[52];
-};
 union TileLut {
     PairLut pair;
     OneLut one;
@@ -65,9 +61,8 @@ struct Carry {
 template <int KIND, int DIM>
 __device__ __forceinline__ void build_lut(TileLut& lut, const uint64_t* table)
 {
-    constexpr int z = 2 * DIM;
     if constexpr (KIND == KIND_ISING_ONE) {
-        for (int t = threadIdx.x; t < 4 * (2 * z + 1); t += blockDim.x) lut.one.e[t] = (uint32_t)(table[t] - 1ull);
+        (void)build_one_lut<DIM>(lut.one, table);
     } else if constexpr (KIND == KIND_ISING_HALF || KIND == KIND_NE_COUPLED) {
         build_pair_lut<KIND == KIND_NE_COUPLED, DIM>(lut.pair, table);
     }
@@ -98,7 +93,7 @@ __device__ __forceinline__ uint32_t hold(uint32_t w)
 template <int KIND>
 __device__ __forceinline__ uint32_t unhold(uint32_t w)
 {
-    return KIND == KIND_ISING_ONE ? (w + 0x7F7F7F7Fu) ^ 0x80808080u : w;
+    return KIND == KIND_ISING_ONE ? spin_of(w) : w;
 }
 
 // New held value of a word.  own: held; same, side, S: prepared other-colour
@@ -124,25 +119,8 @@ __device__ __forceinline__ uint32_t update(uint32_t own, uint32_t S, uint32_t no
         }
         return out;
     } else if constexpr (KIND == KIND_ISING_ONE) {
-        constexpr uint32_t row = 4u * (4u * DIM + 1u);  // bytes of a table row
-        // selector 2 (s + 1) + ch of each site, ch the top bit of its second word
-        const uint32_t t1 = __builtin_amdgcn_perm(wa.w[3], wa.w[1], 0x0C0C0703u);
-        const uint32_t t2 = __builtin_amdgcn_perm(wb.w[3], wb.w[1], 0x07030C0Cu);
-        const uint32_t sel = (own << 1) | (((t1 | t2) & 0x80808080u) >> 7);
-        // proposed s' + 1 and table row by selector: s = -1 -> 0, +1; 0 -> -1, +1; +1 -> -1, 0
-        const uint32_t cand = __builtin_amdgcn_perm(0x00000100u, 0x02000201u, sel);
-        const uint32_t rows = __builtin_amdgcn_perm((1u * row) << 8, (2u * row) | ((3u * row) << 8) |
-                                                    ((1u * row) << 16) | ((2u * row) << 24), sel);
-        const uint32_t idx = (S << 2) + rows;
-        const uint8_t* base = reinterpret_cast<const uint8_t*>(lut.one.e);
-        uint32_t t[4], f[4];
-#pragma unroll
-        for (int b = 0; b < 4; ++b) t[b] = *reinterpret_cast<const uint32_t*>(base + ((idx >> (8 * b)) & 0xFFu));
-        between();
-#pragma unroll
-        for (int b = 0; b < 4; ++b) f[b] = (b < 2 ? wa : wb).w[(b & 1) * 2] <= t[b] ? 0xFFu << (8 * b) : 0u;
-        const uint32_t f4 = (f[0] | f[1] | f[2]) | f[3];
-        const uint32_t out = (cand & f4) | (own & ~f4);
+        uint32_t f4;
+        const uint32_t out = one_move<DIM, false>(own, S, wa, wb, lut.one, f4, between);
         const uint32_t om = out & m;
         o.acc += __builtin_popcount(f4 & m);  // 8 per accepted site
         if (colour == 0) {

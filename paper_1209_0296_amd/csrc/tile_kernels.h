@@ -1,6 +1,7 @@
 // tile_kernels.h -- the tile kernel and its launch, instantiated for one kind
 // of lattice per translation unit (kernels_tile_*.hip).
 #pragma once
+#include "block_order.hpp"
 #include "tile_device.hpp"
 
 namespace spinlat {
@@ -19,12 +20,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_tile(SweepArgs a, TileGeom tg, ui
                                                     uint8_t* dst1)
 {
     __shared__ TileLds<IPT> lds;
-    // neighbouring tiles on one XCD (workgroups go to the 8 XCDs in turn), so
-    // that their shared halos meet in its L2
-    const uint32_t nb = gridDim.x;
-    uint32_t b = blockIdx.x;
-    if ((nb & 7u) == 0) b = (b & 7u) * (nb >> 3) + (b >> 3);
-    tile_run<KIND, DIM, IPT>(a, tg, b, nsweeps, dst0, dst1, a.lut, lds);
+    tile_run<KIND, DIM, IPT>(a, tg, xcd_item(blockIdx.x, gridDim.x), nsweeps, dst0, dst1, a.lut, lds);
 }
 
 template <int KIND, int DIM>

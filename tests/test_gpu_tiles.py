@@ -3,7 +3,8 @@ small and middle lattices): bit-exact against the oracle at the sizes where a
 tile can go wrong -- the whole lattice as one tile, a dimension that a tile
 spans, ragged last tiles, halos deeper than a tile, several rounds of tiles per
 CU, 3D lattices up to the last tiled one -- with chunks that leave every
-remainder of a launch's sweeps."""
+remainder of a launch's sweeps; walks along z, which the larger 3D lattices
+take; and spin-1 tables with zero thresholds, which keep to other kernels."""
 import numpy as np
 import pytest
 
@@ -43,6 +44,25 @@ def test_tiles_2d_many_rounds(L, kind):
 @pytest.mark.parametrize("L", [8, 16, 24, 40, 72, 128])
 def test_tiles_3d(L, kw):
     _same(S.Params(dim=3, L=L, seed=L + 1, record_capacity=64, **kw), [1, 2, 3, 7] if L > 40 else CHUNKS)
+
+
+@pytest.mark.parametrize("kw", [dict(T=4.5), dict(two_s=2, T=3.1, h=-0.2)])
+@pytest.mark.parametrize("L", [136, 144, 200, 264])
+def test_walks_along_z(L, kw):
+    """3D lattices above the tiled ones: columns of rows walked along z, ragged
+    last columns in both directions, odd and even first planes."""
+    _same(S.Params(dim=3, L=L, seed=L + 1, record_capacity=64, **kw), [1, 3])
+
+
+@pytest.mark.parametrize("launch", [None, (S.MODE_HALF, 4, 1), (S.MODE_FUSED, 4, 2), (S.MODE_HALF_ROWS, 4, 4)])
+@pytest.mark.parametrize("dim", [2, 3])
+def test_spin_one_zero_thresholds(dim, launch):
+    """Tables with thresholds of zero beside ones of 2^32 and ordinary ones."""
+    sp = S.Params(dim=dim, L=128 if dim == 2 else 32, two_s=2, T=0.2, h=0.05, seed=3, record_capacity=16)
+    t = S.threshold_table(sp)
+    assert 0 in t and 2 ** 32 in t
+    if not (dim == 3 and launch is not None and launch[0] == S.MODE_FUSED):
+        _same(sp, [2, 5], launch=launch)
 
 
 def test_tiles_between_other_schedules():
