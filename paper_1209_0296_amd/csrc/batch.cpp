@@ -8,6 +8,8 @@
 // buffer for record readback, and a heap from which each job's lattice (two
 // colour arrays, or two copies of them for fused jobs) and record ring are
 // carved first-fit.  Admission by footprint is the heap allocation succeeding.
+// Tiles and walks along z need a second lattice copy; where the heap has no room
+// for it a job runs in the one-copy class that sl_batch_job_bytes reports.
 //
 // A call (sl_batch_sweep) uploads the counters and work lists from pinned
 // staging (double-buffered, so the host never waits for the previous call),
@@ -16,9 +18,12 @@
 // and joins the two.  The per-sweep launches of the kernel families are
 // captured once per (sweeps, grid buckets) shape into HIP graphs, each on one
 // stream, and replayed; the kernels read the true segment counts from device
-// memory.  The two row-group families run on a third stream of the library's,
+// memory.  The families of 3D jobs run on a third stream of the library's,
 // beside the other families (they touch disjoint jobs), so that one family's
-// waves fill the issue slots another leaves idle.
+// waves fill the issue slots another leaves idle.  Workgroups of tiles and
+// columns are listed heaviest first and left in the hardware's order over the
+// XCDs: a contiguous range per XCD, good for one lattice, put the large jobs of
+// a mix on few of them (256 served jobs: 50.7 ms so, 46.1 spread, 43.6 sorted).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -131,8 +136,31 @@ struct JobHost {
     size_t table_n = 0;
 };
 
-bool resident_job(const JobHost& J) { return J.geom.variant == kBvResident; }
-bool fused_job(const JobHost& J) { return J.geom.variant >= kBvFusedD4 && J.geom.variant <= kBvFusedD1; }
+bool resident_job(const JobHost& J) { return J.geom.variant == kBvResident || J.geom.variant == kBvWhole; }
+
+// Launches that `sweeps` sweeps of a job with two copies take: each leaves the
+// state in the other copy.
+uint64_t copy_flips(const JobHost& J, uint64_t sweeps)
+{
+    if (J.geom.variant == kBvTile) return family_launches(4, sweeps);
+    return J.geom.copies == 2 ? sweeps : 0;
+}
+
+// Planes of a column of the walks along z, for a call whose jobs have `planes`
+// planes of columns in all: about 768 workgroups (three per CU), 4 to 32 planes
+// (a column recomputes two colour-0 planes).
+uint32_t plane_depth(uint64_t planes)
+{
+    const uint64_t d = (planes + 767) / 768;
+    return (uint32_t)(d < 4 ? 4 : d > 32 ? 32 : d);
+}
+
+// Workgroups of a job in a call, at most.
+uint64_t most_workgroups(const RowGeomHost& g)
+{
+    const uint64_t per = g.variant == kBvPlane ? 4 : g.items_per_wg;
+    return (g.nitems + per - 1) / per;
+}
 
 // Kernel kind of a job's class: the model kind, with coupled NE jobs apart.
 int class_kind(const JobHost& J)
@@ -227,8 +255,10 @@ sl_status check_job(const sl_batch* b, uint32_t j)
 }
 
 // Parameters of a job (record capacity from the batch), its class and footprint.
+// geom is the class to use, least the one for an arena that has no room for its
+// two lattice copies (foot: the footprint of least).
 sl_status prepare_job(const sl_batch_config* cfg, const sl_params* params, sl_params* p, JobFoot* foot,
-                      RowGeomHost* geom, uint64_t* table, size_t* table_n)
+                      RowGeomHost* geom, RowGeomHost* least, uint64_t* table, size_t* table_n)
 {
     if (!params) return fail(SL_E_INVALID, "params is NULL");
     *p = *params;
@@ -248,20 +278,28 @@ sl_status prepare_job(const sl_batch_config* cfg, const sl_params* params, sl_pa
     const Geom g = geom_of(p, nh);
     const bool fused = p->dim == 2 && !(cfg->flags & SL_BATCH_NO_FUSED);
     const int H = cfg->tile_rows > 0 ? cfg->tile_rows : default_rows(p->dim, fused);
-    if (!(cfg->flags & SL_BATCH_NO_RESIDENT) && batch_resident_geom(g, *geom)) {
+    if (!(cfg->flags & SL_BATCH_NO_RESIDENT) && batch_resident_geom(g, *least)) {
         // resident jobs run the direct update in LDS: any table
-    } else if (!batch_geom(g, H, lut32 || !spin_half_table, fused, *geom)) {
+    } else if (!batch_geom(g, H, lut32 || !spin_half_table, fused, *least)) {
         return fail(SL_E_UNSUPPORTED, "L = %d does not fit the batched kernels", p->L);
     }
-    if (coupled && geom->variant == kBvWindow)
+    if (coupled && least->variant == kBvWindow)
         return fail(SL_E_UNSUPPORTED, "batched coupled NE jobs need a colour row that fits one wave "
                                       "and every threshold >= 1 (L = %d), or a lattice that fits LDS", p->L);
-    *foot = job_foot(p, cfg->record_capacity, geom->copies);
+    *foot = job_foot(p, cfg->record_capacity, least->copies);
+    // tiles and walks along z, unless the caller asked for a strip height or for
+    // fewer workgroups than they take
+    if (!(p->model == SL_NORTH_EAST || lut32) ||
+        !batch_tiled_geom(g, !(cfg->flags & SL_BATCH_NO_RESIDENT),
+                          !(cfg->flags & SL_BATCH_NO_FUSED) && cfg->tile_rows == 0, *geom) ||
+        (cfg->max_workgroups && most_workgroups(*geom) > most_workgroups(*least)))
+        *geom = *least;
     return SL_OK;
 }
 
-// Per-sweep launches of one kernel family: the fused family once per sweep,
-// the others once per colour.
+// Launches of one kernel family for n sweeps: the tiles once per
+// kBatchTileSweeps sweeps, fused jobs and walks along z once per sweep, the
+// others once per colour.
 hipError_t enqueue_family(sl_batch* b, int k, int f, uint64_t n, uint32_t grid, hipStream_t s)
 {
     const UploadLayout& u = b->base.u;
@@ -269,6 +307,11 @@ hipError_t enqueue_family(sl_batch* b, int k, int f, uint64_t n, uint32_t grid, 
     const BatchWG* wgs = reinterpret_cast<const BatchWG*>(d_up(b, k) + u.wgs);
     const uint32_t* meta = reinterpret_cast<const uint32_t*>(d_up(b, k) + u.counts);
     hipError_t e = hipSuccess;
+    if (f == 4 || f == 5) {
+        for (uint64_t m = 0; m < family_launches(f, n) && e == hipSuccess && grid; ++m)
+            e = launch_batch_tiled(f, d_jobs(b), dyn, wgs, meta, grid, (uint32_t)m, s);
+        return e;
+    }
     for (uint64_t s2 = 0; s2 < n && e == hipSuccess && grid; ++s2)
         for (uint32_t c = 0; c < (f == 2 ? 1u : 2u) && e == hipSuccess; ++c)
             e = launch_batch_family(f, d_jobs(b), dyn, wgs, meta, grid, c, (uint32_t)s2, s);
@@ -340,10 +383,10 @@ sl_status sl_batch_job_bytes(const sl_params* params, const sl_batch_config* cfg
     if (!bytes) return fail(SL_E_INVALID, "bytes is NULL");
     sl_params p;
     JobFoot foot;
-    RowGeomHost geom;
+    RowGeomHost geom, least;
     uint64_t table[kMaxLut];
     size_t tn;
-    st = prepare_job(cfg, params, &p, &foot, &geom, table, &tn);
+    st = prepare_job(cfg, params, &p, &foot, &geom, &least, table, &tn);
     if (st != SL_OK) return st;
     *bytes = foot.total;
     return SL_OK;
@@ -413,14 +456,23 @@ sl_status sl_batch_add(sl_batch* b, const sl_params* params, uint64_t sweeps, ui
     if (!b) return fail(SL_E_INVALID, "NULL batch");
     if (!job_id) return fail(SL_E_INVALID, "job_id is NULL");
     JobHost J;
-    sl_status st = prepare_job(&b->cfg, params, &J.params, &J.foot, &J.geom, J.table, &J.table_n);
+    RowGeomHost least;
+    sl_status st = prepare_job(&b->cfg, params, &J.params, &J.foot, &J.geom, &least, J.table, &J.table_n);
     if (st != SL_OK) return st;
     if (sweeps > (1ull << 32) - J.params.t0)  // validate() keeps t0 < 2^32
         return fail(SL_E_OVERFLOW, "t0 + sweeps would pass 2^32");
     uint32_t j = 0;
     while (j < b->jobs.size() && b->jobs[j].used) ++j;
     if (j == b->jobs.size()) return fail(SL_E_STATE, "job table full (%u jobs)", b->cfg.max_jobs);
-    if (!b->heap.alloc(J.foot.total, &J.off))
+    const JobFoot least_foot = J.foot;
+    J.foot = job_foot(&J.params, b->cfg.record_capacity, J.geom.copies);
+    bool room = b->heap.alloc(J.foot.total, &J.off);
+    if (!room && J.geom.copies != least.copies) {  // no room for a second copy
+        J.geom = least;
+        J.foot = least_foot;
+        room = b->heap.alloc(J.foot.total, &J.off);
+    }
+    if (!room)
         return fail(SL_E_BUFFER, "arena has no free block of %zu bytes for this job", J.foot.total);
     J.used = true;
     J.kind = kind_of(&J.params);
@@ -509,29 +561,45 @@ sl_status sl_batch_sweep(sl_batch* b, uint64_t n)
 
     // work list: one segment per kernel family, each grouped by class so
     // neighbouring workgroups run the same code; resident jobs in their own list
-    uint64_t nwg = 0, nres = 0;
+    uint64_t nwg = 0, nres = 0, nwhole = 0, planes = 0;
     uint32_t count[kBatchFamilies] = {}, offset[kBatchFamilies] = {};
+    std::vector<std::pair<uint64_t, uint32_t>> order;  // {family, weight, class; job}
+    order.reserve(top);
+    for (uint32_t j = 0; j < top; ++j) {
+        const JobHost& J = b->jobs[j];
+        if (!J.used || !budget[j] || resident_job(J)) continue;
+        const uint32_t kind = (uint32_t)class_kind(J);
+        // tiles and columns: the heaviest workgroups first
+        const bool tiled = J.geom.variant == kBvTile || J.geom.variant == kBvPlane;
+        const uint64_t weight = tiled ? J.geom.words * (kind == (uint32_t)KIND_ISING_ONE ? 2 : 1) : 0;
+        order.emplace_back(((uint64_t)batch_family(J.geom.variant, kind) << 48) + ((0xFFFFFFull - weight) << 16) +
+                               batch_class((int)kind, J.params.dim, J.geom.variant), j);
+        if (J.geom.variant == kBvPlane) planes += J.geom.nitems;
+    }
+    std::sort(order.begin(), order.end());
+    const uint32_t depth = plane_depth(planes);
+    size_t at = 0;
     for (int fam = 0; fam < kBatchFamilies; ++fam) {
         offset[fam] = (uint32_t)nwg;
-        for (uint32_t kind : {(uint32_t)KIND_ISING_HALF, (uint32_t)KIND_ISING_ONE, (uint32_t)KIND_NE,
-                              (uint32_t)kBatchKindNeCoupled})
-            for (int dim : {2, 3})
-                for (uint32_t v = 0; v < 16; ++v) {
-                    if (v == kBvResident || batch_family(v, kind) != fam) continue;
-                    for (uint32_t j = 0; j < top; ++j) {
-                        const JobHost& J = b->jobs[j];
-                        if (!J.used || !budget[j] || (uint32_t)class_kind(J) != kind || J.params.dim != dim ||
-                            J.geom.variant != v)
-                            continue;
-                        const uint32_t per = J.geom.items_per_wg;
-                        const uint32_t kwg = (J.geom.nitems + per - 1) / per;
-                        if (nwg + kwg > max_wg(&b->cfg))
-                            return fail(SL_E_STATE, "work list full (%llu workgroups); raise max_workgroups",
-                                        (unsigned long long)max_wg(&b->cfg));
-                        for (uint32_t w = 0; w < kwg; ++w) h_wgs[nwg + w] = BatchWG{j, w * per};
-                        nwg += kwg;
-                    }
-                }
+        for (; at < order.size() && (int)(order[at].first >> 48) == fam; ++at) {
+            const uint32_t j = order[at].second;
+            const JobHost& J = b->jobs[j];
+            const uint32_t L = (uint32_t)J.params.L, nz = (L + depth - 1) / depth, hz = (L + nz - 1) / nz;
+            const bool walk = J.geom.variant == kBvPlane;
+            const uint32_t per = walk ? hz : J.geom.items_per_wg;
+            const uint32_t nty = walk ? J.geom.nitems / L : 0;
+            const uint32_t kwg = walk ? nty * ((L + hz - 1) / hz) : (J.geom.nitems + per - 1) / per;
+            if (nwg + kwg > max_wg(&b->cfg))
+                return fail(SL_E_STATE, "work list full (%llu workgroups); raise max_workgroups",
+                            (unsigned long long)max_wg(&b->cfg));
+            if (walk) {
+                for (uint32_t z0 = 0; z0 < L; z0 += hz)
+                    for (uint32_t ty = 0; ty < nty; ++ty)
+                        h_wgs[nwg++] = BatchWG{j, ty + (z0 << 8) + (std::min(hz, L - z0) << 20)};
+            } else {
+                for (uint32_t w = 0; w < kwg; ++w) h_wgs[nwg++] = BatchWG{j, w * per};
+            }
+        }
         count[fam] = (uint32_t)nwg - offset[fam];
     }
     for (uint32_t j = 0; j < top; ++j) {
@@ -541,8 +609,10 @@ sl_status sl_batch_sweep(sl_batch* b, uint64_t n)
         d[1] = (uint32_t)J.pending;
         d[2] = J.used ? (uint32_t)budget[j] : 0u;
         d[3] = J.cur;
-        if (J.used && budget[j] && resident_job(J)) h_res[nres++] = j;
+        if (J.used && budget[j] && J.geom.variant == kBvResident) h_res[nres++] = j;
     }
+    for (uint32_t j = 0; j < top; ++j)
+        if (b->jobs[j].used && budget[j] && b->jobs[j].geom.variant == kBvWhole) h_res[nres + nwhole++] = j;
     for (int f = 0; f < kBatchFamilies; ++f) {
         h_counts[2 * f] = count[f];
         h_counts[2 * f + 1] = offset[f];
@@ -555,8 +625,8 @@ sl_status sl_batch_sweep(sl_batch* b, uint64_t n)
     if (e == hipSuccess)
         e = hipMemcpyAsync(du + u.counts, h_counts, 2 * kBatchFamilies * sizeof(uint32_t), hipMemcpyHostToDevice,
                            b->stream);
-    if (e == hipSuccess && nres)
-        e = hipMemcpyAsync(du + u.res, h_res, nres * sizeof(uint32_t), hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess && nres + nwhole)
+        e = hipMemcpyAsync(du + u.res, h_res, (nres + nwhole) * sizeof(uint32_t), hipMemcpyHostToDevice, b->stream);
     // the staging of set k may be rewritten once these copies have run
     if (e == hipSuccess) e = hipEventRecord(b->ev_up[k], b->stream);
     if (e != hipSuccess) return hip_fail(e, "batch: upload");
@@ -566,16 +636,20 @@ sl_status sl_batch_sweep(sl_batch* b, uint64_t n)
     bool par_work = false, main_work = false;
     for (int f = 0; f < kBatchFamilies; ++f) (row_family(f) ? par_work : main_work) |= count[f] != 0;
     const bool split = par_work && main_work;
-    if (nres || split) {
+    if (nres || nwhole || split) {
         e = hipEventRecord(b->ev_fork, b->stream);
         if (e != hipSuccess) return hip_fail(e, "batch: fork");
     }
-    // resident jobs: one launch on the side stream, overlapping the rest
-    if (nres) {
+    // resident jobs: a launch each of the two kinds on the side stream,
+    // overlapping the rest
+    if (nres || nwhole) {
         e = hipStreamWaitEvent(b->side, b->ev_fork, 0);
         if (e == hipSuccess)
             e = launch_batch_resident(d_jobs(b), reinterpret_cast<const uint32_t*>(du + u.dyn),
                                       reinterpret_cast<const uint32_t*>(du + u.res), (uint32_t)nres, b->side);
+        if (e == hipSuccess)
+            e = launch_batch_whole(d_jobs(b), reinterpret_cast<const uint32_t*>(du + u.dyn),
+                                   reinterpret_cast<const uint32_t*>(du + u.res) + nres, (uint32_t)nwhole, b->side);
         if (e == hipSuccess) e = hipEventRecord(b->ev_join, b->side);
         if (e != hipSuccess) return hip_fail(e, "batch: resident launch");
     }
@@ -617,7 +691,7 @@ sl_status sl_batch_sweep(sl_batch* b, uint64_t n)
             if (e != hipSuccess) return hip_fail(e, "batch: join the row-group stream");
         }
     }
-    if (nres) {
+    if (nres || nwhole) {
         e = hipStreamWaitEvent(b->stream, b->ev_join, 0);
         if (e != hipSuccess) return hip_fail(e, "batch: join resident launch");
     }
@@ -628,7 +702,7 @@ sl_status sl_batch_sweep(sl_batch* b, uint64_t n)
         J.pending += budget[j];
         J.remaining -= budget[j];
         J.done += budget[j];
-        if (fused_job(J)) J.cur ^= (uint32_t)(budget[j] & 1u);
+        J.cur ^= (uint32_t)(copy_flips(J, budget[j]) & 1u);
     }
     return SL_OK;
 }

@@ -6,7 +6,11 @@
 // the random numbers depend on (seed, sweep, site) only, a job's lattice and
 // records are the same alone and in any mix.
 //
-// Job classes (chosen by the host when a job is admitted):
+// Job classes (chosen by the host when a job is admitted; the default ones are
+// those of kernels_batch_tile.hip: whole lattices in one tile, tiles, walks
+// along z.  The classes here take what those do not: tables with zero
+// thresholds, arenas without room for a second lattice copy, callers that ask
+// for a strip height or switch the fused class off):
 //   - resident: the lattice (both colours) fits 48 KiB of LDS.  One launch per
 //     call runs every resident job's sweeps of the call, one workgroup per job,
 //     the whole chunk of sweeps in LDS (k_batch_resident).
@@ -17,7 +21,7 @@
 //     row group (no walk).
 //   - walk / window: one colour per launch, whole-row walks down strips, or
 //     64-lane column windows for rows that fit no wave.
-// The non-resident classes form four kernel families, each with its own
+// The non-resident classes here form four kernel families, each with its own
 // kernel so that its register budget is its own: half (walks and windows),
 // rows of spin-1/2 jobs and rows of spin-1 jobs launch once per colour, fused
 // once per sweep (all colour work of the fused jobs).  A work list names the workgroups as (job, first item) pairs in

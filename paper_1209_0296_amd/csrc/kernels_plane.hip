@@ -13,13 +13,15 @@ __global__ void __launch_bounds__(tilek::kMaxBlock) k_plane(SweepArgs a, PlaneGe
 {
     __shared__ planek::PlaneLds<IPT> lds;
     int32_t v[kQ];
-    planek::plane_run<KIND, IPT>(a, pg, xcd_item(blockIdx.x, gridDim.x), dst0, dst1, a.lut, lds, v);
+    const uint32_t item = xcd_item(blockIdx.x, gridDim.x);
+    const uint32_t tz = item / pg.nty, z0 = tz * pg.Hz;
+    planek::plane_run<KIND, IPT>(a, pg, item - tz * pg.nty, z0, min(pg.Hz, pg.L - z0), dst0, dst1, a.lut, lds, v);
     block_accumulate(v[0], v[1], v[2], v[3], a.acc);
 }
 
 }  // namespace
 
-bool plane_geom(const Geom& g, uint32_t H, uint32_t Hz, PlaneGeom& p)
+bool plane_geom(const Geom& g, uint32_t H, uint32_t Hz, PlaneGeom& p, uint32_t max_items)
 {
     p = PlaneGeom{};
     if (g.dim != 3 || !H || !Hz) return false;
@@ -31,7 +33,7 @@ bool plane_geom(const Geom& g, uint32_t H, uint32_t Hz, PlaneGeom& p)
     p.Hz = Hz < g.L ? Hz : g.L;
     if (p.H + p.hy > g.L) return false;
     p.nitems = p.RY * p.ncols;
-    if (p.nitems > 2 * 1024) return false;
+    if (p.nitems > max_items) return false;
     p.nty = cdiv(g.L, p.H);
     p.ntz = cdiv(g.L, p.Hz);
     p.magicP = (uint32_t)(((1ull << 32) + p.ncols - 1) / p.ncols);

@@ -6,8 +6,6 @@ namespace spinlat {
 
 namespace {
 
-constexpr uint32_t kMaxItems = 4 * 1024;  // words of one colour a workgroup holds
-
 uint32_t cdiv(uint32_t a, uint32_t b) { return (a + b - 1) / b; }
 
 uint32_t magic(uint32_t d) { return (uint32_t)(((1ull << 32) + d - 1) / d); }
@@ -53,7 +51,7 @@ double plan_cost(const TileGeom& t, uint32_t k, const Cost& c)
 
 TilePlan whole_plan(const Geom& g) { return TilePlan{g.Lh / 4, g.L, g.L, kTileWhole}; }
 
-bool tile_geom(const Geom& g, const TilePlan& p, uint32_t k, TileGeom& t)
+bool tile_geom(const Geom& g, const TilePlan& p, uint32_t k, TileGeom& t, uint32_t max_items)
 {
     t = TileGeom{};
     t.L = g.L;
@@ -75,7 +73,7 @@ bool tile_geom(const Geom& g, const TilePlan& p, uint32_t k, TileGeom& t)
     t.RY = t.H + 2 * t.hy;
     t.RZ = t.Z + 2 * t.hz;
     const uint64_t n = (uint64_t)t.P * t.RY * t.RZ;
-    if (n > kMaxItems) return false;
+    if (n > max_items) return false;
     t.nitems = (uint32_t)n;
     t.ntx = cdiv(t.ncols, t.W);
     t.nty = cdiv(t.L, t.H);
@@ -85,6 +83,13 @@ bool tile_geom(const Geom& g, const TilePlan& p, uint32_t k, TileGeom& t)
     t.ipt = t.nitems <= 1024 ? 1 : t.nitems <= 2048 ? 2 : 4;
     t.block = cdiv(cdiv(t.nitems, t.ipt), 64) * 64;
     return true;
+}
+
+uint64_t tile_words(const TileGeom& t, uint32_t j)
+{
+    const uint32_t cut = 2 * (j + 1);
+    const uint64_t ry = t.wrapy ? t.RY : t.RY - cut, rz = t.wrapz ? t.RZ : t.RZ - cut;
+    return ry * rz * t.P * t.ntx * t.nty * t.ntz;
 }
 
 TilePlan tile_plan(const Geom& g, int kind, bool coupled)

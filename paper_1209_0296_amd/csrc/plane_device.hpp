@@ -26,10 +26,10 @@ namespace planek {
 using tilek::Carry;
 using tilek::TileLut;
 
-template <int IPT>
+template <int IPT, int BLOCK = tilek::kMaxBlock>
 struct PlaneLds {
-    uint32_t q1[2][IPT * tilek::kMaxBlock];  // old colour 1, plane i
-    uint32_t q0[2][IPT * tilek::kMaxBlock];  // new colour 0, plane i - 1
+    uint32_t q1[2][IPT * BLOCK];  // old colour 1, plane i
+    uint32_t q0[2][IPT * BLOCK];  // new colour 0, plane i - 1
     TileLut lut;
 };
 
@@ -44,17 +44,18 @@ struct Column {
     uint32_t c1a, c1b, c1c, own0, q0a, q0b;
 };
 
-// Column `item` of the lattice (y tile fastest).  Reads a.col, writes dst0 and
-// dst1; returns the workgroup's share of the record in v (per lane).
-template <int KIND, int IPT>
-__device__ __forceinline__ void plane_run(const SweepArgs& a, const PlaneGeom& pg, uint32_t item, uint8_t* dst0,
-                                          uint8_t* dst1, const uint64_t* table, PlaneLds<IPT>& lds, int32_t (&v)[kQ])
+// Column of the rows ty H .. and the zn planes from z0.  Reads a.col, writes dst0
+// and dst1; leaves each lane's share of the record in v.  Every thread of the
+// block calls this (barriers inside); blockDim.x * IPT >= pg.nitems.
+template <int KIND, int IPT, int BLOCK>
+__device__ __forceinline__ void plane_run(const SweepArgs& a, const PlaneGeom& pg, uint32_t ty, uint32_t z0, uint32_t zn,
+                                          uint8_t* dst0, uint8_t* dst1, const uint64_t* table, PlaneLds<IPT, BLOCK>& lds,
+                                          int32_t (&v)[kQ])
 {
     constexpr bool one = KIND == KIND_ISING_ONE;
     const uint32_t tid = threadIdx.x;
-    const uint32_t tz = item / pg.nty, ty = item - tz * pg.nty;
-    const uint32_t y0 = ty * pg.H, z0 = tz * pg.Hz;
-    const uint32_t hi = min(pg.H, pg.L - y0), zn = min(pg.Hz, pg.L - z0);
+    const uint32_t y0 = ty * pg.H;
+    const uint32_t hi = min(pg.H, pg.L - y0);
     const uint32_t pl = pg.L * pg.ncols;  // words of a plane
 
     uint32_t at[IPT], pos[IPT], up[IPT], down[IPT], sideE[IPT], sideO[IPT], selE[IPT], selO[IPT], m[IPT];

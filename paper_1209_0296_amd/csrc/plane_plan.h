@@ -14,7 +14,9 @@ struct PlaneGeom {
     uint32_t block, ipt;
 };
 
-bool plane_geom(const Geom& g, uint32_t H, uint32_t Hz, PlaneGeom& pg);
+constexpr uint32_t kPlaneItems = 2 * 1024;  // words of a plane that a workgroup holds
+
+bool plane_geom(const Geom& g, uint32_t H, uint32_t Hz, PlaneGeom& pg, uint32_t max_items = kPlaneItems);
 // Column size for a single lattice; false if the walk does not take it.
 bool plane_plan(const Geom& g, int kind, PlaneGeom& pg);
 // One sweep, reading a.col and writing another copy; every threshold >= 1.

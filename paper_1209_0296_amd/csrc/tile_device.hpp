@@ -191,9 +191,9 @@ __device__ __forceinline__ void finish(const Carry& o, int words, int32_t (&v)[k
     }
 }
 
-template <int IPT>
+template <int IPT, int BLOCK = kMaxBlock>
 struct TileLds {
-    uint32_t q[2][IPT * kMaxBlock];
+    uint32_t q[2][IPT * BLOCK];
     TileLut lut;
     int32_t obs[kFlush][kQ][kObsSlots];
 };
@@ -201,9 +201,9 @@ struct TileLds {
 // Sweeps a.t .. a.t + nsweeps - 1 of tile `tile`: reads a.col, writes dst0 and
 // dst1, adds the record of sweep s to a.acc + s slots.  Every thread of the
 // block calls this (barriers inside); blockDim.x * IPT >= tg.nitems.
-template <int KIND, int DIM, int IPT>
+template <int KIND, int DIM, int IPT, int BLOCK>
 __device__ __forceinline__ void tile_run(const SweepArgs& a, const TileGeom& tg, uint32_t tile, uint32_t nsweeps,
-                                         uint8_t* dst0, uint8_t* dst1, const uint64_t* table, TileLds<IPT>& lds)
+                                         uint8_t* dst0, uint8_t* dst1, const uint64_t* table, TileLds<IPT, BLOCK>& lds)
 {
     const uint32_t tid = threadIdx.x;
     // the tile's place: x fastest

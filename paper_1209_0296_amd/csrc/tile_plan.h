@@ -34,7 +34,10 @@ constexpr uint32_t kTileWhole = 4096;  // sweeps per launch of a tile that is th
 inline bool tile_whole(const TileGeom& t) { return t.wrapx && t.wrapy && t.wrapz; }
 
 // Geometry of launches of k sweeps with the plan's tile; false if it does not fit.
-bool tile_geom(const Geom& g, const TilePlan& p, uint32_t k, TileGeom& tg);
+constexpr uint32_t kTileItems = 4 * 1024;  // words of one colour that a workgroup holds
+bool tile_geom(const Geom& g, const TilePlan& p, uint32_t k, TileGeom& tg, uint32_t max_items = kTileItems);
+// Words of one colour that half-sweep j of a launch updates, over all tiles.
+uint64_t tile_words(const TileGeom& t, uint32_t j);
 // Fastest plan for a lattice by the launch cost model (kernels_tile.hip).
 TilePlan tile_plan(const Geom& g, int kind, bool coupled);
 // Sweeps a.t .. a.t + k - 1, reading a.col and writing dst (another copy, or

@@ -1,0 +1,69 @@
+"""Batched jobs on tiles (several sweeps per launch), by walks along z and whole
+in one tile: bit-exact against the oracle run of each job alone, for calls that
+leave every remainder of a tile launch's four sweeps, shapes with ragged last
+tiles and columns, arenas with room for one lattice copy only, and a limit on
+the work list."""
+import numpy as np
+import pytest
+
+import paper_1209_0296_amd as S
+from helpers import run_oracle
+
+pytestmark = pytest.mark.gpu
+
+JOBS = [
+    S.Params(L=32, T=2.2, seed=1), S.Params(L=128, two_s=2, T=1.7, seed=2), S.Params(L=136, T=2.4, h=0.1, seed=3),
+    S.Params(L=520, two_s=2, T=1.6, seed=4), S.Params(L=1000, T=2.3, seed=5),
+    S.Params(model=S.NORTH_EAST, L=200, c=0.2, seed=6), S.Params(model=S.NORTH_EAST, L=1000, c=0.6, seed=7),
+    S.Params(model=S.NE_COUPLED, L=400, c=0.5, T=3.0, seed=8), S.Params(model=S.NE_COUPLED, L=64, c=0.5, T=3.0, seed=9),
+    S.Params(dim=3, L=16, two_s=2, T=3.0, seed=10), S.Params(dim=3, L=24, T=4.4, seed=11),
+    S.Params(dim=3, L=32, two_s=2, T=3.1, seed=12), S.Params(dim=3, L=72, T=4.6, h=0.05, seed=13),
+    S.Params(dim=3, L=104, two_s=2, T=3.2, seed=14), S.Params(dim=3, L=128, T=4.5, seed=15),
+]
+
+
+@pytest.mark.parametrize("flags", [0, S.BATCH_NO_GRAPH, S.BATCH_NO_RESIDENT])
+def test_tiled_jobs_match_each_job_alone(flags):
+    b = S.Batch(arena_bytes=128 << 20, max_jobs=24, record_capacity=32, flags=flags)
+    budget = [13 + i % 6 for i in range(len(JOBS))]
+    ids = [b.add(p, sweeps=n) for p, n in zip(JOBS, budget)]
+    assert all(i is not None for i in ids)
+    recs = {i: [] for i in ids}
+    for n in (1, 2, 3, 4, 5, 30):
+        b.sweep(n)
+        for i, r in b.drain().items():
+            recs[i].append(r)
+    for i, p, n in zip(ids, JOBS, budget):
+        print(f"case batch tiles flags={flags} job {i} model={p.model} dim={p.dim} L={p.L}", flush=True)
+        assert b.status(i)[:2] == (n, 0)
+        o_s, o_r = run_oracle(p, n)
+        np.testing.assert_array_equal(np.vstack(recs[i]), o_r)
+        np.testing.assert_array_equal(b.spins(i), o_s)
+    b.close()
+
+
+@pytest.mark.parametrize("p", [S.Params(dim=3, L=72, T=4.6, seed=3), S.Params(L=936, two_s=2, T=1.6, seed=4)])
+def test_an_arena_of_exactly_the_reported_bytes_admits_the_job(p):
+    """sl_batch_job_bytes is what a job needs at least: with no room for a second
+    lattice copy it runs on one."""
+    cfg = S.batch_config(max_jobs=2, record_capacity=16)
+    b = S.Batch(S.batch_base_bytes(cfg) + S.batch_job_bytes(p, cfg), max_jobs=2, record_capacity=16)
+    i = b.add(p, sweeps=7)
+    assert i is not None
+    b.sweep(3)
+    b.sweep(4)
+    o_s, o_r = run_oracle(p, 7)
+    np.testing.assert_array_equal(S.records_to_array(b.measure(i)), o_r)
+    np.testing.assert_array_equal(b.spins(i), o_s)
+    b.close()
+
+
+def test_a_work_list_limit_keeps_the_classes_that_fit_it():
+    p = S.Params(L=1024, T=2.3, seed=6)
+    b = S.Batch(32 << 20, max_jobs=2, record_capacity=16, max_workgroups=64)
+    i = b.add(p, sweeps=5)
+    b.sweep(5)
+    o_s, o_r = run_oracle(p, 5)
+    np.testing.assert_array_equal(S.records_to_array(b.measure(i)), o_r)
+    np.testing.assert_array_equal(b.spins(i), o_s)
+    b.close()
