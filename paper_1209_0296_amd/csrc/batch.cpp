@@ -197,7 +197,6 @@ struct sl_batch {
     BaseLayout base;
     std::vector<JobHost> jobs;
     FreeList heap;       // free ranges of the job heap
-    BatchJob* h_jobs;    // pinned [max_jobs]: one staging entry per job slot
     uint8_t* h_up[2];    // pinned upload staging, one per upload set
     sl_record* h_stage;  // pinned [max_jobs * record_capacity]
     BatchFold* h_fold;   // pinned [max_jobs]
@@ -243,7 +242,6 @@ SweepArgs job_args(const sl_batch* b, uint32_t j)
     a.key1 = (uint32_t)(J.params.seed >> 32);
     a.lut = d_jobs(b)[j].table;
     a.lut_n = (int32_t)J.table_n;
-    a.update = 1;
     return a;
 }
 
@@ -420,13 +418,11 @@ sl_status sl_batch_create(const sl_batch_config* cfg, void* device_arena, size_t
     b->jobs.resize(cfg->max_jobs);
     const size_t heap = round_up(base.heap, kAlign);
     b->heap.reset(heap, arena_bytes > heap ? (arena_bytes - heap) / kAlign * kAlign : 0);
-    b->h_jobs = nullptr;
     b->h_up[0] = b->h_up[1] = nullptr;
     b->h_stage = nullptr;
     b->h_fold = nullptr;
     b->calls = 0;
-    hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&b->h_jobs), (size_t)cfg->max_jobs * sizeof(BatchJob),
-                                 hipHostMallocDefault);
+    hipError_t e = hipSuccess;
     for (int k = 0; k < 2 && e == hipSuccess; ++k)
         e = hipHostMalloc(reinterpret_cast<void**>(&b->h_up[k]), base.u.bytes, hipHostMallocDefault);
     if (e == hipSuccess)
@@ -482,9 +478,10 @@ sl_status sl_batch_add(sl_batch* b, const sl_params* params, uint64_t sweeps, ui
     J.cur = 0;
     b->jobs[j] = J;
 
-    // device job-table entry, staged in this slot's own pinned entry: the
-    // slot is rewritten only after sl_batch_remove, which synchronises
-    BatchJob* hj = b->h_jobs + j;
+    // device job-table entry, written by the start kernel
+    static_assert(sizeof(BatchJob) <= sizeof(StartBlob), "a job entry travels in the start kernel's arguments");
+    BatchJob entry;
+    BatchJob* hj = &entry;
     std::memset(hj, 0, sizeof(BatchJob));
     for (uint32_t cp = 0; cp < J.geom.copies; ++cp)
         for (uint32_t c = 0; c < 2; ++c) hj->col[cp][c] = col_of(b, J, cp, c);
@@ -497,26 +494,13 @@ sl_status sl_batch_add(sl_batch* b, const sl_params* params, uint64_t sweeps, ui
     hj->table_n = (uint32_t)J.table_n;
     std::memcpy(hj->rg_words, J.geom.bytes, sizeof(hj->rg_words));
     std::memcpy(hj->table, J.table, J.table_n * sizeof(uint64_t));
-    hipError_t e = hipMemcpyAsync(d_jobs(b) + j, hj, sizeof(BatchJob), hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess)
-        e = launch_fill_u64(ring_of(b, j), (uint64_t)b->cfg.record_capacity * kSlotWords, b->stream);
     SweepArgs a = job_args(b, j);
-    if (e == hipSuccess) {
-        if (J.params.init == SL_INIT_BUFFER) {
-            e = launch_from_natural(a, J.params.init_spins, b->stream);
-        } else {
-            const uint64_t bern = thr_from_prob(J.params.c);
-            e = launch_init(a, J.kind, J.params.init == SL_INIT_COLD ? 0 : 1, (uint32_t)bern,
-                            (uint32_t)(bern >> 32), b->stream);
-        }
-    }
+    const uint64_t bern = thr_from_prob(J.params.c);
+    hipError_t e = start_lattice(a, &J.params, J.kind, bern, ring_of(b, j), (uint64_t)b->cfg.record_capacity * kSlotWords,
+                                 d_jobs(b) + j, hj, sizeof(BatchJob), b->stream);
     // record r_0: observables of the initial state
-    a.update = 0;
     a.acc = ring_of(b, j);
-    for (uint32_t c = 0; c < 2 && e == hipSuccess; ++c) {
-        a.colour = c;
-        e = launch_simple_half(a, J.kind, b->stream);
-    }
+    if (e == hipSuccess) e = launch_observe(a, J.kind, b->stream);
     if (e != hipSuccess) {
         (void)hipStreamSynchronize(b->stream);
         b->heap.release(J.off, J.foot.total);
@@ -830,7 +814,6 @@ sl_status sl_batch_destroy(sl_batch* b)
     if (b->side) (void)hipStreamDestroy(b->side);
     if (b->par) (void)hipStreamDestroy(b->par);
     if (b->cap) (void)hipStreamDestroy(b->cap);
-    if (b->h_jobs) (void)hipHostFree(b->h_jobs);
     for (int k = 0; k < 2; ++k)
         if (b->h_up[k]) (void)hipHostFree(b->h_up[k]);
     if (b->h_stage) (void)hipHostFree(b->h_stage);

@@ -255,22 +255,9 @@ __global__ void __launch_bounds__(simplek::kResidentBlock) k_batch_resident(cons
 __global__ void __launch_bounds__(256) k_batch_fold(const BatchFold* __restrict__ tab, int64_t* out)
 {
     const BatchFold f = tab[blockIdx.x];
-    for (uint32_t i = threadIdx.x; i < f.n; i += 256) {
-        unsigned long long* slot = f.ring + (uint64_t)i * kSlotWords;
-        int64_t sum[kQ] = {0, 0, 0, 0};
-        for (int s = 0; s < kSub; ++s)
-#pragma unroll
-            for (int q = 0; q < kQ; ++q) {
-                sum[q] += (int64_t)slot[s * kSubStride + q];
-                slot[s * kSubStride + q] = 0ull;
-            }
-        int64_t* o = out + (f.out_off + i) * kRecordWords;
-        o[0] = (int64_t)(f.first_t + i);
-        o[1] = sum[0];
-        o[2] = sum[1];
-        o[3] = sum[2];
-        o[4] = f.ising ? -1 : sum[3];
-    }
+    for (uint32_t i = threadIdx.x / kSub; i < f.n; i += 256 / kSub)
+        fold_record(f.ring + (uint64_t)i * kSlotWords, threadIdx.x % kSub, out + (f.out_off + i) * kRecordWords,
+                    f.first_t + i, f.ising != 0);
 }
 
 }  // namespace

@@ -32,6 +32,25 @@ sl_status hip_fail(hipError_t e, const char* what)
     return fail(SL_E_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 
+hipError_t start_lattice(const SweepArgs& a, const sl_params* p, int kind, uint64_t bern, unsigned long long* ring,
+                         uint64_t ring_words, void* tables_dst, const void* tables, size_t bytes, hipStream_t stream)
+{
+    StartBlob blob{};
+    if (bytes > sizeof(blob.w) || bytes % sizeof(uint32_t)) return hipErrorInvalidValue;
+    std::memcpy(blob.w, tables, bytes);
+    StartArgs s{};
+    s.a = a;
+    s.nat = p->init == SL_INIT_BUFFER ? p->init_spins : nullptr;
+    s.thr = bern;
+    s.ring = ring;
+    s.ring_words = ring_words;
+    s.blob_dst = static_cast<uint32_t*>(tables_dst);
+    s.blob_words = (uint32_t)(bytes / sizeof(uint32_t));
+    s.random = p->init == SL_INIT_COLD ? 0 : 1;
+    s.aligned = natural_aligned(s.nat);
+    return launch_start(s, kind, blob, stream);
+}
+
 }  // namespace host
 }  // namespace spinlat
 
@@ -85,7 +104,6 @@ SweepArgs args_of(const sl_lattice* h)
     a.key1 = (uint32_t)(h->params.seed >> 32);
     a.lut = reinterpret_cast<const uint64_t*>(h->base + h->lay.off_lut);
     a.lut_n = (int32_t)h->table_n;
-    a.update = 1;
     a.tile_rows = h->launch.tile_rows;
     a.tile_words = h->launch.tile_words;
     return a;
@@ -304,18 +322,13 @@ sl_status check_launch(const sl_lattice* h, sl_launch* l)
     return fail(SL_E_INVALID, "unknown launch mode %d", l->mode);
 }
 
-// Record of the current state without any update (r_0): both colours with
-// update = 0 through the direct kernel.
+// Record of the current state without any update (r_0).
 sl_status enqueue_observe(sl_lattice* h, uint64_t slot)
 {
     SweepArgs a = args_of(h);
-    a.update = 0;
     a.acc = slot_ptr(h, slot);
-    for (uint32_t c = 0; c < 2; ++c) {
-        a.colour = c;
-        hipError_t e = launch_simple_half(a, h->kind, h->stream);
-        if (e != hipSuccess) return hip_fail(e, "observe kernel");
-    }
+    const hipError_t e = launch_observe(a, h->kind, h->stream);
+    if (e != hipSuccess) return hip_fail(e, "observe kernel");
     return SL_OK;
 }
 
@@ -568,22 +581,9 @@ sl_status sl_create_lattice(const sl_params* params, void* device_buf, size_t by
         delete h;
         return hip_fail(e, "create: pinned record staging");
     }
-    e = hipMemcpyAsync(h->base + lay.off_lut, h->table, h->table_n * sizeof(uint64_t),
-                                  hipMemcpyHostToDevice, h->stream);
-    if (e == hipSuccess)
-        e = launch_fill_u64(slot_ptr(h, 0), params->record_capacity * kSlotWords, h->stream);
-    if (e != hipSuccess) {
-        release(h);
-        return hip_fail(e, "create: table upload / ring clear");
-    }
-    SweepArgs a = args_of(h);
-    if (params->init == SL_INIT_BUFFER) {
-        e = launch_from_natural(a, params->init_spins, h->stream);
-    } else {
-        const uint64_t bern = thr_from_prob(params->c);
-        e = launch_init(a, h->kind, params->init == SL_INIT_COLD ? 0 : 1, (uint32_t)bern,
-                        (uint32_t)(bern >> 32), h->stream);
-    }
+    e = start_lattice(args_of(h), params, h->kind, thr_from_prob(params->c), slot_ptr(h, 0),
+                      params->record_capacity * kSlotWords, h->base + lay.off_lut, h->table,
+                      h->table_n * sizeof(uint64_t), h->stream);
     if (e != hipSuccess) {
         release(h);
         return hip_fail(e, "create: initial state");
@@ -594,7 +594,7 @@ sl_status sl_create_lattice(const sl_params* params, void* device_buf, size_t by
         return st;
     }
     h->pending = 1;
-    // the table upload reads h->table; keep it alive until the copy is done
+    // init_spins may be released once the call returns
     e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) {
         release(h);

@@ -32,17 +32,15 @@ __device__ __forceinline__ int move_ne_coupled(int byte, int north, int east, in
 // ---------------------------------------------------------------------------
 // Direct update of one 4-site word gi of colour c: the neighbours are read
 // straight from the other colour array (global memory, or LDS in the resident
-// kernel).  With update == 0 only the observables of the current state are
-// accumulated (record r_0).  `coupled` (NE only) takes the Ising rates of the
+// kernel).  `coupled` (NE only) takes the Ising rates of the
 // spin-1/2 table instead of the two J = 0 thresholds.
 template <int KIND, int DIM>
 __device__ __forceinline__ void simple_word(uint8_t* own, const int8_t* oth, const Geom& g, uint32_t c,
-                                            uint64_t gi, uint32_t t, int update, const PhiloxKey& ks,
+                                            uint64_t gi, uint32_t t, const PhiloxKey& ks,
                                             const uint64_t* lut, bool coupled, int32_t& q_bond,
                                             int32_t& q_mag, int32_t& q_acc, int32_t& q_unfl)
 {
     {
-        const bool upd = update != 0;
         const uint64_t k0 = gi * 4;
         const uint64_t row = k0 / g.Lh;
         const uint32_t kk0 = (uint32_t)(k0 - row * g.Lh);
@@ -55,14 +53,12 @@ __device__ __forceinline__ void simple_word(uint8_t* own, const int8_t* oth, con
         const uint64_t r_zp = (uint64_t)wrap_inc(zc, g.L) * g.L + y;
 
         const uint32_t cur = *reinterpret_cast<const uint32_t*>(own + k0);
-        Words4 wa = {{0, 0, 0, 0}}, wb = {{0, 0, 0, 0}};
-        if (upd) {
-            if (KIND == KIND_ISING_ONE) {
-                wa = philox4x32_10((uint32_t)(2 * gi), c, t, 0u, ks);
-                wb = philox4x32_10((uint32_t)(2 * gi + 1), c, t, 0u, ks);
-            } else {
-                wa = philox4x32_10((uint32_t)gi, c, t, 0u, ks);
-            }
+        Words4 wa, wb = {{0, 0, 0, 0}};
+        if (KIND == KIND_ISING_ONE) {
+            wa = philox4x32_10((uint32_t)(2 * gi), c, t, 0u, ks);
+            wb = philox4x32_10((uint32_t)(2 * gi + 1), c, t, 0u, ks);
+        } else {
+            wa = philox4x32_10((uint32_t)gi, c, t, 0u, ks);
         }
         constexpr int z = 2 * DIM;
         uint32_t out = 0;
@@ -80,8 +76,7 @@ __device__ __forceinline__ void simple_word(uint8_t* own, const int8_t* oth, con
                     south = oth[r_yp * g.Lh + kk];
                     west = oth[row * g.Lh + (p ? kk : kside)];
                 }
-                if (!upd) nv = sv;
-                else if (coupled) nv = move_ne_coupled(sv, north, east, south, west, wa.w[b], lut);
+                if (coupled) nv = move_ne_coupled(sv, north, east, south, west, wa.w[b], lut);
                 else nv = move_ne(sv, north, east, wa.w[b], lut[0], lut[1]);
                 q_mag += nv & 1;
                 q_unfl += (nv & 2) ? 0 : 1;
@@ -90,9 +85,7 @@ __device__ __forceinline__ void simple_word(uint8_t* own, const int8_t* oth, con
                 int nsum = oth[row * g.Lh + kk] + oth[row * g.Lh + kside] + oth[r_ym * g.Lh + kk] +
                            oth[r_yp * g.Lh + kk];
                 if (DIM == 3) nsum += oth[r_zm * g.Lh + kk] + oth[r_zp * g.Lh + kk];
-                if (!upd) {
-                    nv = sv;
-                } else if (KIND == KIND_ISING_HALF) {
+                if (KIND == KIND_ISING_HALF) {
                     nv = move_ising_half(sv, nsum, wa.w[b], lut, z);
                 } else {
                     const Words4& w = (b < 2) ? wa : wb;
@@ -104,7 +97,7 @@ __device__ __forceinline__ void simple_word(uint8_t* own, const int8_t* oth, con
             q_acc += (nv != sv) ? 1 : 0;
             out |= (uint32_t)(uint8_t)(int8_t)nv << (8 * b);
         }
-        if (upd) *reinterpret_cast<uint32_t*>(own + k0) = out;
+        *reinterpret_cast<uint32_t*>(own + k0) = out;
     }
 }
 
@@ -135,7 +128,7 @@ __device__ __forceinline__ void resident_run(const SweepArgs& a, uint32_t nsweep
             uint8_t* own = sm + c * nh;
             const int8_t* oth = reinterpret_cast<const int8_t*>(sm + (c ^ 1u) * nh);
             for (uint32_t gi = threadIdx.x; gi < nwords; gi += kResidentBlock)
-                simple_word<KIND, DIM>(own, oth, a.g, c, gi, a.t + s, 1, ks, lut, coupled, q_bond, q_mag,
+                simple_word<KIND, DIM>(own, oth, a.g, c, gi, a.t + s, ks, lut, coupled, q_bond, q_mag,
                                        q_acc, q_unfl);
             __syncthreads();
         }

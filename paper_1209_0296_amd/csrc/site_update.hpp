@@ -133,4 +133,28 @@ __device__ __forceinline__ void lane_accumulate(const int32_t (&v)[kQ], LanePart
     }
 }
 
+// Record of one ring slot by a row of 16 lanes (lane `sub` of it takes
+// sub-slot `sub`): the sub-slots' sums as {t, q0 .. q3}, the slot cleared.
+__device__ __forceinline__ void fold_record(unsigned long long* slot, uint32_t sub, int64_t* out, uint64_t t, bool ising)
+{
+    unsigned long long* p = slot + sub * kSubStride;
+    int64_t q[kQ];
+#pragma unroll
+    for (int k = 0; k < kQ; ++k) {
+        q[k] = (int64_t)p[k];
+        p[k] = 0ull;
+    }
+#pragma unroll
+    for (int k = 0; k < kQ; ++k)
+#pragma unroll
+        for (int off = kSub / 2; off > 0; off >>= 1) q[k] += __shfl_xor(q[k], off, kSub);
+    if (sub == 0) {
+        out[0] = (int64_t)t;
+        out[1] = q[0];
+        out[2] = q[1];
+        out[3] = q[2];
+        out[4] = ising ? -1 : q[3];
+    }
+}
+
 }  // namespace spinlat

@@ -28,7 +28,6 @@ struct SweepArgs {
     uint32_t key0, key1;      // Philox key = seed
     uint32_t t;               // sweep index
     uint32_t colour;          // half-sweep colour (SIMPLE/HALF modes)
-    int32_t update;           // 0: only accumulate observables (record r_0)
     int32_t lut_n;
     unsigned long long* acc;  // record slot [kSub][kQ]
     const uint64_t* lut;      // threshold table (device), lut_n entries
@@ -46,9 +45,27 @@ __device__ __forceinline__ uint8_t* colour_array(const SweepArgs& a, uint32_t c)
 }
 
 hipError_t launch_fill_u64(unsigned long long* p, uint64_t n, hipStream_t s);
-hipError_t launch_init(const SweepArgs& a, int kind, int init_mode, uint32_t bern_thr_lo,
-                       uint32_t bern_thr_hi, hipStream_t s);
-hipError_t launch_from_natural(const SweepArgs& a, const int8_t* nat, hipStream_t s);
+// A new lattice in a.col: its start, its cleared record ring and the host's
+// tables (`blob`) at blob_dst, in one launch.
+struct StartArgs {
+    SweepArgs a;
+    const int8_t* nat;             // SL_INIT_BUFFER: natural-order spins, else null
+    uint64_t thr;                  // NE: initial up-density threshold
+    unsigned long long* ring;      // ring_words u64 to clear
+    uint64_t ring_words;
+    uint32_t* blob_dst;
+    uint32_t blob_words;
+    int32_t random;                // else cold
+    int32_t aligned;               // nat is 8-byte aligned
+};
+constexpr uint32_t kStartBlobWords = 160;
+struct StartBlob {
+    uint32_t w[kStartBlobWords];
+};
+inline int natural_aligned(const int8_t* nat) { return (reinterpret_cast<uintptr_t>(nat) & 7u) == 0 ? 1 : 0; }
+hipError_t launch_start(const StartArgs& s, int kind, const StartBlob& blob, hipStream_t st);
+// Record of the lattice as it is, added to a.acc.
+hipError_t launch_observe(const SweepArgs& a, int kind, hipStream_t s);
 hipError_t launch_to_natural(const SweepArgs& a, int8_t* nat, hipStream_t s);
 hipError_t launch_clear_flags(const SweepArgs& a, hipStream_t s);
 // Small lattices: both colour arrays in the LDS of one workgroup, nsweeps

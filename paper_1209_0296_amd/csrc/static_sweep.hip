@@ -39,15 +39,6 @@ static __device__ __align__(256) uint8_t scratch[kStaticScratchBytes];
 std::mutex g_mutex;
 uint8_t* g_scratch[kMaxDevices] = {};  // device address of `scratch` per device
 
-struct TableArg {
-    unsigned long long v[kMaxLut];
-};
-
-__global__ void k_store_table(unsigned long long* dst, TableArg t, int n)
-{
-    if ((int)threadIdx.x < n) dst[threadIdx.x] = t.v[threadIdx.x];
-}
-
 // Device address of this device's `scratch`, looked up once per device.
 sl_status scratch_of(uint8_t** out)
 {
@@ -104,23 +95,10 @@ sl_status sl_sweep_static(const sl_params* params, uint64_t n, int8_t* spins_out
     h.launch = auto_launch(&h, &h.tile, &h.plane);
     h.stage = nullptr;
 
-    TableArg tab{};
-    for (size_t i = 0; i < h.table_n; ++i) tab.v[i] = h.table[i];
-    hipLaunchKernelGGL(k_store_table, dim3(1), dim3(kMaxLut), 0, h.stream,
-                       reinterpret_cast<unsigned long long*>(base + lay.off_lut), tab, (int)h.table_n);
-    hipError_t e = hipGetLastError();
-    // the ring keeps the last call's sums: clear it with a kernel (no memset node)
-    if (e == hipSuccess) e = launch_fill_u64(slot_ptr(&h, 0), (uint64_t)kStaticRing * kSlotWords, h.stream);
-    SweepArgs a = args_of(&h);
-    if (e == hipSuccess) {
-        if (p.init == SL_INIT_BUFFER) {
-            e = launch_from_natural(a, p.init_spins, h.stream);
-        } else {
-            const uint64_t bern = thr_from_prob(p.c);
-            e = launch_init(a, h.kind, p.init == SL_INIT_COLD ? 0 : 1, (uint32_t)bern, (uint32_t)(bern >> 32),
-                            h.stream);
-        }
-    }
+    // the ring keeps the last call's sums: the start kernel clears it (no memset node)
+    hipError_t e = start_lattice(args_of(&h), &p, h.kind, thr_from_prob(p.c), slot_ptr(&h, 0),
+                                 (uint64_t)kStaticRing * kSlotWords, base + lay.off_lut, h.table,
+                                 h.table_n * sizeof(uint64_t), h.stream);
     if (e != hipSuccess) return hip_fail(e, "sweep_static: set-up");
     st = enqueue_observe(&h, 0);
     if (st != SL_OK) return st;
