@@ -11,46 +11,60 @@
 // the launch reads one copy of the lattice and writes the other.  Neighbours
 // in the same sub-lattice are read as they were at the start of the iteration.
 //
+// Balanced variant (end of Sec. 3.2): each iteration draws lambda sites of
+// colour 0, then lambda sites of colour 1 (half h); P/(8 lambda) iterations per
+// launch, four launches per sweep.  Sites of one colour are not neighbours, so
+// the attempts of a half only read frozen neighbours; when attempts of a half
+// draw the same site only the lowest-numbered one applies.
+//
 // Mapping: a sub-lattice belongs to one wavefront, lambda/2 lanes of it, each
-// lane making two attempts per iteration from one Philox4x32-10 call
-// (counter (tau, a/2, launch, 2) for attempts a, a+1).  Because a whole
-// sub-lattice lives in one wavefront, the iteration needs no barrier: the
-// wavefront's LDS instructions execute in program order, so every read of an
-// iteration precedes every write of it.  A workgroup is one wavefront holding
-// up to 64/(lambda/2) sub-lattices in LDS.
+// lane making two attempts per step (an iteration, or a half of one) from one
+// Philox4x32-10 call (counter (tau, a/2, launch, 2) for attempts a, a+1; tag 3
+// when balanced).  Because a whole sub-lattice lives in one wavefront, a step
+// needs no barrier: the wavefront's LDS instructions execute in program order,
+// so every read of a step precedes every write of it.  A workgroup is one
+// wavefront holding up to 64/(lambda/2) sub-lattices in LDS.
 //
-// LDS holds each sub-lattice in natural order: B+1 rows of stride S = B + 8
-// (row 0 = the north row, rows 1..B = the sub-lattice), with the east column
-// in column B.  A site's north and east neighbours are then at fixed offsets
-// (-S, +1) from it, so an attempt costs three byte reads from one address.
-// The colour-split rows of HBM are interleaved on the way in and split on the
-// way out.
+// What bounds it: instructions.  At L = 4096, B = 32, lambda = 16 the algorithm
+// leaves 2 waves per SIMD, all resident at once, so a launch is the sum of its
+// phases: 4.5 us to start, load and store, 11 us for 32 steps, of which the draws
+// are 4.7.  Hence as little as possible around a draw:
+// - LDS holds each sub-lattice as one bit row per lattice row (the occupations;
+//   the north row first), so an attempt's site and its north and east neighbours
+//   are two rows read by one instruction and 12 instructions decide it.  The rows
+//   of two steps are read together; the second's again only if an attempt of the
+//   wavefront was accepted in the first.  (Four steps together 16.0 us a launch,
+//   two 15.7.  Deciding four steps from the same rows and again after an accepted
+//   one: 20.0 us against 18.8 then.)
+// - Accepted moves are kept as lane masks, so the test whether there are any is
+//   scalar (as bools: 18.3 us a launch).
+// - Between the launches of one call the lattice is kept as those bit rows, an
+//   eighth of the bytes for the occupations and as much for the flags: 8 MB
+//   instead of 33 MB a launch, and nothing to repack.  The call's first launch
+//   reads colour arrays, its last one writes them.  (Colour arrays at every
+//   launch: 24 us.)
+// Before, with bytes in LDS and memory and three byte reads per attempt: 22.2 us.
 //
-// Accepted moves: the move sets n to 1-n and raises the "has flipped" flag
-// with LDS atomics on the containing 32-bit word (AND clears n for a
-// down-flip, OR sets n for an up-flip and sets the flag).  Attempts of one
-// iteration on one site all see the same iteration-start n, so the value an
+// Accepted moves clear or set the site's bit with LDS atomics (AND for a
+// down-flip, OR for an up-flip; both are issued, one of them with nothing to
+// do, and nothing waits until the last) and set its "has flipped" flag in a
+// second bit row.  Attempts of one step on one site all see the same n, so the value an
 // atomic returns tells whether another attempt already changed the site: each
-// changed site is counted once, and a site drawn twice flips once.  The four
-// atomics of a lane's two attempts are issued back to back (no-op masks for an
-// attempt that was not accepted).
-//
-// Latency: the Philox words of iteration j+1 do not depend on the lattice, so
-// they are computed while iteration j's LDS traffic is in flight.
+// changed site is counted once, and a site drawn twice flips once.  The balanced
+// variant keeps an owner word per site of a colour for the steps with accepted
+// moves: attempts post their number with an LDS atomic minimum, read it back, and
+// only the owner may apply its move.
 //
 // Records: the first launch of a sweep also measures the lattice it starts
 // from -- the state after the previous sweep -- from the sub-lattices it has
 // just loaded (bonds to the north and east neighbours, which tile the lattice's
 // bonds exactly once), so no separate pass reads the lattice for that record.
-//
-// The balanced variant (k_ne_bal, end of Sec. 3.2) shares the loads, stores and
-// records; its iterations alternate the two colours of the sub-lattice and
-// four launches make a sweep (see the comment above the kernel).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "philox.hpp"
+#include "site_update.hpp"
 #include "spinlat_internal.h"
 
 namespace spinlat {
@@ -63,42 +77,72 @@ constexpr uint32_t kTagNeBal = 3u;
 
 constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
 
+// ---- bit rows --------------------------------------------------------------
+// Row: a row in LDS and registers; Bits: a row, or a column, between launches.
 template <int B>
-struct SubLayout {
-    static constexpr int half = B / 2;                  // bytes of a colour row
-    static constexpr int stride = B + 8;                // LDS row stride (8-byte aligned)
-    static constexpr int bytes = (B + 1) * stride;      // one sub-lattice with its boundary
-    static constexpr int unit = half < 16 ? half : 16;  // bytes of a colour vector copy
-    static constexpr int units_per_row = half / unit;
+struct BitRows;
+template <>
+struct BitRows<8> {
+    using Row = uint32_t;
+    using Bits = uint8_t;
+};
+template <>
+struct BitRows<16> {
+    using Row = uint32_t;
+    using Bits = uint16_t;
+};
+template <>
+struct BitRows<32> {
+    using Row = uint32_t;
+    using Bits = uint32_t;
+};
+template <>
+struct BitRows<64> {
+    using Row = unsigned long long;
+    using Bits = unsigned long long;
 };
 
-template <int B, int LPT>
+// LDS of one sub-lattice: rows[0] the north row, rows[1 ..] its own, their
+// flags, and (B >= 32) the east column.  For B < 32 the east neighbour of a
+// row's last site is bit B of the row.
+template <int B>
+struct BitTile {
+    typename BitRows<B>::Row rows[B + 1], flags[B];
+    typename BitRows<B>::Row ecol;
+};
+
+template <int B, bool BAL>
+constexpr int owner_words()
+{
+    return BAL ? B * B / 2 : 0;
+}
+
+template <int B, int LPT, bool BAL>
 constexpr int tiles_per_wave()
 {
-    return (64 / LPT) < (kLdsBudget / SubLayout<B>::bytes) ? (64 / LPT)
-                                                           : (kLdsBudget / SubLayout<B>::bytes);
+    constexpr int fit = kLdsBudget / ((int)sizeof(BitTile<B>) + 4 * owner_words<B, BAL>());
+    return 64 / LPT < fit ? 64 / LPT : fit;
 }
+
+// The lattice between launches, in the colour arrays' memory: occupations as
+// Bits[sub-lattice][row] in colour 0's; in colour 1's the flags likewise, then
+// each sub-lattice's first column.  B / 8 bytes a row of B / 2 per colour.
+template <int B>
+struct BitLattice {
+    using Bits = typename BitRows<B>::Bits;
+    Bits *rows, *flags, *column;
+    __device__ __forceinline__ BitLattice(uint8_t* c0, uint8_t* c1, uint32_t ntiles)
+        : rows(reinterpret_cast<Bits*>(c0)),
+          flags(reinterpret_cast<Bits*>(c1)),
+          column(reinterpret_cast<Bits*>(c1) + (size_t)ntiles * B)
+    {
+    }
+};
 
 template <int N>
 struct ColourVec {
     uint32_t w[N / 4];
 };
-
-// Natural order from colour order: e holds the sites at even x, o those at
-// odd x (4 each); the result is the 8 sites in x order.
-__device__ __forceinline__ uint2 interleave(uint32_t e, uint32_t o)
-{
-    uint2 r;
-    r.x = (e & 0xFFu) | ((o & 0xFFu) << 8) | ((e & 0xFF00u) << 8) | ((o & 0xFF00u) << 16);
-    r.y = ((e >> 16) & 0xFFu) | ((o >> 8) & 0xFF00u) | ((e >> 8) & 0xFF0000u) | (o & 0xFF000000u);
-    return r;
-}
-
-__device__ __forceinline__ void split(uint2 v, uint32_t& e, uint32_t& o)
-{
-    e = (v.x & 0xFFu) | ((v.x >> 8) & 0xFF00u) | ((v.y & 0xFFu) << 16) | ((v.y << 8) & 0xFF000000u);
-    o = ((v.x >> 8) & 0xFFu) | ((v.x >> 16) & 0xFF00u) | ((v.y << 8) & 0xFF0000u) | (v.y & 0xFF000000u);
-}
 
 template <int N>
 __device__ __forceinline__ ColourVec<N> load_vec(const uint8_t* p)
@@ -128,156 +172,251 @@ __device__ __forceinline__ void store_vec(uint8_t* p, const ColourVec<N>& v)
     }
 }
 
-// Measurement of the sub-lattice as loaded (launch-start state): occupation,
-// bonds to the north and east neighbours, sites with the flag clear.
+// A lane's rows in steps of up to 64 registers of loads in flight.
 template <int B, int LPT>
-__device__ __forceinline__ void observe_tile(const uint8_t* t, uint32_t l, int& mag, int& bond,
-                                             int& fresh)
+struct RowSteps {
+    static constexpr int most = B <= 32 ? 8 : 4;
+    static constexpr int rows = (B + LPT) / LPT;  // of B + 1, per lane
+    static constexpr int steps = (rows + most - 1) / most;
+    static constexpr int per_step = (rows + steps - 1) / steps;
+};
+
+// Bit k of each byte of e (4 sites at even x) and o (odd x), in x order: the
+// result's bits k .. k + 7.
+template <int K>
+__device__ __forceinline__ uint32_t gather8(uint32_t e, uint32_t o)
 {
-    using Lay = SubLayout<B>;
-    constexpr int WPR = B / 4;  // 4-byte words per row
-    constexpr int NWORD = B * WPR;
-#pragma unroll
-    for (int i = 0; i < (NWORD + LPT - 1) / LPT; ++i) {
-        const int u = (int)l + i * LPT;
-        if (u < NWORD) {
-            const uint8_t* p = t + (1 + u / WPR) * Lay::stride + 4 * (u % WPR);
-            const uint32_t v = *reinterpret_cast<const uint32_t*>(p);
-            const uint32_t north = *reinterpret_cast<const uint32_t*>(p - Lay::stride);
-            const uint32_t next = *reinterpret_cast<const uint32_t*>(p + 4);
-            const uint32_t east = __builtin_amdgcn_alignbyte(next, v, 1);
-            const uint32_t nv = v & 0x01010101u;
-            mag += __builtin_popcount(nv);
-            bond += __builtin_popcount(nv & north) + __builtin_popcount(nv & east);
-            fresh += 4 - __builtin_popcount(v & 0x02020202u);
-        }
-    }
+    const uint32_t lo = __builtin_amdgcn_udot4(o & (0x01010101u << K), 0x80200802u, 0u, false);
+    return __builtin_amdgcn_udot4(e & (0x01010101u << K), 0x40100401u, lo, false);
 }
 
-// LDS offsets of a site and of its north and east neighbours.
-template <int B, bool WRAP>
-__device__ __forceinline__ void site_offsets(uint32_t site, uint32_t& own, uint32_t& north,
-                                             uint32_t& east)
+// Bits 0, 2, 4, 6 of v to bit 0 of bytes 0 .. 3 (the products' other terms meet
+// in bits that no byte starts at).
+__device__ __forceinline__ uint32_t spread4(uint32_t v)
 {
-    constexpr int S = SubLayout<B>::stride;
-    constexpr int LOGB = ilog2(B);
-    const uint32_t r = site >> LOGB;
-    if constexpr (!WRAP) {
-        north = site + r * (S - B);  // r * S + c
-        own = north + S;
-        east = own + 1;
-    } else {  // one sub-lattice: the periodic neighbours are inside it
-        const uint32_t c = site & (B - 1);
-        own = (r + 1) * S + c;
-        north = (r == 0 ? (uint32_t)B : r) * S + c;
-        east = (r + 1) * S + (c == B - 1 ? 0u : c + 1);
-    }
+    return __umul24(v & 0x55u, 0x41041u) & 0x01010101u;
 }
 
-// Copy sub-lattice tau with its north row and east column from the colour
-// arrays into LDS (natural order, see SubLayout); lanes l of LPT share it.
+// Sub-lattice (x0, y0) of the colour arrays into bit rows; lanes l of LPT share it.
 template <int B, int LPT>
-__device__ __forceinline__ void load_tile(const NeSubArgs& a, uint8_t* t, uint32_t l, uint32_t x0,
-                                          uint32_t y0)
+__device__ __forceinline__ void load_colours(const NeSubArgs& a, BitTile<B>& t, uint32_t l, uint32_t x0, uint32_t y0)
 {
-    using Lay = SubLayout<B>;
-    constexpr int S = Lay::stride;
-    constexpr int UNIT = Lay::unit;
-    constexpr int NU = (B + 1) * Lay::units_per_row;  // colour-vector pairs
-    const uint32_t ynorth = y0 == 0 ? a.L - 1 : y0 - 1;
-    const size_t kx = x0 >> 1;
-    // north row and sub-lattice rows: both colours, interleaved
-#pragma unroll
-    for (int i = 0; i < (NU + LPT - 1) / LPT; ++i) {
-        const int u = (int)l + i * LPT;
-        if (u < NU) {
-            const int pr = u / Lay::units_per_row, part = u % Lay::units_per_row;
-            const uint32_t y = pr == 0 ? ynorth : y0 + pr - 1;
-            const size_t off = (size_t)y * a.Lh + kx + part * UNIT;
-            const ColourVec<UNIT> c0 = load_vec<UNIT>(a.src[0] + off);
-            const ColourVec<UNIT> c1 = load_vec<UNIT>(a.src[1] + off);
-            const bool odd = (y & 1u) != 0;  // colour 1 holds the even x of odd rows
-            uint2* dstp = reinterpret_cast<uint2*>(t + pr * S + part * 2 * UNIT);
-#pragma unroll
-            for (int k = 0; k < UNIT / 4; ++k)
-                dstp[k] = odd ? interleave(c1.w[k], c0.w[k]) : interleave(c0.w[k], c1.w[k]);
-        }
-    }
-    // east column: site (x0 + B, y) has colour (x0 + B + y) & 1
+    using Row = typename BitRows<B>::Row;
+    using Steps = RowSteps<B, LPT>;
+    constexpr int UNIT = B / 2 < 16 ? B / 2 : 16;  // bytes of a colour vector load
+    constexpr int NV = B / 2 / UNIT;
+    constexpr int K = Steps::per_step;
     const uint32_t xe = x0 + B == a.L ? 0u : x0 + B;
+    if (B >= 32 && l == 0) t.ecol = 0;
+    Row ecol = 0;
+#pragma nounroll
+    for (int s = 0; s < Steps::steps; ++s) {
+        ColourVec<UNIT> e[K][NV], o[K][NV];
+        uint32_t east[K];
 #pragma unroll
-    for (int i = 0; i < (B + LPT - 1) / LPT; ++i) {
-        const int r = (int)l + i * LPT;
-        if (r < B) {
-            const uint32_t y = y0 + r;
-            t[(r + 1) * S + B] = a.src[(xe + y) & 1u][(size_t)y * a.Lh + (xe >> 1)];
+        for (int i = 0; i < K; ++i) {
+            const uint32_t pr = min(l + (uint32_t)((s * K + i) * LPT), (uint32_t)B);
+            const uint32_t y = pr == 0 ? (y0 == 0 ? a.L - 1 : y0 - 1) : y0 + pr - 1u;
+            const size_t off = (size_t)y * a.Lh;
+            // colour 1 holds the even x of odd rows
+            const uint8_t* even = ((y & 1u) != 0 ? a.src[1] : a.src[0]) + off + (x0 >> 1);
+            const uint8_t* odd = ((y & 1u) != 0 ? a.src[0] : a.src[1]) + off + (x0 >> 1);
+#pragma unroll
+            for (int u = 0; u < NV; ++u) {
+                e[i][u] = load_vec<UNIT>(even + u * UNIT);
+                o[i][u] = load_vec<UNIT>(odd + u * UNIT);
+            }
+            // east neighbour of the row's last site: colour (x0 + B + y) & 1
+            east[i] = a.src[(xe + y) & 1u][off + (xe >> 1)];
         }
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            const uint32_t pr = l + (uint32_t)((s * K + i) * LPT);
+            Row row = 0, flags = 0;
+#pragma unroll
+            for (int u = 0; u < NV; ++u)
+#pragma unroll
+                for (int k = 0; k < UNIT / 4; ++k) {
+                    const int sh = 8 * (u * (UNIT / 4) + k);
+                    row |= (Row)gather8<0>(e[i][u].w[k], o[i][u].w[k]) << sh;
+                    flags |= (Row)(gather8<1>(e[i][u].w[k], o[i][u].w[k]) >> 1) << sh;
+                }
+            if (B < 32) row |= (Row)(east[i] & 1u) << (B & 31);
+            if (pr <= (uint32_t)B) t.rows[pr] = row;
+            if (pr - 1u < (uint32_t)B) {
+                t.flags[pr - 1u] = flags;
+                if (B >= 32) ecol |= (Row)(east[i] & 1u) << (pr - 1u);
+            }
+        }
+    }
+    if (B >= 32) atomicOr(&t.ecol, ecol);
+}
+
+// Sub-lattice (tx, ty) of bit rows.
+template <int B, int LPT>
+__device__ __forceinline__ void load_bits(const NeSubArgs& a, BitTile<B>& t, uint32_t l, uint32_t tx, uint32_t ty)
+{
+    using Row = typename BitRows<B>::Row;
+    using Bits = typename BitRows<B>::Bits;
+    constexpr int R = (B + LPT - 1) / LPT;
+    constexpr int K = R < 8 ? R : 8;  // rows in flight
+    const BitLattice<B> src(const_cast<uint8_t*>(a.src[0]), const_cast<uint8_t*>(a.src[1]), a.ntiles);
+    const uint32_t tau = ty * a.tiles_x + tx;
+    const uint32_t north = (ty == 0 ? a.tiles_x - 1 : ty - 1) * a.tiles_x + tx;
+    const uint32_t east = ty * a.tiles_x + (tx + 1 == a.tiles_x ? 0u : tx + 1);
+    const Bits column = src.column[east];
+    const Row above = src.rows[(size_t)north * B + (B - 1)];
+#pragma nounroll
+    for (int i0 = 0; i0 < R; i0 += K) {
+        Bits row[K], flags[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            const uint32_t r = min(l + (uint32_t)((i0 + i) * LPT), (uint32_t)(B - 1));
+            row[i] = src.rows[(size_t)tau * B + r];
+            flags[i] = src.flags[(size_t)tau * B + r];
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            const uint32_t r = l + (uint32_t)((i0 + i) * LPT);
+            if (r < (uint32_t)B) {
+                t.rows[r + 1] = B < 32 ? (Row)row[i] | (((Row)column >> r) & 1u) << (B & 31) : (Row)row[i];
+                t.flags[r] = flags[i];
+            }
+        }
+    }
+    if (l == 0) {
+        t.rows[0] = above;
+        t.ecol = column;
     }
 }
 
-// The sub-lattice rows back to the colour arrays of the destination copy.
+// Occupation, bonds to the north and east neighbours, and sites with the flag
+// clear, of the rows as loaded.
 template <int B, int LPT>
-__device__ __forceinline__ void store_tile(const NeSubArgs& a, const uint8_t* t, uint32_t l,
-                                           uint32_t x0, uint32_t y0)
+__device__ __forceinline__ void observe_rows(const BitTile<B>& t, uint32_t l, int& mag, int& bond, int& fresh)
 {
-    using Lay = SubLayout<B>;
-    constexpr int S = Lay::stride;
-    constexpr int UNIT = Lay::unit;
-    constexpr int NW = B * Lay::units_per_row;
-    const size_t kx = x0 >> 1;
+    using Row = typename BitRows<B>::Row;
+    constexpr Row mask = B >= 32 ? ~(Row)0 : ((Row)1 << (B & 31)) - 1;
+    for (int r = (int)l; r < B; r += LPT) {
+        const Row row = t.rows[r + 1], n = row & mask;
+        Row east = row >> 1;
+        if (B >= 32) east |= (Row)((t.ecol >> r) & 1u) << (B - 1);
+        mag += __builtin_popcountll(n);
+        bond += __builtin_popcountll(n & t.rows[r]) + __builtin_popcountll(n & east);
+        fresh += B - __builtin_popcountll(t.flags[r]);
+    }
+}
+
+// The rows to the colour arrays of the destination copy.
+template <int B, int LPT>
+__device__ __forceinline__ void store_colours(const NeSubArgs& a, const BitTile<B>& t, uint32_t l, uint32_t x0, uint32_t y0)
+{
+    using Row = typename BitRows<B>::Row;
+    constexpr int UNIT = B / 2 < 16 ? B / 2 : 16;
+#pragma unroll 2
+    for (uint32_t r = l; r < (uint32_t)B; r += LPT) {
+        const Row row = t.rows[r + 1], flags = t.flags[r];
+        const size_t off = (size_t)(y0 + r) * a.Lh + (x0 >> 1);
+        // y0 is even; colour 1 holds the even x of odd rows
+        uint8_t* even = ((r & 1u) != 0 ? a.dst[1] : a.dst[0]) + off;
+        uint8_t* odd = ((r & 1u) != 0 ? a.dst[0] : a.dst[1]) + off;
 #pragma unroll
-    for (int i = 0; i < (NW + LPT - 1) / LPT; ++i) {
-        const int u = (int)l + i * LPT;
-        if (u < NW) {
-            const int r = u / Lay::units_per_row, part = u % Lay::units_per_row;
-            const uint32_t y = y0 + r;
-            const uint2* srcp = reinterpret_cast<const uint2*>(t + (r + 1) * S + part * 2 * UNIT);
-            ColourVec<UNIT> c0, c1;
-            const bool odd = (y & 1u) != 0;
+        for (int u = 0; u < B / 2 / UNIT; ++u) {
+            ColourVec<UNIT> e, o;
 #pragma unroll
             for (int k = 0; k < UNIT / 4; ++k) {
-                uint32_t e, o;
-                split(srcp[k], e, o);
-                c0.w[k] = odd ? o : e;
-                c1.w[k] = odd ? e : o;
+                const int sh = 8 * (u * (UNIT / 4) + k);
+                const uint32_t n8 = (uint32_t)(row >> sh), f8 = (uint32_t)(flags >> sh);
+                e.w[k] = spread4(n8) | (spread4(f8) << 1);
+                o.w[k] = spread4(n8 >> 1) | (spread4(f8 >> 1) << 1);
             }
-            const size_t off = (size_t)y * a.Lh + kx + part * UNIT;
-            store_vec<UNIT>(a.dst[0] + off, c0);
-            store_vec<UNIT>(a.dst[1] + off, c1);
+            store_vec<UNIT>(even + u * UNIT, e);
+            store_vec<UNIT>(odd + u * UNIT, o);
         }
     }
 }
 
-// Wavefront sums of the per-lane counts into the records.
+// The rows as bit rows.
+template <int B, int LPT>
+__device__ __forceinline__ void store_bits(const NeSubArgs& a, BitTile<B>& t, uint32_t l, uint32_t tau)
+{
+    using Row = typename BitRows<B>::Row;
+    using Bits = typename BitRows<B>::Bits;
+    const BitLattice<B> dst(a.dst[0], a.dst[1], a.ntiles);
+    if (l == 0) t.ecol = 0;
+    Row column = 0;
+#pragma unroll 4
+    for (uint32_t r = l; r < (uint32_t)B; r += LPT) {
+        const Row row = t.rows[r + 1];
+        dst.rows[(size_t)tau * B + r] = (Bits)row;
+        dst.flags[(size_t)tau * B + r] = (Bits)t.flags[r];
+        column |= (row & 1u) << r;
+    }
+    atomicOr(&t.ecol, column);
+    asm volatile("" ::: "memory");  // all lanes' parts
+    if (l == 0) dst.column[tau] = (Bits)t.ecol;
+}
+
+// Wavefront sums of the per-lane counts into the records: one atomic
+// instruction, four lanes on one line or two (an instruction each: 1.1 us more
+// per launch of 2048 waves, which meet on kSub lines).
 __device__ __forceinline__ void add_counts(const NeSubArgs& a, uint32_t lane, int changed, int mag,
                                            int bond, int fresh)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) changed += __shfl_xor(changed, off, 64);
-    if (lane == 0 && changed != 0)
-        atomicAdd(&a.acc[(blockIdx.x % kSub) * kSubStride + 2], (unsigned long long)changed);
+    int sum = wave_sum(changed);
+    unsigned long long* p = a.acc + 2;
     if (a.obs) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            mag += __shfl_xor(mag, off, 64);
-            bond += __shfl_xor(bond, off, 64);
-            fresh += __shfl_xor(fresh, off, 64);
+        const int q[3] = {wave_sum(bond), wave_sum(mag), wave_sum(fresh)};
+        if (lane != 2) {
+            sum = lane == 0 ? q[0] : lane == 1 ? q[1] : q[2];
+            p = a.obs + lane;
         }
-        unsigned long long* o = a.obs + (blockIdx.x % kSub) * kSubStride;
-        if (lane == 0 && bond != 0) atomicAdd(&o[0], (unsigned long long)bond);
-        if (lane == 1 && mag != 0) atomicAdd(&o[1], (unsigned long long)mag);
-        if (lane == 2 && fresh != 0) atomicAdd(&o[3], (unsigned long long)fresh);
     }
+    if ((lane == 2 || (a.obs && lane < 4)) && sum != 0)
+        atomicAdd(p + (blockIdx.x % kSub) * kSubStride, (unsigned long long)sum);
 }
 
-template <int B, int LPT, bool WRAP>
+// The site an attempt's word draws: row r, column c() (c5: with other bits above
+// the low 5, which a shift by it ignores).  Balanced: a site of colour h.
+template <int B, bool BAL>
+struct Draw {
+    uint32_t r, c5;
+    __device__ __forceinline__ Draw(uint32_t word, int h)
+        : r(word >> (32 - ilog2(B))),
+          c5(BAL ? 2u * (word >> (33 - 2 * ilog2(B))) + ((r + (uint32_t)h) & 1u) : word >> (32 - 2 * ilog2(B)))
+    {
+    }
+    __device__ __forceinline__ uint32_t c() const { return c5 & (B - 1); }
+};
+
+// The two rows an attempt reads: its own and the one to the north.
+template <int B>
+struct RowPair {
+    typename BitRows<B>::Row north, own;
+};
+
+template <int B, bool WRAP>
+__device__ __forceinline__ RowPair<B> read_rows(const BitTile<B>& t, uint32_t word)
+{
+    const uint32_t r = word >> (32 - ilog2(B));
+    RowPair<B> p;
+    // one sub-lattice: the periodic neighbours are inside it
+    p.north = t.rows[WRAP && r == 0 ? B : r];
+    p.own = t.rows[r + 1];
+    return p;
+}
+
+template <int B, int LPT, bool WRAP, bool BAL>
 __global__ void __launch_bounds__(64) k_ne_sub(NeSubArgs a)
 {
-    using Lay = SubLayout<B>;
-    constexpr int TPW = tiles_per_wave<B, LPT>();
-    constexpr int LOGB = ilog2(B);
-    constexpr int QIT = B * B / (4 * LPT);  // q = P / (2 lambda), lambda = 2 LPT
-    __shared__ __align__(16) uint8_t lds[TPW * Lay::bytes];
+    using Row = typename BitRows<B>::Row;
+    constexpr int TPW = tiles_per_wave<B, LPT, BAL>();
+    constexpr uint32_t TAG = BAL ? kTagNeBal : kTagNeSub;
+    constexpr int STEPS = ne_sub_steps(B, 2 * LPT, BAL);
+    constexpr int G = STEPS < 2 ? 1 : 2;  // steps whose rows are read together
+    constexpr int OW = owner_words<B, BAL>();
+    __shared__ BitTile<B> lds[TPW];
+    __shared__ uint32_t lds_owner[BAL ? TPW * OW : 1];
 
     const uint32_t lane = threadIdx.x;
     const uint32_t g = lane / LPT;
@@ -285,198 +424,154 @@ __global__ void __launch_bounds__(64) k_ne_sub(NeSubArgs a)
     const uint32_t tau = blockIdx.x * TPW + g;
     int changed = 0, mag = 0, bond = 0, fresh = 0;
     if (g < (uint32_t)TPW && tau < a.ntiles) {
-        uint8_t* t = lds + g * Lay::bytes;
+        BitTile<B>& t = lds[g];
+        uint32_t* owner = lds_owner + (BAL ? g * OW : 0);
         const uint32_t tx = tau % a.tiles_x, ty = tau / a.tiles_x;
-        const uint32_t x0 = tx * B, y0 = ty * B;
-        load_tile<B, LPT>(a, t, l, x0, y0);
-
-        if (a.obs) observe_tile<B, LPT>(t, l, mag, bond, fresh);
-
-        const PhiloxKey ks = philox_schedule(a.key0, a.key1);
-        uint32_t* w32 = reinterpret_cast<uint32_t*>(t);
-        Words4 w = philox4x32_10(tau, l, a.launch, kTagNeSub, ks);
-        for (int j = 0; j < QIT; ++j) {
-            uint32_t own[2], nocc[2], vs[2], vn[2], ve[2], acc_word[2];
-            bool ok[2];
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                uint32_t north, east;
-                site_offsets<B, WRAP>(w.w[2 * m] >> (32 - 2 * LOGB), own[m], north, east);
-                vs[m] = t[own[m]];
-                vn[m] = t[north];
-                ve[m] = t[east];
-                acc_word[m] = w.w[2 * m + 1];
-            }
-            // next iteration's words while the reads are in flight; the empty
-            // asm pins them here (the compiler would otherwise sink them past
-            // the atomics, where they would wait for the atomics' results)
-            w = philox4x32_10(tau, (uint32_t)(j + 1) * LPT + l, a.launch, kTagNeSub, ks);
-            asm volatile("" : "+v"(w.w[0]), "+v"(w.w[1]), "+v"(w.w[2]), "+v"(w.w[3]));
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                const uint32_t n = vs[m] & 1u;
-                const uint32_t allow = vn[m] & ve[m] & 1u;
-                // accept iff word < thr, thr in [0, 2^32]: word <= thr - 1 unless thr = 0
-                const uint32_t thr_m1 = n ? a.thr_m1_down : a.thr_m1_up;
-                const uint32_t never = (a.never >> n) & 1u;
-                ok[m] = (allow & (acc_word[m] <= thr_m1 ? 1u : 0u) & (never ^ 1u)) != 0u;
-                nocc[m] = n;
-            }
-            if (ok[0] | ok[1]) {
-                uint32_t sh[2], old_and[2], old_or[2];
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    sh[m] = (own[m] & 3u) * 8u;
-                    const bool dn = ok[m] & (nocc[m] != 0u);
-                    old_and[m] = atomicAnd(w32 + (own[m] >> 2), dn ? ~(1u << sh[m]) : ~0u);
-                }
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    const uint32_t set = ok[m] ? (nocc[m] ? 2u : 3u) : 0u;
-                    old_or[m] = atomicOr(w32 + (own[m] >> 2), set << sh[m]);
-                }
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    // first change of the site in this iteration: n still as at its start
-                    const uint32_t before = nocc[m] ? old_and[m] : old_or[m];
-                    changed += (int)(ok[m] & (((before >> sh[m]) & 1u) == nocc[m]));
-                }
-            }
-        }
-
-        store_tile<B, LPT>(a, t, l, x0, y0);
-    }
-    add_counts(a, lane, changed, mag, bond, fresh);
-}
-
-// Balanced variant: each iteration draws lambda sites of colour 0, then lambda
-// sites of colour 1 (half h); P/(8 lambda) iterations per launch, four
-// launches per sweep.  Sites of one colour are not neighbours, so the
-// attempts of a half only read frozen neighbours; when attempts of a half
-// draw the same site only the lowest-numbered one applies.  Each sub-lattice
-// keeps an owner word per site of the half's colour: attempts post their
-// number with an LDS atomic minimum, read it back, and only the owner
-// evaluates the move and resets the word.  The winner's site is unique, so
-// its store needs no atomic.
-template <int B, int LPT>
-constexpr int bal_tile_bytes()
-{
-    return SubLayout<B>::bytes + 4 * (B * B / 2);
-}
-
-template <int B, int LPT>
-constexpr int bal_tiles_per_wave()
-{
-    return (64 / LPT) < (kLdsBudget / bal_tile_bytes<B, LPT>()) ? (64 / LPT)
-                                                                : (kLdsBudget / bal_tile_bytes<B, LPT>());
-}
-
-template <int B, int LPT, bool WRAP>
-__global__ void __launch_bounds__(64) k_ne_bal(NeSubArgs a)
-{
-    using Lay = SubLayout<B>;
-    constexpr int TB = bal_tile_bytes<B, LPT>();
-    constexpr int TPW = bal_tiles_per_wave<B, LPT>();
-    constexpr int HS = B * B / 2;  // sites of one colour
-    constexpr int LOGHS = ilog2(HS), LOGBH = ilog2(B / 2);
-    constexpr int QIT = B * B / (16 * LPT);  // P / (8 lambda), lambda = 2 LPT
-    static_assert(Lay::bytes % 4 == 0, "owner words must be aligned");
-    __shared__ __align__(16) uint8_t lds[TPW * TB];
-
-    const uint32_t lane = threadIdx.x;
-    const uint32_t g = lane / LPT;
-    const uint32_t l = lane % LPT;
-    const uint32_t tau = blockIdx.x * TPW + g;
-    int changed = 0, mag = 0, bond = 0, fresh = 0;
-    if (g < (uint32_t)TPW && tau < a.ntiles) {
-        uint8_t* t = lds + g * TB;
-        uint32_t* owner = reinterpret_cast<uint32_t*>(t + Lay::bytes);
-        const uint32_t x0 = (tau % a.tiles_x) * B, y0 = (tau / a.tiles_x) * B;
-        load_tile<B, LPT>(a, t, l, x0, y0);
-        for (int i = (int)l; i < HS; i += LPT) owner[i] = 0xFFFFFFFFu;
-        if (a.obs) observe_tile<B, LPT>(t, l, mag, bond, fresh);
-
-        const PhiloxKey ks = philox_schedule(a.key0, a.key1);
-        for (int j = 0; j < QIT; ++j) {
-#pragma unroll
-            for (uint32_t h = 0; h < 2; ++h) {
-                const Words4 w =
-                    philox4x32_10(tau, (2u * j + h) * LPT + l, a.launch, kTagNeBal, ks);
-                uint32_t idx[2], own[2], vs[2], vn[2], ve[2];
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    idx[m] = w.w[2 * m] >> (32 - LOGHS);  // floor(word (P/2) / 2^32)
-                    const uint32_t r = idx[m] >> LOGBH;
-                    const uint32_t cc = 2u * (idx[m] & (B / 2 - 1)) + ((r + h) & 1u);
-                    uint32_t north, east;
-                    site_offsets<B, WRAP>((r << ilog2(B)) + cc, own[m], north, east);
-                    vs[m] = t[own[m]];
-                    vn[m] = t[north];
-                    ve[m] = t[east];
-                    atomicMin(owner + idx[m], 2u * l + (uint32_t)m);
-                }
-                uint32_t win[2];
-#pragma unroll
-                for (int m = 0; m < 2; ++m)
-                    win[m] = __hip_atomic_load(owner + idx[m], __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_WORKGROUP) == 2u * l + (uint32_t)m;
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    const uint32_t n = vs[m] & 1u;
-                    const uint32_t allow = vn[m] & ve[m] & 1u;
-                    const uint32_t thr_m1 = n ? a.thr_m1_down : a.thr_m1_up;
-                    const uint32_t never = (a.never >> n) & 1u;
-                    const bool ok = (win[m] & allow & (w.w[2 * m + 1] <= thr_m1 ? 1u : 0u) &
-                                     (never ^ 1u)) != 0u;
-                    if (ok) {
-                        t[own[m]] = (uint8_t)((n ^ 1u) | 2u);
-                        changed += 1;
-                    }
-                    if (win[m]) owner[idx[m]] = 0xFFFFFFFFu;
-                }
-            }
-        }
-        store_tile<B, LPT>(a, t, l, x0, y0);
-    }
-    add_counts(a, lane, changed, mag, bond, fresh);
-}
-
-template <int B, int LPT>
-hipError_t launch_one(const NeSubArgs& a, bool balanced, hipStream_t s)
-{
-    if (balanced) {
-        constexpr int TPW = bal_tiles_per_wave<B, LPT>();
-        static_assert(TPW >= 1, "a sub-lattice must fit the LDS budget");
-        const uint32_t blocks = (a.ntiles + TPW - 1) / TPW;
-        if (a.ntiles == 1)
-            hipLaunchKernelGGL((k_ne_bal<B, LPT, true>), dim3(blocks), dim3(64), 0, s, a);
+        if (a.bits_in)
+            load_bits<B, LPT>(a, t, l, tx, ty);
         else
-            hipLaunchKernelGGL((k_ne_bal<B, LPT, false>), dim3(blocks), dim3(64), 0, s, a);
-        return hipGetLastError();
+            load_colours<B, LPT>(a, t, l, tx * B, ty * B);
+        if (BAL)
+            for (int i = (int)l; i < OW; i += LPT) owner[i] = 0xFFFFFFFFu;
+        asm volatile("" ::: "memory");  // other lanes' rows from here on
+        if (a.obs) observe_rows<B, LPT>(t, l, mag, bond, fresh);
+        const Row ecol = B >= 32 && !WRAP ? t.ecol : 0;
+        const uint64_t may_up = (a.never & 1u) == 0u ? ~0ull : 0ull, may_down = (a.never & 2u) == 0u ? ~0ull : 0ull;
+
+        const PhiloxKey ks = philox_schedule(a.key0, a.key1);
+        Words4 w[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) w[i] = philox4x32_10(tau, (uint32_t)(i * LPT) + l, a.launch, TAG, ks);
+#pragma nounroll
+        for (uint32_t j = 0; j < a.steps; j += G) {
+            RowPair<B> rows[G][2];
+#pragma unroll
+            for (int i = 0; i < 2 * G; ++i) rows[i / 2][i & 1] = read_rows<B, WRAP>(t, w[i / 2].w[2 * (i & 1)]);
+#pragma unroll
+            for (int i = 0; i < 2 * G; ++i)  // together, not each before its use
+                asm volatile("" : "+v"(rows[i / 2][i & 1].own), "+v"(rows[i / 2][i & 1].north));
+            Words4 wn[G];
+#pragma unroll
+            for (int i = 0; i < G; ++i)
+                wn[i] = philox4x32_10(tau, (j + (uint32_t)(G + i)) * LPT + l, a.launch, TAG, ks);
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                uint64_t up_mask[2], down_mask[2];  // accepted attempts, by lane
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const Draw<B, BAL> d(w[i].w[2 * m], i & 1);
+                    // bit 0 of s the site, bit 1 its east neighbour
+                    const Row own = rows[i][m].own;
+                    uint32_t s, north;
+                    if constexpr (B < 32)
+                        s = (WRAP ? (own & ((1u << (B & 31)) - 1u)) | (own << (B & 31)) : own) >> d.c();
+                    else if constexpr (B == 32)
+                        s = __builtin_amdgcn_alignbit(WRAP ? own : ecol >> d.r, own, d.c5);
+                    else
+                        s = (uint32_t)(own >> d.c()) |
+                            (d.c() == B - 1 ? (uint32_t)((WRAP ? own : ecol >> d.r) & 1u) << 1 : 0u);
+                    if constexpr (B <= 32)
+                        north = __builtin_amdgcn_ubfe((uint32_t)rows[i][m].north, B == 32 ? d.c5 : d.c(), 1);
+                    else
+                        north = (uint32_t)(rows[i][m].north >> d.c()) & 1u;
+                    const uint32_t k = north << 2 | (s & 3u), word = w[i].w[2 * m + 1];
+                    // accept iff word < thr, thr in [0, 2^32]: word <= thr - 1 unless thr = 0
+                    up_mask[m] = __builtin_amdgcn_ballot_w64(k == 6u) &
+                                 __builtin_amdgcn_ballot_w64(word <= a.thr_m1_up) & may_up;
+                    down_mask[m] = __builtin_amdgcn_ballot_w64(k == 7u) &
+                                   __builtin_amdgcn_ballot_w64(word <= a.thr_m1_down) & may_down;
+                }
+                if ((up_mask[0] | up_mask[1] | down_mask[0] | down_mask[1]) != 0ull) {
+                    bool up[2], down[2];
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) {
+                        up[m] = __builtin_amdgcn_inverse_ballot_w64(up_mask[m]);
+                        down[m] = __builtin_amdgcn_inverse_ballot_w64(down_mask[m]);
+                    }
+                    if constexpr (BAL) {
+                        uint32_t idx[2];
+                        bool win[2];
+#pragma unroll
+                        for (int m = 0; m < 2; ++m) {
+                            idx[m] = w[i].w[2 * m] >> (33 - 2 * ilog2(B));
+                            atomicMin(owner + idx[m], 2u * l + (uint32_t)m);
+                        }
+#pragma unroll
+                        for (int m = 0; m < 2; ++m)
+                            win[m] = __hip_atomic_load(owner + idx[m], __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_WORKGROUP) == 2u * l + (uint32_t)m;
+#pragma unroll
+                        for (int m = 0; m < 2; ++m) {
+                            if (win[m]) owner[idx[m]] = 0xFFFFFFFFu;
+                            up[m] = up[m] && win[m];
+                            down[m] = down[m] && win[m];
+                        }
+                    }
+                    if (up[0] || down[0] || up[1] || down[1]) {
+                        Row and_old[2], or_old[2], bit[2];
+#pragma unroll
+                        for (int m = 0; m < 2; ++m) {
+                            const Draw<B, BAL> d(w[i].w[2 * m], i & 1);
+                            bit[m] = (Row)1 << d.c();
+                            and_old[m] = atomicAnd(&t.rows[d.r + 1], down[m] ? ~bit[m] : ~(Row)0);
+                            or_old[m] = atomicOr(&t.rows[d.r + 1], up[m] ? bit[m] : (Row)0);
+                            atomicOr(&t.flags[d.r], up[m] || down[m] ? bit[m] : (Row)0);
+                        }
+                        // the first change of the site in this step: n still as at its start
+#pragma unroll
+                        for (int m = 0; m < 2; ++m)
+                            changed += (down[m] && (and_old[m] & bit[m]) != 0) || (up[m] && (or_old[m] & bit[m]) == 0) ? 1 : 0;
+                    }
+                    asm volatile("" ::: "memory");  // also rows that other lanes changed
+#pragma unroll
+                    for (int k = 2 * (i + 1); k < 2 * G; ++k)
+                        rows[k / 2][k & 1] = read_rows<B, WRAP>(t, w[k / 2].w[2 * (k & 1)]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < G; ++i) w[i] = wn[i];
+        }
+        asm volatile("" ::: "memory");
+        if (a.bits_out)
+            store_bits<B, LPT>(a, t, l, tau);
+        else
+            store_colours<B, LPT>(a, t, l, tx * B, ty * B);
     }
-    constexpr int TPW = tiles_per_wave<B, LPT>();
+    add_counts(a, lane, changed, mag, bond, fresh);
+}
+
+template <int B, int LPT, bool BAL>
+hipError_t launch_one(const NeSubArgs& a, hipStream_t s)
+{
+    constexpr int TPW = tiles_per_wave<B, LPT, BAL>();
     static_assert(TPW >= 1, "a sub-lattice must fit the LDS budget");
     const uint32_t blocks = (a.ntiles + TPW - 1) / TPW;
     if (a.ntiles == 1)
-        hipLaunchKernelGGL((k_ne_sub<B, LPT, true>), dim3(blocks), dim3(64), 0, s, a);
+        hipLaunchKernelGGL((k_ne_sub<B, LPT, true, BAL>), dim3(blocks), dim3(64), 0, s, a);
     else
-        hipLaunchKernelGGL((k_ne_sub<B, LPT, false>), dim3(blocks), dim3(64), 0, s, a);
+        hipLaunchKernelGGL((k_ne_sub<B, LPT, false, BAL>), dim3(blocks), dim3(64), 0, s, a);
     return hipGetLastError();
+}
+
+template <int B, bool BAL>
+hipError_t launch_lambda(const NeSubArgs& a, int lambda, hipStream_t s)
+{
+    switch (lambda) {
+        case 2: return launch_one<B, 1, BAL>(a, s);
+        case 4: return launch_one<B, 2, BAL>(a, s);
+        case 8: return launch_one<B, 4, BAL>(a, s);
+        case 16: return launch_one<B, 8, BAL>(a, s);
+        case 32: return launch_one<B, 16, BAL>(a, s);
+        case 64: return launch_one<B, 32, BAL>(a, s);
+        case 128: return launch_one<B, 64, BAL>(a, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int B>
 hipError_t launch_side(const NeSubArgs& a, int lambda, bool balanced, hipStream_t s)
 {
-    switch (lambda) {
-        case 2: return launch_one<B, 1>(a, balanced, s);
-        case 4: return launch_one<B, 2>(a, balanced, s);
-        case 8: return launch_one<B, 4>(a, balanced, s);
-        case 16: return launch_one<B, 8>(a, balanced, s);
-        case 32: return launch_one<B, 16>(a, balanced, s);
-        case 64: return launch_one<B, 32>(a, balanced, s);
-        case 128: return launch_one<B, 64>(a, balanced, s);
-    }
-    return hipErrorInvalidValue;
+    return balanced ? launch_lambda<B, true>(a, lambda, s) : launch_lambda<B, false>(a, lambda, s);
 }
 
 }  // namespace nesub

@@ -339,6 +339,8 @@ sl_status enqueue_observe(sl_lattice* h, uint64_t slot)
 // the sweep's record slot.  The lattice part of a sweep's record is measured by
 // the first launch of the next sweep from the state it loads; after the last
 // sweep of the call a separate pass (both colours, no update) measures it.
+// The copies hold bit rows between the call's launches and colour arrays again
+// after it.
 sl_status sweep_ne_sub(sl_lattice* h, uint64_t n)
 {
     const int B = h->params.ne_side, lam = h->params.ne_lambda;
@@ -359,11 +361,14 @@ sl_status sweep_ne_sub(sl_lattice* h, uint64_t n)
     uint8_t* cur[2] = {h->base + h->lay.off_col[h->cur][0], h->base + h->lay.off_col[h->cur][1]};
     uint8_t* oth[2] = {h->base + h->lay.off_col[h->cur ^ 1][0],
                        h->base + h->lay.off_col[h->cur ^ 1][1]};
+    const uint32_t steps = (uint32_t)ne_sub_steps(B, lam, bal);
     for (uint64_t i = 0; i < n; ++i) {
         const uint64_t t = h->next_t + i;
         na.acc = slot_ptr(h, h->pending + i);
+        na.steps = steps;
         hipError_t e = hipSuccess;
-        for (int k = 0; k < per && e == hipSuccess; ++k) {
+        int k = 0;
+        for (; k < per && e == hipSuccess; ++k) {
             uint8_t** from = (k & 1) == 0 ? cur : oth;
             uint8_t** to = (k & 1) == 0 ? oth : cur;
             na.src[0] = from[0];
@@ -372,12 +377,27 @@ sl_status sweep_ne_sub(sl_lattice* h, uint64_t n)
             na.dst[1] = to[1];
             na.launch = (uint32_t)((uint64_t)per * t + (uint64_t)k);
             na.obs = (k == 0 && i > 0) ? slot_ptr(h, h->pending + i - 1) : nullptr;
+            na.bits_in = (i > 0 || k > 0) ? 1u : 0u;
+            na.bits_out = (i + 1 < n || k + 1 < per) ? 1u : 0u;
             e = launch_ne_sub(na, B, lam, bal, h->stream);
         }
         sl_status st = SL_OK;
         if (e != hipSuccess) {
             st = hip_fail(e, "sub-lattice launch");
-            if (i > 0) (void)enqueue_observe(h, h->pending + i - 1);
+            if (i > 0 || k > 2) {  // launch k - 1 failed
+                // the current copy holds bit rows: the state after sweep i - 1, or (balanced)
+                // after this sweep's second launch
+                for (int c = 0; c < 2; ++c) {
+                    na.src[c] = cur[c];
+                    na.dst[c] = oth[c];
+                }
+                na.obs = nullptr;
+                na.bits_in = 1u;
+                na.bits_out = 0u;
+                na.steps = 0u;
+                if (launch_ne_sub(na, B, lam, bal, h->stream) == hipSuccess) h->cur ^= 1;
+                if (i > 0) (void)enqueue_observe(h, h->pending + i - 1);
+            }
         } else if (i + 1 == n) {
             st = enqueue_observe(h, h->pending + i);
         }

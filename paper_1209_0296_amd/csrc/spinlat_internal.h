@@ -104,6 +104,9 @@ hipError_t launch_row_fused(const SweepArgs& a, int kind, int H, int D, const ui
 struct NeSubArgs {
     const uint8_t* src[2];      // colour arrays at launch start
     uint8_t* dst[2];            // colour arrays after the launch
+    uint32_t bits_in, bits_out; // the arrays hold bit rows instead (a launch of the same
+                                // B has written them, or reads them next)
+    uint32_t steps;             // ne_sub_steps; 0: only change the form
     uint32_t L, Lh, tiles_x, ntiles;
     uint32_t key0, key1;        // Philox key = seed
     uint32_t launch;            // launch index: 2 t, 2 t + 1 (balanced: 4 t .. 4 t + 3)
@@ -118,6 +121,10 @@ struct NeSubArgs {
 // Shapes: host::ne_sub_supported.
 // balanced: colour 0 then colour 1 per iteration, P/(8 lambda) iterations
 // (four launches per sweep); else q = P/(2 lambda) iterations (two launches)
+constexpr int ne_sub_steps(int B, int lambda, bool balanced)
+{
+    return balanced ? B * B / (4 * lambda) : B * B / (2 * lambda);
+}
 hipError_t launch_ne_sub(const NeSubArgs& a, int B, int lambda, bool balanced, hipStream_t s);
 
 }  // namespace spinlat
