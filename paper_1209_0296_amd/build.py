@@ -15,6 +15,7 @@ SOURCES = ["kernels_simple.hip", "kernels_stream.hip", "kernels_row.hip", "kerne
            "kernels_ne_sub_b32.hip", "kernels_ne_sub_b64.hip", "host_logic.cpp", "runtime.cpp",
            "batch.cpp", "static_sweep.hip", "kernels_rows.hip", "kernels_tile.hip",
            "kernels_tile_half.hip", "kernels_tile_one.hip", "kernels_tile_ne.hip",
+           "kernels_tile_bits.hip",
            "kernels_plane.hip", "kernels_batch_tile.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

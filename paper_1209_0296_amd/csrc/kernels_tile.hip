@@ -47,6 +47,17 @@ double plan_cost(const TileGeom& t, uint32_t k, const Cost& c)
     return c.launch + rounds * (c.load + 2.0 * k * (c.step + c.word * at_once * waves / 4.0));
 }
 
+// The same for tiles on bit words at c = 0.1: every word costs its load and store,
+// and a half-sweep is mostly latency (within 5% of 20 timings, L = 1048 .. 4096).
+double bits_cost(const TileGeom& t, uint32_t k)
+{
+    const uint32_t per_cu = (t.ntx * t.nty + 255) / 256, fit = t.ipt == 1 ? 2048 / t.block : 2;
+    const uint32_t at_once = per_cu < fit ? per_cu : fit;
+    const double rounds = (double)((per_cu + at_once - 1) / at_once);
+    const double held = at_once * ((t.nitems + 63) / 64), updated = at_once * (t.P / 8) * (t.RY - 2.0 * k) / 64.0;
+    return 1.0 + rounds * (0.26 * held + 2.0 * k * (0.85 + 0.0235 * updated));
+}
+
 }  // namespace
 
 TilePlan whole_plan(const Geom& g) { return TilePlan{g.Lh / 4, g.L, g.L, kTileWhole}; }
@@ -60,25 +71,27 @@ bool tile_geom(const Geom& g, const TilePlan& p, uint32_t k, TileGeom& t, uint32
     t.H = p.H < g.L ? p.H : g.L;
     t.Z = g.dim == 3 ? (p.Z < g.L ? p.Z : g.L) : 1;
     if (!t.W || !t.H || !t.Z || !k) return false;
-    t.wrapx = t.W == t.ncols;
+    t.bits = p.bits;
+    t.wrapx = !t.bits && t.W == t.ncols;
     t.wrapy = t.H == g.L;
     t.wrapz = g.dim == 2 || t.Z == g.L;
     // a half-sweep needs one more site on each side: 2 k rows and planes, and
     // 2 k sites of the 8 that a word pair covers in x
-    t.hx = t.wrapx ? 0 : cdiv(2 * k, 8);
+    t.hx = t.bits ? 8 : t.wrapx ? 0 : cdiv(2 * k, 8);
     t.hy = t.wrapy ? 0 : 2 * k;
     t.hz = t.wrapz ? 0 : 2 * k;
     if (t.W + t.hx > t.ncols || t.H + t.hy > t.L || (g.dim == 3 && t.Z + t.hz > t.L)) return false;
     t.P = t.W + 2 * t.hx;
     t.RY = t.H + 2 * t.hy;
     t.RZ = t.Z + 2 * t.hz;
-    const uint64_t n = (uint64_t)t.P * t.RY * t.RZ;
-    if (n > max_items) return false;
+    const uint32_t words = t.bits ? t.P / 8 : t.P;  // of a row
+    const uint64_t n = (uint64_t)words * t.RY * t.RZ;
+    if (n > max_items || (t.bits && (t.wrapy || 2 * k > 32 || t.W % 8 != 0 || n > 2048))) return false;
     t.nitems = (uint32_t)n;
     t.ntx = cdiv(t.ncols, t.W);
     t.nty = cdiv(t.L, t.H);
     t.ntz = g.dim == 3 ? cdiv(t.L, t.Z) : 1;
-    t.magicP = magic(t.P);
+    t.magicP = magic(words);
     t.magicRY = magic(t.RY);
     t.ipt = t.nitems <= 1024 ? 1 : t.nitems <= 2048 ? 2 : 4;
     t.block = cdiv(cdiv(t.nitems, t.ipt), 64) * 64;
@@ -92,7 +105,32 @@ uint64_t tile_words(const TileGeom& t, uint32_t j)
     return ry * rz * t.P * t.ntx * t.nty * t.ntz;
 }
 
-TilePlan tile_plan(const Geom& g, int kind, bool coupled)
+// Large North-East lattices with J = 0 where an up-flip draws, not a down-flip (c <=
+// 1/2), so that few groups draw: tiles of bit words (kernels_tile_bits.hip).  us per
+// sweep, 4-site words against bits: L = 1536, c = 0.1 4.05 and 2.26; 1800, c = 0.3
+// 4.3 and 3.6; 4096 13.6 and 3.5 (c = 0.3 6.3), 8192, rows otherwise, 48 and 12; but
+// 1304, c = 0.3 2.6 and 3.2, and 4096, c = 0.7 13.7 and 15.2.
+static TilePlan bits_plan(const Geom& g, const TilePlan& other)
+{
+    TilePlan best = other;
+    TileGeom t;
+    double best_us = 1e30;
+    for (uint32_t k : {4u, 6u, 8u, 12u})
+        for (uint32_t W : {16u, 32u, 64u, 128u})
+            for (uint32_t H : {16u, 32u, 64u, 128u}) {
+                TilePlan p{W, H, 1, k};
+                p.bits = 1;
+                if (!tile_geom(g, p, k, t)) continue;
+                const double us = bits_cost(t, k) / k;
+                if (us < best_us) {
+                    best_us = us;
+                    best = p;
+                }
+            }
+    return best;
+}
+
+TilePlan tile_plan(const Geom& g, int kind, bool coupled, bool sparse)
 {
     const Cost& c = cost_of(kind, g.dim, coupled);
     TilePlan best{};
@@ -108,7 +146,10 @@ TilePlan tile_plan(const Geom& g, int kind, bool coupled)
     // (spin-1/2 L = 4096: 12.6 against 14-16 for the other shapes of 4 sweeps,
     // 16 and more with 2 or 3; L = 3000: 8.4 against 11-12)
     const TilePlan large{16, 64, 1, 4};
-    if (g.dim == 2 && tile_geom(g, large, large.k, t) && t.ntx * t.nty > 2 * 256) return large;
+    if (g.dim == 2 && tile_geom(g, large, large.k, t)) {
+        if (sparse && kind == KIND_NE && !coupled && t.ntx * t.nty > 256) return bits_plan(g, large);
+        if (t.ntx * t.nty > 2 * 256) return large;
+    }
     for (uint32_t k : {1u, 2u, 3u, 4u, 6u, 8u, 12u})
         for (uint32_t W : {4u, 8u, 16u, 32u, 64u})
             for (uint32_t H : {2u, 4u, 8u, 16u, 32u, 64u, 128u})
@@ -129,6 +170,7 @@ TilePlan tile_plan(const Geom& g, int kind, bool coupled)
 hipError_t launch_tile(const SweepArgs& a, int kind, const TileGeom& tg, uint32_t k, uint8_t* dst0, uint8_t* dst1,
                        hipStream_t s)
 {
+    if (tg.bits) return launch_tile_bits(a, tg, k, dst0, dst1, s);
     if (kind == KIND_ISING_HALF) return launch_tile_half(a, tg, k, dst0, dst1, s);
     if (kind == KIND_ISING_ONE) return launch_tile_one(a, tg, k, dst0, dst1, s);
     return launch_tile_ne(a, tg, k, dst0, dst1, s);

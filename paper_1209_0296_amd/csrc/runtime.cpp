@@ -219,10 +219,12 @@ sl_launch row_launch(const sl_lattice* h)
 // sweeps per launch on LDS tiles (tile_device.hpp) where that is faster (us
 // per sweep, per-sweep launches against tiles): 2D L = 64: 2.2 against 0.81;
 // 512: 4.2 and 1.3; 1048, where rows fit no row kernel: 36 and 2.5; 4096: 14.6
-// and 12.5; 6144: 35.2 and 26.6; 8200: 77.7 and 48.4; 3D L = 64: 8.0 and 2.8;
+// and 12.5; 6144: 35.2 and 26.6; 8200: 77.7 and 48.4; North-East L = 4096, c =
+// 0.1: 17.2 and 3.5; 3D L = 64: 8.0 and 2.8;
 // 128: 8.7 and 5.9.  Not for lattices of L >= 8192 whose rows fit the fused
 // kernels (8192: spin-1/2 36.6 against 45.7, spin-1 68.0 and 71.9, coupled NE
-// 41.9 and 51.5, NE 48.0 and 48.5).  3D lattices above L = 128, where a tile's
+// 41.9 and 51.5) unless North-East moves draw rarely (8192, c = 0.1: 48.0 and
+// 11.9).  3D lattices above L = 128, where a tile's
 // halo costs more than the launches, walk along z with both colours per launch
 // (plane_device.hpp; spin-1/2 L = 136: 9.8 against 6.8; 232: 19.6 and 14.8;
 // 264: 23.4 and 18.1; spin-1 200: 17.4 and 16.0), but not L = 256, whose rows
@@ -242,8 +244,9 @@ sl_launch auto_launch(const sl_lattice* h, TilePlan* tile, PlaneGeom* plane)
         if (h->params.L < 512 && h->params.L != 256 && !plane_plan(g, h->kind, *plane)) *plane = PlaneGeom{};
         return l;
     }
-    if (h->params.L >= 8192 && l.mode == SL_MODE_FUSED) return l;
-    *tile = tile_plan(g, h->kind, coupled);
+    const bool sparse = h->params.model == SL_NORTH_EAST && h->table[1] >= (1ull << 32);
+    if (h->params.L >= 8192 && l.mode == SL_MODE_FUSED && !sparse) return l;
+    *tile = tile_plan(g, h->kind, coupled, sparse);
     return l;
 }
 

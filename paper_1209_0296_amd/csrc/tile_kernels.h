@@ -13,6 +13,9 @@ hipError_t launch_tile_one(const SweepArgs& a, const TileGeom& tg, uint32_t k, u
 hipError_t launch_tile_ne(const SweepArgs& a, const TileGeom& tg, uint32_t k, uint8_t* dst0, uint8_t* dst1,
                           hipStream_t s);
 
+hipError_t launch_tile_bits(const SweepArgs& a, const TileGeom& tg, uint32_t k, uint8_t* dst0, uint8_t* dst1,
+                            hipStream_t s);
+
 namespace tilek {
 
 template <int KIND, int DIM, int IPT>

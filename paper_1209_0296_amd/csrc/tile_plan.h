@@ -18,11 +18,14 @@ struct TileGeom {
     uint32_t nitems;           // words of one colour held: P RY RZ
     uint32_t magicP, magicRY;  // ceil(2^32 / P), ceil(2^32 / RY)
     uint32_t block, ipt;       // threads per workgroup, words per thread and colour
+    uint32_t bits;             // words of 32 sites (kernels_tile_bits.hip): 8 columns each; nitems and
+                               // magicP count those, W, hx and P still columns
 };
 
 // The tile schedule of a lattice: tile size and sweeps per launch (k = 0: none).
 struct TilePlan {
     uint32_t W, H, Z, k;
+    uint32_t bits = 0;  // large North-East lattices (W a multiple of 8)
 };
 
 // The whole lattice as one tile (the resident schedule; does not fit if larger
@@ -38,8 +41,9 @@ constexpr uint32_t kTileItems = 4 * 1024;  // words of one colour that a workgro
 bool tile_geom(const Geom& g, const TilePlan& p, uint32_t k, TileGeom& tg, uint32_t max_items = kTileItems);
 // Words of one colour that half-sweep j of a launch updates, over all tiles.
 uint64_t tile_words(const TileGeom& t, uint32_t j);
-// Fastest plan for a lattice by the launch cost model (kernels_tile.hip).
-TilePlan tile_plan(const Geom& g, int kind, bool coupled);
+// Fastest plan for a lattice by the launch cost model (kernels_tile.hip).  sparse:
+// North-East moves that draw are few (only up-flips draw).
+TilePlan tile_plan(const Geom& g, int kind, bool coupled, bool sparse);
 // Sweeps a.t .. a.t + k - 1, reading a.col and writing dst (another copy, or
 // the same one where a single tile holds the lattice); record s to a.acc + s
 // slots.  Needs every threshold of an Ising or coupled NE table >= 1.
