@@ -31,11 +31,11 @@
 // are 4.7.  Hence as little as possible around a draw:
 // - LDS holds each sub-lattice as one bit row per lattice row (the occupations;
 //   the north row first), so an attempt's site and its north and east neighbours
-//   are two rows read by one instruction and 12 instructions decide it.  The rows
-//   of two steps are read together; the second's again only if an attempt of the
-//   wavefront was accepted in the first.  (Four steps together 16.0 us a launch,
-//   two 15.7.  Deciding four steps from the same rows and again after an accepted
-//   one: 20.0 us against 18.8 then.)
+//   are two rows read by one instruction and 12 instructions decide it (B = 64,
+//   whose rows are two words: 18).  The rows of two steps are read together; the
+//   second's again only if an attempt of the wavefront was accepted in the first.
+//   (Four steps together 16.0 us a launch, two 15.7.  Deciding four steps from the
+//   same rows and again after an accepted one: 20.0 us against 18.8 then.)
 // - Accepted moves are kept as lane masks, so the test whether there are any is
 //   scalar (as bools: 18.3 us a launch).
 // - Between the launches of one call the lattice is kept as those bit rows, an
@@ -48,12 +48,12 @@
 // Accepted moves clear or set the site's bit with LDS atomics (AND for a
 // down-flip, OR for an up-flip; both are issued, one of them with nothing to
 // do, and nothing waits until the last) and set its "has flipped" flag in a
-// second bit row.  Attempts of one step on one site all see the same n, so the value an
-// atomic returns tells whether another attempt already changed the site: each
-// changed site is counted once, and a site drawn twice flips once.  The balanced
-// variant keeps an owner word per site of a colour for the steps with accepted
-// moves: attempts post their number with an LDS atomic minimum, read it back, and
-// only the owner may apply its move.
+// second bit row.  Attempts of one step on one site all see the same n, so the
+// value an atomic returns tells whether another attempt already changed the site:
+// each changed site is counted once, and a site drawn twice flips once.  The
+// balanced variant keeps an owner word per site of a colour for the steps with
+// accepted moves: attempts post their number with an LDS atomic minimum, read it
+// back, and only the owner may apply its move, by XOR.
 //
 // Records: the first launch of a sweep also measures the lattice it starts
 // from -- the state after the previous sweep -- from the sub-lattices it has
@@ -71,7 +71,11 @@ namespace spinlat {
 
 namespace nesub {
 
-constexpr int kLdsBudget = 32768;  // bytes of LDS per one-wavefront workgroup
+// Bytes of LDS per one-wavefront workgroup, while a CU has one workgroup at most,
+// and for more of them (owner words make the difference, balanced us per sweep at c =
+// 0.1, 33 against 19 kB: B = 64, lambda = 16: L = 1536 128 and 163, L = 4096 232 and
+// 147).
+constexpr int kLdsBudget = 32768, kLdsBudgetShared = 19000;
 constexpr uint32_t kTagNeSub = 2u;
 constexpr uint32_t kTagNeBal = 3u;
 
@@ -105,11 +109,37 @@ struct BitRows<64> {
 // LDS of one sub-lattice: rows[0] the north row, rows[1 ..] its own, their
 // flags, and (B >= 32) the east column.  For B < 32 the east neighbour of a
 // row's last site is bit B of the row.
+// Words of 32 bits, which attempts read and change: a row of B = 64 is two.
 template <int B>
-struct BitTile {
-    typename BitRows<B>::Row rows[B + 1], flags[B];
-    typename BitRows<B>::Row ecol;
+struct alignas(8) BitTile {
+    static constexpr int W = B == 64 ? 2 : 1;
+    uint32_t rows[W * (B + 1)], flags[W * B], ecol[W];
 };
+
+template <int B>
+__device__ __forceinline__ typename BitRows<B>::Row row_of(const uint32_t* words, uint32_t r)
+{
+    if constexpr (B == 64) return words[2 * r] | (unsigned long long)words[2 * r + 1] << 32;
+    else return words[r];
+}
+
+template <int B>
+__device__ __forceinline__ void set_row(uint32_t* words, uint32_t r, typename BitRows<B>::Row v)
+{
+    if constexpr (B == 64) {
+        words[2 * r] = (uint32_t)v;
+        words[2 * r + 1] = (uint32_t)(v >> 32);
+    } else {
+        words[r] = v;
+    }
+}
+
+template <int B>
+__device__ __forceinline__ void or_row(uint32_t* words, typename BitRows<B>::Row v)
+{
+    atomicOr(words, (uint32_t)v);
+    if constexpr (B == 64) atomicOr(words + 1, (uint32_t)(v >> 32));
+}
 
 template <int B, bool BAL>
 constexpr int owner_words()
@@ -118,9 +148,9 @@ constexpr int owner_words()
 }
 
 template <int B, int LPT, bool BAL>
-constexpr int tiles_per_wave()
+constexpr int tiles_per_wave(int budget)
 {
-    constexpr int fit = kLdsBudget / ((int)sizeof(BitTile<B>) + 4 * owner_words<B, BAL>());
+    const int fit = budget / ((int)sizeof(BitTile<B>) + 4 * owner_words<B, BAL>());
     return 64 / LPT < fit ? 64 / LPT : fit;
 }
 
@@ -207,7 +237,7 @@ __device__ __forceinline__ void load_colours(const NeSubArgs& a, BitTile<B>& t, 
     constexpr int NV = B / 2 / UNIT;
     constexpr int K = Steps::per_step;
     const uint32_t xe = x0 + B == a.L ? 0u : x0 + B;
-    if (B >= 32 && l == 0) t.ecol = 0;
+    if (B >= 32 && l == 0) set_row<B>(t.ecol, 0, 0);
     Row ecol = 0;
 #pragma nounroll
     for (int s = 0; s < Steps::steps; ++s) {
@@ -242,14 +272,14 @@ __device__ __forceinline__ void load_colours(const NeSubArgs& a, BitTile<B>& t, 
                     flags |= (Row)(gather8<1>(e[i][u].w[k], o[i][u].w[k]) >> 1) << sh;
                 }
             if (B < 32) row |= (Row)(east[i] & 1u) << (B & 31);
-            if (pr <= (uint32_t)B) t.rows[pr] = row;
+            if (pr <= (uint32_t)B) set_row<B>(t.rows, pr, row);
             if (pr - 1u < (uint32_t)B) {
-                t.flags[pr - 1u] = flags;
+                set_row<B>(t.flags, pr - 1u, flags);
                 if (B >= 32) ecol |= (Row)(east[i] & 1u) << (pr - 1u);
             }
         }
     }
-    if (B >= 32) atomicOr(&t.ecol, ecol);
+    if (B >= 32) or_row<B>(t.ecol, ecol);
 }
 
 // Sub-lattice (tx, ty) of bit rows.
@@ -279,14 +309,14 @@ __device__ __forceinline__ void load_bits(const NeSubArgs& a, BitTile<B>& t, uin
         for (int i = 0; i < K; ++i) {
             const uint32_t r = l + (uint32_t)((i0 + i) * LPT);
             if (r < (uint32_t)B) {
-                t.rows[r + 1] = B < 32 ? (Row)row[i] | (((Row)column >> r) & 1u) << (B & 31) : (Row)row[i];
-                t.flags[r] = flags[i];
+                set_row<B>(t.rows, r + 1, B < 32 ? (Row)row[i] | (((Row)column >> r) & 1u) << (B & 31) : (Row)row[i]);
+                set_row<B>(t.flags, r, flags[i]);
             }
         }
     }
     if (l == 0) {
-        t.rows[0] = above;
-        t.ecol = column;
+        set_row<B>(t.rows, 0, above);
+        set_row<B>(t.ecol, 0, column);
     }
 }
 
@@ -298,12 +328,12 @@ __device__ __forceinline__ void observe_rows(const BitTile<B>& t, uint32_t l, in
     using Row = typename BitRows<B>::Row;
     constexpr Row mask = B >= 32 ? ~(Row)0 : ((Row)1 << (B & 31)) - 1;
     for (int r = (int)l; r < B; r += LPT) {
-        const Row row = t.rows[r + 1], n = row & mask;
+        const Row row = row_of<B>(t.rows, r + 1), n = row & mask;
         Row east = row >> 1;
-        if (B >= 32) east |= (Row)((t.ecol >> r) & 1u) << (B - 1);
+        if (B >= 32) east |= ((row_of<B>(t.ecol, 0) >> r) & 1u) << (B - 1);
         mag += __builtin_popcountll(n);
-        bond += __builtin_popcountll(n & t.rows[r]) + __builtin_popcountll(n & east);
-        fresh += B - __builtin_popcountll(t.flags[r]);
+        bond += __builtin_popcountll(n & row_of<B>(t.rows, r)) + __builtin_popcountll(n & east);
+        fresh += B - __builtin_popcountll(row_of<B>(t.flags, r));
     }
 }
 
@@ -315,7 +345,7 @@ __device__ __forceinline__ void store_colours(const NeSubArgs& a, const BitTile<
     constexpr int UNIT = B / 2 < 16 ? B / 2 : 16;
 #pragma unroll 2
     for (uint32_t r = l; r < (uint32_t)B; r += LPT) {
-        const Row row = t.rows[r + 1], flags = t.flags[r];
+        const Row row = row_of<B>(t.rows, r + 1), flags = row_of<B>(t.flags, r);
         const size_t off = (size_t)(y0 + r) * a.Lh + (x0 >> 1);
         // y0 is even; colour 1 holds the even x of odd rows
         uint8_t* even = ((r & 1u) != 0 ? a.dst[1] : a.dst[0]) + off;
@@ -343,18 +373,18 @@ __device__ __forceinline__ void store_bits(const NeSubArgs& a, BitTile<B>& t, ui
     using Row = typename BitRows<B>::Row;
     using Bits = typename BitRows<B>::Bits;
     const BitLattice<B> dst(a.dst[0], a.dst[1], a.ntiles);
-    if (l == 0) t.ecol = 0;
+    if (l == 0) set_row<B>(t.ecol, 0, 0);
     Row column = 0;
 #pragma unroll 4
     for (uint32_t r = l; r < (uint32_t)B; r += LPT) {
-        const Row row = t.rows[r + 1];
+        const Row row = row_of<B>(t.rows, r + 1);
         dst.rows[(size_t)tau * B + r] = (Bits)row;
-        dst.flags[(size_t)tau * B + r] = (Bits)t.flags[r];
+        dst.flags[(size_t)tau * B + r] = (Bits)row_of<B>(t.flags, r);
         column |= (row & 1u) << r;
     }
-    atomicOr(&t.ecol, column);
+    or_row<B>(t.ecol, column);
     asm volatile("" ::: "memory");  // all lanes' parts
-    if (l == 0) dst.column[tau] = (Bits)t.ecol;
+    if (l == 0) dst.column[tau] = (Bits)row_of<B>(t.ecol, 0);
 }
 
 // Wavefront sums of the per-lane counts into the records: one atomic
@@ -389,31 +419,54 @@ struct Draw {
     __device__ __forceinline__ uint32_t c() const { return c5 & (B - 1); }
 };
 
-// The two rows an attempt reads: its own and the one to the north.
+// The rows an attempt reads, its own and the one to the north.
 template <int B>
 struct RowPair {
-    typename BitRows<B>::Row north, own;
+    uint32_t north[BitTile<B>::W], own[BitTile<B>::W];
 };
 
 template <int B, bool WRAP>
 __device__ __forceinline__ RowPair<B> read_rows(const BitTile<B>& t, uint32_t word)
 {
+    constexpr uint32_t W = BitTile<B>::W;
     const uint32_t r = word >> (32 - ilog2(B));
     RowPair<B> p;
     // one sub-lattice: the periodic neighbours are inside it
-    p.north = t.rows[WRAP && r == 0 ? B : r];
-    p.own = t.rows[r + 1];
+    const uint32_t* north = t.rows + W * (WRAP && r == 0 ? (uint32_t)B : r);
+    __builtin_memcpy(p.north, __builtin_assume_aligned(north, 4 * W), 4 * W);
+    __builtin_memcpy(p.own, __builtin_assume_aligned(t.rows + W * (r + 1), 4 * W), 4 * W);
     return p;
 }
 
-template <int B, int LPT, bool WRAP, bool BAL>
+// Balanced: whether each attempt is the lowest-numbered one on its site in this
+// half; owner words are as before again afterwards.
+template <int B>
+__device__ __forceinline__ void claim(uint32_t* owner, uint32_t l, const Words4& w, bool (&win)[2])
+{
+    uint32_t idx[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        idx[m] = w.w[2 * m] >> (33 - 2 * ilog2(B));
+        atomicMin(owner + idx[m], 2u * l + (uint32_t)m);
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+        win[m] = __hip_atomic_load(owner + idx[m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 2u * l + (uint32_t)m;
+    asm volatile("" ::: "memory");  // all lanes have read
+#pragma unroll
+    for (int m = 0; m < 2; ++m) owner[idx[m]] = 0xFFFFFFFFu;
+}
+
+template <int B, int LPT, bool WRAP, bool BAL, int TPW>
 __global__ void __launch_bounds__(64) k_ne_sub(NeSubArgs a)
 {
-    using Row = typename BitRows<B>::Row;
-    constexpr int TPW = tiles_per_wave<B, LPT, BAL>();
+    static_assert(TPW >= 1, "a sub-lattice must fit the LDS budget");
     constexpr uint32_t TAG = BAL ? kTagNeBal : kTagNeSub;
     constexpr int STEPS = ne_sub_steps(B, 2 * LPT, BAL);
-    constexpr int G = STEPS < 2 ? 1 : 2;  // steps whose rows are read together
+    // steps whose rows are read together: few wavefronts with many steps each have
+    // the latency of a step as their bound (B = 64, L = 512 two against four, us per
+    // sweep: lambda = 16 77.5 and 73.4, lambda = 32 41.2 and 43.1)
+    constexpr int G = STEPS < 2 ? 1 : B == 64 && LPT <= 8 ? 4 : 2;
     constexpr int OW = owner_words<B, BAL>();
     __shared__ BitTile<B> lds[TPW];
     __shared__ uint32_t lds_owner[BAL ? TPW * OW : 1];
@@ -435,7 +488,8 @@ __global__ void __launch_bounds__(64) k_ne_sub(NeSubArgs a)
             for (int i = (int)l; i < OW; i += LPT) owner[i] = 0xFFFFFFFFu;
         asm volatile("" ::: "memory");  // other lanes' rows from here on
         if (a.obs) observe_rows<B, LPT>(t, l, mag, bond, fresh);
-        const Row ecol = B >= 32 && !WRAP ? t.ecol : 0;
+        const uint32_t ecol_lo = B >= 32 && !WRAP ? t.ecol[0] : 0u;
+        const uint32_t ecol_hi = B == 64 && !WRAP ? t.ecol[BitTile<B>::W - 1] : 0u;
         const uint64_t may_up = (a.never & 1u) == 0u ? ~0ull : 0ull, may_down = (a.never & 2u) == 0u ? ~0ull : 0ull;
 
         const PhiloxKey ks = philox_schedule(a.key0, a.key1);
@@ -449,7 +503,9 @@ __global__ void __launch_bounds__(64) k_ne_sub(NeSubArgs a)
             for (int i = 0; i < 2 * G; ++i) rows[i / 2][i & 1] = read_rows<B, WRAP>(t, w[i / 2].w[2 * (i & 1)]);
 #pragma unroll
             for (int i = 0; i < 2 * G; ++i)  // together, not each before its use
-                asm volatile("" : "+v"(rows[i / 2][i & 1].own), "+v"(rows[i / 2][i & 1].north));
+#pragma unroll
+                for (int k = 0; k < BitTile<B>::W; ++k)
+                    asm volatile("" : "+v"(rows[i / 2][i & 1].own[k]), "+v"(rows[i / 2][i & 1].north[k]));
             Words4 wn[G];
 #pragma unroll
             for (int i = 0; i < G; ++i)
@@ -461,19 +517,22 @@ __global__ void __launch_bounds__(64) k_ne_sub(NeSubArgs a)
                 for (int m = 0; m < 2; ++m) {
                     const Draw<B, BAL> d(w[i].w[2 * m], i & 1);
                     // bit 0 of s the site, bit 1 its east neighbour
-                    const Row own = rows[i][m].own;
-                    uint32_t s, north;
-                    if constexpr (B < 32)
+                    const RowPair<B>& row = rows[i][m];
+                    const bool low = B < 64 || (d.c5 & 32u) == 0u;  // B = 64: the row's first word
+                    const uint32_t own_lo = row.own[0], own_hi = row.own[BitTile<B>::W - 1];
+                    const uint32_t north_lo = row.north[0], north_hi = row.north[BitTile<B>::W - 1];
+                    const uint32_t own = low ? own_lo : own_hi;
+                    uint32_t s;
+                    if constexpr (B < 32) {
                         s = (WRAP ? (own & ((1u << (B & 31)) - 1u)) | (own << (B & 31)) : own) >> d.c();
-                    else if constexpr (B == 32)
-                        s = __builtin_amdgcn_alignbit(WRAP ? own : ecol >> d.r, own, d.c5);
-                    else
-                        s = (uint32_t)(own >> d.c()) |
-                            (d.c() == B - 1 ? (uint32_t)((WRAP ? own : ecol >> d.r) & 1u) << 1 : 0u);
-                    if constexpr (B <= 32)
-                        north = __builtin_amdgcn_ubfe((uint32_t)rows[i][m].north, B == 32 ? d.c5 : d.c(), 1);
-                    else
-                        north = (uint32_t)(rows[i][m].north >> d.c()) & 1u;
+                    } else if constexpr (B == 32) {
+                        s = __builtin_amdgcn_alignbit(WRAP ? own : ecol_lo >> d.r, own, d.c5);
+                    } else {
+                        const uint32_t past = WRAP ? own_lo : (d.r & 32u ? ecol_hi : ecol_lo) >> (d.r & 31u);
+                        const uint32_t next = low ? own_hi : past;
+                        s = __builtin_amdgcn_alignbit(next, own, d.c5);
+                    }
+                    const uint32_t north = __builtin_amdgcn_ubfe(low ? north_lo : north_hi, B >= 32 ? d.c5 : d.c(), 1);
                     const uint32_t k = north << 2 | (s & 3u), word = w[i].w[2 * m + 1];
                     // accept iff word < thr, thr in [0, 2^32]: word <= thr - 1 unless thr = 0
                     up_mask[m] = __builtin_amdgcn_ballot_w64(k == 6u) &
@@ -489,38 +548,39 @@ __global__ void __launch_bounds__(64) k_ne_sub(NeSubArgs a)
                         down[m] = __builtin_amdgcn_inverse_ballot_w64(down_mask[m]);
                     }
                     if constexpr (BAL) {
-                        uint32_t idx[2];
                         bool win[2];
+                        claim<B>(owner, l, w[i], win);
 #pragma unroll
                         for (int m = 0; m < 2; ++m) {
-                            idx[m] = w[i].w[2 * m] >> (33 - 2 * ilog2(B));
-                            atomicMin(owner + idx[m], 2u * l + (uint32_t)m);
-                        }
-#pragma unroll
-                        for (int m = 0; m < 2; ++m)
-                            win[m] = __hip_atomic_load(owner + idx[m], __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_WORKGROUP) == 2u * l + (uint32_t)m;
-#pragma unroll
-                        for (int m = 0; m < 2; ++m) {
-                            if (win[m]) owner[idx[m]] = 0xFFFFFFFFu;
                             up[m] = up[m] && win[m];
                             down[m] = down[m] && win[m];
                         }
                     }
                     if (up[0] || down[0] || up[1] || down[1]) {
-                        Row and_old[2], or_old[2], bit[2];
+                        uint32_t and_old[2], or_old[2], bit[2];
 #pragma unroll
                         for (int m = 0; m < 2; ++m) {
                             const Draw<B, BAL> d(w[i].w[2 * m], i & 1);
-                            bit[m] = (Row)1 << d.c();
-                            and_old[m] = atomicAnd(&t.rows[d.r + 1], down[m] ? ~bit[m] : ~(Row)0);
-                            or_old[m] = atomicOr(&t.rows[d.r + 1], up[m] ? bit[m] : (Row)0);
-                            atomicOr(&t.flags[d.r], up[m] || down[m] ? bit[m] : (Row)0);
+                            const uint32_t half = B == 64 ? (d.c5 >> 5) & 1u : 0u;
+                            uint32_t* row = &t.rows[BitTile<B>::W * (d.r + 1) + half];
+                            bit[m] = 1u << (B < 32 ? d.c() : d.c5 & 31u);
+                            const uint32_t set = up[m] || down[m] ? bit[m] : 0u;
+                            if constexpr (BAL) {  // one attempt per site
+                                atomicXor(row, set);
+                                changed += set != 0u ? 1 : 0;
+                            } else {
+                                and_old[m] = atomicAnd(row, down[m] ? ~bit[m] : ~0u);
+                                or_old[m] = atomicOr(row, up[m] ? bit[m] : 0u);
+                            }
+                            atomicOr(&t.flags[BitTile<B>::W * d.r + half], set);
                         }
                         // the first change of the site in this step: n still as at its start
+                        if constexpr (!BAL) {
 #pragma unroll
-                        for (int m = 0; m < 2; ++m)
-                            changed += (down[m] && (and_old[m] & bit[m]) != 0) || (up[m] && (or_old[m] & bit[m]) == 0) ? 1 : 0;
+                            for (int m = 0; m < 2; ++m)
+                                changed +=
+                                    (down[m] && (and_old[m] & bit[m]) != 0) || (up[m] && (or_old[m] & bit[m]) == 0) ? 1 : 0;
+                        }
                     }
                     asm volatile("" ::: "memory");  // also rows that other lanes changed
 #pragma unroll
@@ -543,13 +603,15 @@ __global__ void __launch_bounds__(64) k_ne_sub(NeSubArgs a)
 template <int B, int LPT, bool BAL>
 hipError_t launch_one(const NeSubArgs& a, hipStream_t s)
 {
-    constexpr int TPW = tiles_per_wave<B, LPT, BAL>();
-    static_assert(TPW >= 1, "a sub-lattice must fit the LDS budget");
-    const uint32_t blocks = (a.ntiles + TPW - 1) / TPW;
+    constexpr int WIDE = tiles_per_wave<B, LPT, BAL>(kLdsBudget);
+    constexpr int SHARED = tiles_per_wave<B, LPT, BAL>(kLdsBudgetShared);
+    const uint32_t wide = (a.ntiles + WIDE - 1) / WIDE, shared = (a.ntiles + SHARED - 1) / SHARED;
     if (a.ntiles == 1)
-        hipLaunchKernelGGL((k_ne_sub<B, LPT, true, BAL>), dim3(blocks), dim3(64), 0, s, a);
+        hipLaunchKernelGGL((k_ne_sub<B, LPT, true, BAL, 1>), dim3(1), dim3(64), 0, s, a);
+    else if (wide <= 256)
+        hipLaunchKernelGGL((k_ne_sub<B, LPT, false, BAL, WIDE>), dim3(wide), dim3(64), 0, s, a);
     else
-        hipLaunchKernelGGL((k_ne_sub<B, LPT, false, BAL>), dim3(blocks), dim3(64), 0, s, a);
+        hipLaunchKernelGGL((k_ne_sub<B, LPT, false, BAL, SHARED>), dim3(shared), dim3(64), 0, s, a);
     return hipGetLastError();
 }
 
