@@ -152,7 +152,10 @@ typedef struct sl_record {
 
 /* Launch schedule.  Every schedule produces the same lattice and records. */
 typedef enum sl_mode {
-    SL_MODE_AUTO = 0,         /* library's choice for the shape */
+    SL_MODE_AUTO = 0,         /* library's choice for the shape; where that is faster it
+                                 runs several sweeps per launch on tiles in LDS, or 3D
+                                 sweeps as walks along z, instead of the schedule that
+                                 sl_get_launch names */
     SL_MODE_SIMPLE = 1,       /* one thread per 4 same-colour sites, direct global loads,
                                  two launches per sweep */
     SL_MODE_HALF = 2,         /* row-group streaming, one colour in place per launch,
@@ -291,7 +294,11 @@ sl_status sl_record_observables(const sl_params* params, const sl_record* record
  * in the free arena space; removing a job returns its space.
  * Batched jobs need L % 8 == 0 and a checkerboard model (SL_ISING,
  * SL_NORTH_EAST or SL_NE_COUPLED).  Each job gets a kernel class when it is
- * admitted:
+ * admitted.  Jobs whose table has no threshold of zero (or J = 0 NE jobs) run on
+ * tiles in LDS, four sweeps per launch (2D), as walks along z (3D), or, if one
+ * tile holds the lattice, a whole call in one launch, while the arena has room
+ * to spare for a second copy of the lattice and tile_rows is 0 (admission does
+ * not depend on it); else, or with the flags:
  *   - resident: both colours fit 48 KiB; one workgroup per job runs the
  *     call's sweeps in LDS, in one launch per call for all such jobs, on a
  *     stream of the library's own that overlaps the other launches;

@@ -8,8 +8,9 @@
 // buffer for record readback, and a heap from which each job's lattice (two
 // colour arrays, or two copies of them for fused jobs) and record ring are
 // carved first-fit.  Admission by footprint is the heap allocation succeeding.
-// Tiles and walks along z need a second lattice copy; where the heap has no room
-// for it a job runs in the one-copy class that sl_batch_job_bytes reports.
+// Tiles and walks along z need a second lattice copy, lent from the heap's free
+// ranges; where there is no room for it, or a new job takes it, a job runs in the
+// one-copy class that sl_batch_job_bytes reports.
 //
 // A call (sl_batch_sweep) uploads the counters and work lists from pinned
 // staging (double-buffered, so the host never waits for the previous call),
@@ -129,7 +130,9 @@ struct JobHost {
     int kind = 0;
     size_t off = 0;
     JobFoot foot{};
-    RowGeomHost geom{};
+    RowGeomHost geom{}, least{};  // class in use; the one the footprint is for
+    bool lent = false;            // copy 1 lies at off2, in a free range of the heap
+    size_t off2 = 0;
     uint32_t cur = 0;  // copy holding the current state (fused jobs alternate)
     uint64_t t = 0, remaining = 0, pending = 0, first_t = 0, done = 0;
     uint64_t table[kMaxLut] = {};
@@ -222,13 +225,14 @@ Geom geom_of(const sl_params* p, uint64_t nh)
 
 uint8_t* col_of(const sl_batch* b, const JobHost& J, uint32_t copy, uint32_t colour)
 {
+    if (J.lent && copy == 1) return b->arena + J.off2 + colour * J.foot.col_bytes;
     return b->arena + J.off + (2 * copy + colour) * J.foot.col_bytes;
 }
 
 unsigned long long* ring_of(const sl_batch* b, uint32_t j)
 {
     const JobHost& J = b->jobs[j];
-    return reinterpret_cast<unsigned long long*>(b->arena + J.off + 2 * J.geom.copies * J.foot.col_bytes);
+    return reinterpret_cast<unsigned long long*>(b->arena + J.off + 2 * J.least.copies * J.foot.col_bytes);
 }
 
 SweepArgs job_args(const sl_batch* b, uint32_t j)
@@ -245,6 +249,81 @@ SweepArgs job_args(const sl_batch* b, uint32_t j)
     return a;
 }
 
+// Device job-table entry of a job in its present class.
+BatchJob job_entry(const sl_batch* b, uint32_t j)
+{
+    const JobHost& J = b->jobs[j];
+    BatchJob entry;
+    std::memset(&entry, 0, sizeof(BatchJob));
+    for (uint32_t cp = 0; cp < J.geom.copies; ++cp)
+        for (uint32_t c = 0; c < 2; ++c) entry.col[cp][c] = col_of(b, J, cp, c);
+    entry.acc = ring_of(b, j);
+    entry.key0 = (uint32_t)J.params.seed;
+    entry.key1 = (uint32_t)(J.params.seed >> 32);
+    entry.cls = batch_class(class_kind(J), J.params.dim, J.geom.variant);
+    entry.copies = J.geom.copies;
+    entry.dim = (uint32_t)J.params.dim;
+    entry.table_n = (uint32_t)J.table_n;
+    std::memcpy(entry.rg_words, J.geom.bytes, sizeof(entry.rg_words));
+    std::memcpy(entry.table, J.table, J.table_n * sizeof(uint64_t));
+    return entry;
+}
+
+// Tiles and walks along z need a second copy of the lattice, which the footprint
+// that callers are told, and by which jobs are admitted, does not hold.  It lies in
+// a free range of the heap, as high as possible, without being allocated there: a
+// job that is given that range takes it back.  So what fits an arena does not
+// depend on the second copies.
+bool find_second(const sl_batch* b, size_t bytes, size_t* off)
+{
+    std::map<size_t, size_t> lent;  // end -> start
+    for (const JobHost& J : b->jobs)
+        if (J.used && J.lent) lent[J.off2 + 2 * J.foot.col_bytes] = J.off2;
+    const std::map<size_t, size_t>& ranges = b->heap.map();
+    for (auto r = ranges.rbegin(); r != ranges.rend(); ++r) {
+        const size_t start = r->first;
+        size_t end = start + r->second;
+        for (auto l = lent.rbegin(); l != lent.rend(); ++l) {
+            if (l->first > end || l->second < start) continue;  // of another range
+            if (end - l->first >= bytes) break;
+            end = l->second;
+        }
+        if (end - start >= bytes) {
+            *off = end - bytes;
+            return true;
+        }
+    }
+    return false;
+}
+
+// Second copies in [off, off + bytes) are given up: their jobs go on in the class
+// that needs one.
+hipError_t take_back(sl_batch* b, size_t off, size_t bytes)
+{
+    for (uint32_t j = 0; j < b->jobs.size(); ++j) {
+        JobHost& J = b->jobs[j];
+        const size_t second = 2 * J.foot.col_bytes;
+        if (!J.used || !J.lent || J.off2 >= off + bytes || J.off2 + second <= off) continue;
+        if (J.cur == 1) {
+            const hipError_t e = hipMemcpyAsync(col_of(b, J, 0, 0), col_of(b, J, 1, 0), second,
+                                                hipMemcpyDeviceToDevice, b->stream);
+            if (e != hipSuccess) return e;
+        }
+        J.geom = J.least;
+        J.lent = false;
+        J.cur = 0;
+        const BatchJob entry = job_entry(b, j);
+        StartArgs s{};  // no lattice, no ring: the entry alone
+        s.blob_dst = reinterpret_cast<uint32_t*>(d_jobs(b) + j);
+        s.blob_words = (uint32_t)(sizeof(BatchJob) / 4);
+        StartBlob blob;
+        std::memcpy(blob.w, &entry, sizeof(BatchJob));
+        const hipError_t e = launch_start(s, J.kind, blob, b->stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 sl_status check_job(const sl_batch* b, uint32_t j)
 {
     if (!b) return fail(SL_E_INVALID, "NULL batch");
@@ -253,8 +332,8 @@ sl_status check_job(const sl_batch* b, uint32_t j)
 }
 
 // Parameters of a job (record capacity from the batch), its class and footprint.
-// geom is the class to use, least the one for an arena that has no room for its
-// two lattice copies (foot: the footprint of least).
+// geom is the class to use, least the one while the arena has no room for a second
+// lattice copy (foot: the footprint of least).
 sl_status prepare_job(const sl_batch_config* cfg, const sl_params* params, sl_params* p, JobFoot* foot,
                       RowGeomHost* geom, RowGeomHost* least, uint64_t* table, size_t* table_n)
 {
@@ -452,24 +531,25 @@ sl_status sl_batch_add(sl_batch* b, const sl_params* params, uint64_t sweeps, ui
     if (!b) return fail(SL_E_INVALID, "NULL batch");
     if (!job_id) return fail(SL_E_INVALID, "job_id is NULL");
     JobHost J;
-    RowGeomHost least;
-    sl_status st = prepare_job(&b->cfg, params, &J.params, &J.foot, &J.geom, &least, J.table, &J.table_n);
+    sl_status st = prepare_job(&b->cfg, params, &J.params, &J.foot, &J.geom, &J.least, J.table, &J.table_n);
     if (st != SL_OK) return st;
     if (sweeps > (1ull << 32) - J.params.t0)  // validate() keeps t0 < 2^32
         return fail(SL_E_OVERFLOW, "t0 + sweeps would pass 2^32");
     uint32_t j = 0;
     while (j < b->jobs.size() && b->jobs[j].used) ++j;
     if (j == b->jobs.size()) return fail(SL_E_STATE, "job table full (%u jobs)", b->cfg.max_jobs);
-    const JobFoot least_foot = J.foot;
-    J.foot = job_foot(&J.params, b->cfg.record_capacity, J.geom.copies);
-    bool room = b->heap.alloc(J.foot.total, &J.off);
-    if (!room && J.geom.copies != least.copies) {  // no room for a second copy
-        J.geom = least;
-        J.foot = least_foot;
-        room = b->heap.alloc(J.foot.total, &J.off);
-    }
-    if (!room)
+    if (!b->heap.alloc(J.foot.total, &J.off))
         return fail(SL_E_BUFFER, "arena has no free block of %zu bytes for this job", J.foot.total);
+    hipError_t e = take_back(b, J.off, J.foot.total);
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(b->stream);
+        b->heap.release(J.off, J.foot.total);
+        return hip_fail(e, "batch add");
+    }
+    if (J.geom.copies > J.least.copies) {
+        J.lent = find_second(b, 2 * J.foot.col_bytes, &J.off2);
+        if (!J.lent) J.geom = J.least;
+    }
     J.used = true;
     J.kind = kind_of(&J.params);
     J.t = J.params.t0;
@@ -480,24 +560,11 @@ sl_status sl_batch_add(sl_batch* b, const sl_params* params, uint64_t sweeps, ui
 
     // device job-table entry, written by the start kernel
     static_assert(sizeof(BatchJob) <= sizeof(StartBlob), "a job entry travels in the start kernel's arguments");
-    BatchJob entry;
-    BatchJob* hj = &entry;
-    std::memset(hj, 0, sizeof(BatchJob));
-    for (uint32_t cp = 0; cp < J.geom.copies; ++cp)
-        for (uint32_t c = 0; c < 2; ++c) hj->col[cp][c] = col_of(b, J, cp, c);
-    hj->acc = ring_of(b, j);
-    hj->key0 = (uint32_t)J.params.seed;
-    hj->key1 = (uint32_t)(J.params.seed >> 32);
-    hj->cls = batch_class(class_kind(J), J.params.dim, J.geom.variant);
-    hj->copies = J.geom.copies;
-    hj->dim = (uint32_t)J.params.dim;
-    hj->table_n = (uint32_t)J.table_n;
-    std::memcpy(hj->rg_words, J.geom.bytes, sizeof(hj->rg_words));
-    std::memcpy(hj->table, J.table, J.table_n * sizeof(uint64_t));
+    const BatchJob entry = job_entry(b, j);
     SweepArgs a = job_args(b, j);
     const uint64_t bern = thr_from_prob(J.params.c);
-    hipError_t e = start_lattice(a, &J.params, J.kind, bern, ring_of(b, j), (uint64_t)b->cfg.record_capacity * kSlotWords,
-                                 d_jobs(b) + j, hj, sizeof(BatchJob), b->stream);
+    e = start_lattice(a, &J.params, J.kind, bern, ring_of(b, j), (uint64_t)b->cfg.record_capacity * kSlotWords,
+                      d_jobs(b) + j, &entry, sizeof(BatchJob), b->stream);
     // record r_0: observables of the initial state
     a.acc = ring_of(b, j);
     if (e == hipSuccess) e = launch_observe(a, J.kind, b->stream);

@@ -278,7 +278,7 @@ hipError_t launch_start(const StartArgs& s, int kind, const StartBlob& blob, hip
     // enough blocks for the sites, and for the ring of a small lattice (2 KiB a
     // record: with the two blocks of 2D L = 64 a ring of 1002 took 20 us)
     const unsigned sites = blocks_for(s.a.g.nh >> 2), ring = blocks_for(std::min<uint64_t>(s.ring_words, 1u << 18));
-    const dim3 grid(std::max(sites, ring)), block(kBlock);
+    const dim3 grid(std::max({sites, ring, 1u})), block(kBlock);
     if (kind == KIND_ISING_HALF) hipLaunchKernelGGL(k_start<KIND_ISING_HALF>, grid, block, 0, st, s, blob);
     else if (kind == KIND_ISING_ONE) hipLaunchKernelGGL(k_start<KIND_ISING_ONE>, grid, block, 0, st, s, blob);
     else hipLaunchKernelGGL(k_start<KIND_NE>, grid, block, 0, st, s, blob);

@@ -67,3 +67,31 @@ def test_a_work_list_limit_keeps_the_classes_that_fit_it():
     np.testing.assert_array_equal(S.records_to_array(b.measure(i)), o_r)
     np.testing.assert_array_equal(b.spins(i), o_s)
     b.close()
+
+
+@pytest.mark.parametrize("jobs", [
+    [S.Params(dim=3, L=72, T=4.6, seed=3), S.Params(dim=3, L=40, T=4.4, seed=5), S.Params(dim=3, L=72, two_s=2, T=3.1, seed=7)],
+    [S.Params(L=936, two_s=2, T=1.6, seed=4), S.Params(dim=3, L=64, T=4.5, seed=6), S.Params(L=104, T=2.2, seed=8)]])
+def test_an_arena_of_the_sum_of_the_reported_bytes_admits_every_job(jobs):
+    """Second lattice copies give way to new jobs, also while one holds the state."""
+    cfg = S.batch_config(max_jobs=len(jobs), record_capacity=16)
+    room = S.batch_base_bytes(cfg) + sum(S.batch_job_bytes(p, cfg) for p in jobs)
+    b = S.Batch(room, max_jobs=len(jobs), record_capacity=16)
+    ids, recs = [], {}
+    for p in jobs:
+        i = b.add(p, sweeps=3 * len(jobs))
+        assert i is not None
+        ids.append(i)
+        recs[i] = []
+        b.sweep(3)
+        for k in ids:
+            recs[k].append(S.records_to_array(b.measure(k)))
+    for n in (5, 1, 3):
+        b.sweep(n)
+        for k in ids:
+            recs[k].append(S.records_to_array(b.measure(k)))
+    for i, p in zip(ids, jobs):
+        o_s, o_r = run_oracle(p, 3 * len(jobs))
+        np.testing.assert_array_equal(np.vstack(recs[i]), o_r)
+        np.testing.assert_array_equal(b.spins(i), o_s)
+    b.close()
