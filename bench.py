@@ -30,16 +30,18 @@ HBM_PEAK_GBS = 8000.0        # MI355X HBM3E, 8 TB/s
 ALGO_BYTES_PER_ATTEMPT = 2   # one int8 read + one int8 write per site per sweep
 VALU_WAVE_INSTS_PER_S = 256 * 4 * 2.4e9 / 4  # 3.93e13 32-bit lane-ops/s in wave64 instructions
 # sources of the profiled kernels, hashed into profiles/traffic.json
-ROW_SOURCES = ("kernels_row.hip", "row_device.hpp", "site_update.hpp", "philox.hpp",
-               "spinlat_internal.h", "host_logic.h")
-ROWS_SOURCES = ("kernels_rows.hip", "rows_device.hpp", "row_device.hpp", "site_update.hpp", "philox.hpp",
-                "spinlat_internal.h", "host_logic.h")
+ROW_SOURCES = ("kernels_row.hip", "row_device.hpp", "accept.hpp", "block_order.hpp", "site_update.hpp",
+               "philox.hpp", "spinlat_internal.h", "host_logic.h")
+ROWS_SOURCES = ("kernels_rows.hip", "rows_device.hpp", "row_device.hpp", "accept.hpp", "block_order.hpp",
+                "site_update.hpp", "philox.hpp", "spinlat_internal.h", "host_logic.h")
 KERNEL_SOURCES = {
     "ising2d_L8192": ROW_SOURCES,
     "ising3d_L256_s12": ROWS_SOURCES,
     "ising3d_L256_s1": ROWS_SOURCES,
-    "ne2d_L4096": ROW_SOURCES,
-    "ne2d_sub_L4096": ("ne_sub_device.hpp", "philox.hpp", "spinlat_internal.h", "host_logic.h"),
+    "ne2d_L4096": ("kernels_tile_bits.hip", "kernels_tile.hip", "tile_plan.h", "block_order.hpp",
+                   "site_update.hpp", "philox.hpp", "spinlat_internal.h", "host_logic.h"),
+    "ne2d_sub_L4096": ("ne_sub_device.hpp", "site_update.hpp", "philox.hpp", "spinlat_internal.h",
+                       "host_logic.h"),
 }
 
 
@@ -66,7 +68,8 @@ def _profile_entry(workload):
 
 
 def measured_traffic(workload):
-    """HBM bytes per launch from the committed FETCH_SIZE/WRITE_SIZE profile."""
+    """HBM bytes per launch (of several sweeps: a sweep's share) from the committed
+    FETCH_SIZE/WRITE_SIZE profile."""
     entry = _profile_entry(workload)
     return entry["bytes_per_launch"] if entry else None
 
@@ -130,10 +133,13 @@ def time_workload(S, torch, name, cfg, steps, warmup, T=None, prewarm_s=0.0):
     lat.close()
     attempts = p.nsites * steps
     if p.model in (S.NE_SUBLATTICE, S.NE_SUBLATTICE_BALANCED):
-        # two (balanced: four) launches per sweep, each reading and writing the lattice
+        # two (balanced: four) launches per sweep, each reading and writing the lattice,
+        # which between a call's launches is two bits a site
         launches_per_sweep = 2 if p.model == S.NE_SUBLATTICE else 4
-        bytes_per_launch = 2 * p.nsites
+        bytes_per_launch = p.nsites // 2
     else:
+        # by the schedule that get_launch names; the default runs several sweeps per
+        # launch where that is faster, and a "launch" is then a sweep's share of one
         launches_per_sweep = 1 if mode[0] == S.MODE_FUSED else 2
         bytes_per_launch = ALGO_BYTES_PER_ATTEMPT * p.nsites / launches_per_sweep
     per_launch_s = sweep_ms / 1e3 / (steps * launches_per_sweep)
