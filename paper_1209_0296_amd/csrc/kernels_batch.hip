@@ -183,9 +183,11 @@ __device__ __forceinline__ void dispatch(uint32_t v, const BatchJob& J, const ui
 static_assert(kBatchKindNeCoupled == KIND_NE_COUPLED, "batch class kind of coupled NE jobs");
 
 // One family's launch: meta = {count, offset} of the family's work-list
-// segment (valid entries; the grid may be larger: a bucket size).
+// segment (valid entries; the grid may be larger: a bucket size).  The walks and
+// windows keep to 96 registers, five waves a SIMD (64 NE jobs of L = 2048: 99 registers
+// 196 us a sweep, 96 186).
 template <int FAM>
-__global__ void __launch_bounds__(256) k_batch_family(const BatchJob* __restrict__ jobs,
+__global__ void __launch_bounds__(256, FAM == kFamHalf ? 5 : 1) k_batch_family(const BatchJob* __restrict__ jobs,
                                                       const uint32_t* __restrict__ dyn,
                                                       const BatchWG* __restrict__ wgs,
                                                       const uint32_t* __restrict__ meta, uint32_t colour, uint32_t step)
