@@ -78,7 +78,7 @@ __device__ __forceinline__ uint32_t pair_accept(const PairLut& lut, uint32_t idx
 // Spin-1: entry row (2z + 1) + nsum + z, row = ds_index(s' - s) in 0 .. 3.
 struct OneLut {
     uint32_t e[52];     // thr - 1
-    uint32_t zero[52];  // 1 where thr is 0 (read only if a table has such)
+    uint32_t live[52];  // all ones, 0 where thr is 0 (read only if a table has such)
 };
 
 // Called by all threads of the block (the first wave writes); returns whether
@@ -91,7 +91,7 @@ __device__ __forceinline__ bool build_one_lut(OneLut& lut, const uint64_t* table
     const uint64_t thr = table[t < n ? t : 0u];
     if (threadIdx.x < n) {
         lut.e[t] = (uint32_t)(thr - 1ull);
-        lut.zero[t] = thr == 0 ? 1u : 0u;
+        lut.live[t] = thr == 0 ? 0u : ~0u;
     }
     return __builtin_amdgcn_ballot_w64(thr == 0) != 0ull;
 }
@@ -115,19 +115,18 @@ __device__ __forceinline__ uint32_t one_move(uint32_t q, uint32_t S, const Words
                                                 ((2u * row) << 24), sel);
     const uint32_t idx = (S << 2) + rows;
     const uint8_t* base = reinterpret_cast<const uint8_t*>(lut.e);
-    uint32_t t[4], b4[4];
+    const uint8_t* live = reinterpret_cast<const uint8_t*>(lut.live);
+    uint32_t t[4], on[4], b4[4];
 #pragma unroll
-    for (int b = 0; b < 4; ++b) t[b] = *reinterpret_cast<const uint32_t*>(base + ((idx >> (8 * b)) & 0xFFu));
+    for (int b = 0; b < 4; ++b) {
+        const uint32_t at = (idx >> (8 * b)) & 0xFFu;
+        t[b] = *reinterpret_cast<const uint32_t*>(base + at);
+        on[b] = ZERO ? *reinterpret_cast<const uint32_t*>(live + at) : ~0u;
+    }
     between();
 #pragma unroll
-    for (int b = 0; b < 4; ++b) b4[b] = (b < 2 ? wa : wb).w[(b & 1) * 2] <= t[b] ? 0xFFu << (8 * b) : 0u;
+    for (int b = 0; b < 4; ++b) b4[b] = (b < 2 ? wa : wb).w[(b & 1) * 2] <= t[b] ? on[b] & (0xFFu << (8 * b)) : 0u;
     f = (b4[0] | b4[1] | b4[2]) | b4[3];
-    if constexpr (ZERO) {
-        const uint8_t* zb = reinterpret_cast<const uint8_t*>(lut.zero);
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-            if (*reinterpret_cast<const uint32_t*>(zb + ((idx >> (8 * b)) & 0xFFu))) f &= ~(0xFFu << (8 * b));
-    }
     return (cand & f) | (q & ~f);
 }
 

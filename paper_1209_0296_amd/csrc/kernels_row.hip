@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(1024) k_row_fused(SweepArgs a, RowGeom rg, con
     if constexpr (KIND == KIND_ISING_ONE) zero = thr_up != 0;  // tables with a zero threshold
     if constexpr (KIND == KIND_ISING_ONE)
         if (zero)
-            fused_item<KIND_ISING_ONE_ZERO, D, XW, 0>(a, rg, item, ln, lut, xch, thr_up, thr_down, S0, S1, D0, D1, o);
+            fused_item<KIND_ISING_ONE_ZERO, D, XW, HT == 2 ? 2 : 0>(a, rg, item, ln, lut, xch, thr_up, thr_down, S0, S1, D0, D1, o);
     if (!zero) fused_item<KIND, D, XW, HT>(a, rg, item, ln, lut, xch, thr_up, thr_down, S0, S1, D0, D1, o);
     int32_t bond, mag, acc, unfl;
     finish_obs<KIND, 2>(o, bond, mag, acc, unfl);

@@ -421,7 +421,14 @@ sl_status enqueue_sweeps(sl_lattice* h, uint64_t n)
 {
     if (is_sub_lattice(h->params.model)) return sweep_ne_sub(h, n);
     SweepArgs a = args_of(h);
-    if (h->tile.k) {
+    // One sweep alone does not pay for a tile's halo where whole rows run it in one
+    // launch (us, rows against tiles: spin-1/2 L = 1536 16.6 and 17.5, 4096 26.1 and
+    // 34.0, 6144 45.8 and 55.8), nor do two of spin-1/2 around L = 4096 (41.4 and 43.6;
+    // 2048 24.7 and 21.0, 6144 81 and 78)
+    const int L = h->params.L;
+    const bool few = n == 1 || (n == 2 && h->kind == KIND_ISING_HALF && L >= 4096 && L < 6144);
+    const bool rows = few && !h->tile.bits && h->launch.mode == SL_MODE_FUSED && L >= 1536;
+    if (h->tile.k && !rows) {
         // equal launches of at most k sweeps
         const uint64_t launches = (n + h->tile.k - 1) / h->tile.k;
         for (uint64_t i = 0, l = 0; l < launches; ++l) {

@@ -78,3 +78,9 @@ def test_tiles_between_other_schedules():
     np.testing.assert_array_equal(np.vstack(recs), ref_r)
     np.testing.assert_array_equal(lat.spins(), ref_s)
     lat.close()
+
+
+@pytest.mark.parametrize("L,kind", [(1536, "half"), (1536, "one"), (2048, "ne_up"), (2048, "coupled"), (4096, "half")])
+def test_short_calls_between_tile_launches(L, kind):
+    """Calls of one (or two) sweeps run on whole rows, longer ones on tiles."""
+    _same(S.Params(L=L, seed=L + 5, record_capacity=16, **KINDS[kind]), [1, 3, 1, 2] if L < 4000 else [2, 3, 1])
