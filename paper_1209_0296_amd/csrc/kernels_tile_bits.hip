@@ -119,7 +119,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_tile_bits(SweepArgs a, TileGeom t
 #pragma unroll
             for (int g = 0; g < 8; ++g) {
                 const uint32_t x = gx + g, col = x >= tg.ncols ? x - tg.ncols : x;
-                const uint32_t off = 4u * (row0[i] + col);
+                const uint64_t off = 4ull * (row0[i] + col);
                 v[0][g] = *reinterpret_cast<const uint32_t*>(a.col[0] + off);
                 v[1][g] = *reinterpret_cast<const uint32_t*>(a.col[1] + off);
             }
