@@ -161,6 +161,7 @@ uint32_t plane_depth(uint64_t planes)
 // Workgroups of a job in a call, at most.
 uint64_t most_workgroups(const RowGeomHost& g)
 {
+    if (g.variant == kBvResident || g.variant == kBvWhole) return 0;  // not in the work list
     const uint64_t per = g.variant == kBvPlane ? 4 : g.items_per_wg;
     return (g.nitems + per - 1) / per;
 }
@@ -296,30 +297,69 @@ bool find_second(const sl_batch* b, size_t bytes, size_t* off)
     return false;
 }
 
+// Job j goes on in its least class: the state moves to its own copy, a lent one is
+// given up.
+hipError_t demote(sl_batch* b, uint32_t j)
+{
+    JobHost& J = b->jobs[j];
+    if (J.lent && J.cur == 1) {
+        const hipError_t e = hipMemcpyAsync(col_of(b, J, 0, 0), col_of(b, J, 1, 0), 2 * J.foot.col_bytes,
+                                            hipMemcpyDeviceToDevice, b->stream);
+        if (e != hipSuccess) return e;
+    }
+    if (J.lent) J.cur = 0;
+    J.lent = false;
+    J.geom = J.least;
+    const BatchJob entry = job_entry(b, j);
+    StartArgs s{};  // no lattice, no ring: the entry alone
+    s.blob_dst = reinterpret_cast<uint32_t*>(d_jobs(b) + j);
+    s.blob_words = (uint32_t)(sizeof(BatchJob) / 4);
+    StartBlob blob;
+    std::memcpy(blob.w, &entry, sizeof(BatchJob));
+    return launch_start(s, J.kind, blob, b->stream);
+}
+
 // Second copies in [off, off + bytes) are given up: their jobs go on in the class
 // that needs one.
 hipError_t take_back(sl_batch* b, size_t off, size_t bytes)
 {
     for (uint32_t j = 0; j < b->jobs.size(); ++j) {
-        JobHost& J = b->jobs[j];
-        const size_t second = 2 * J.foot.col_bytes;
-        if (!J.used || !J.lent || J.off2 >= off + bytes || J.off2 + second <= off) continue;
-        if (J.cur == 1) {
-            const hipError_t e = hipMemcpyAsync(col_of(b, J, 0, 0), col_of(b, J, 1, 0), second,
-                                                hipMemcpyDeviceToDevice, b->stream);
-            if (e != hipSuccess) return e;
-        }
-        J.geom = J.least;
-        J.lent = false;
-        J.cur = 0;
-        const BatchJob entry = job_entry(b, j);
-        StartArgs s{};  // no lattice, no ring: the entry alone
-        s.blob_dst = reinterpret_cast<uint32_t*>(d_jobs(b) + j);
-        s.blob_words = (uint32_t)(sizeof(BatchJob) / 4);
-        StartBlob blob;
-        std::memcpy(blob.w, &entry, sizeof(BatchJob));
-        const hipError_t e = launch_start(s, J.kind, blob, b->stream);
+        const JobHost& J = b->jobs[j];
+        if (!J.used || !J.lent || J.off2 >= off + bytes || J.off2 + 2 * J.foot.col_bytes <= off) continue;
+        const hipError_t e = demote(b, j);
         if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// Workgroups of every job's class in a call, at most.
+uint64_t list_workgroups(const sl_batch* b)
+{
+    uint64_t total = 0;
+    for (const JobHost& J : b->jobs)
+        if (J.used) total += most_workgroups(J.geom);
+    return total;
+}
+
+// Tiles of 2D rows that a row class takes in few strips need more workgroups than
+// it (L = 1536: 276 and 96).  Jobs whose least classes fit the work list must not
+// overflow it, so where `more` further workgroups would, jobs leave their tiles,
+// those that save most first.
+hipError_t make_list_room(sl_batch* b, uint64_t more)
+{
+    uint64_t total = list_workgroups(b) + more;
+    if (total <= max_wg(&b->cfg)) return hipSuccess;
+    std::vector<std::pair<uint64_t, uint32_t>> saves;
+    for (uint32_t j = 0; j < b->jobs.size(); ++j) {
+        const JobHost& J = b->jobs[j];
+        if (J.used && most_workgroups(J.geom) > most_workgroups(J.least))
+            saves.emplace_back(most_workgroups(J.geom) - most_workgroups(J.least), j);
+    }
+    std::sort(saves.rbegin(), saves.rend());
+    for (size_t i = 0; i < saves.size() && total > max_wg(&b->cfg); ++i) {
+        const hipError_t e = demote(b, saves[i].second);
+        if (e != hipSuccess) return e;
+        total -= saves[i].first;
     }
     return hipSuccess;
 }
@@ -548,6 +588,10 @@ sl_status sl_batch_add(sl_batch* b, const sl_params* params, uint64_t sweeps, ui
     if (!b->heap.alloc(J.foot.total, &J.off))
         return fail(SL_E_BUFFER, "arena has no free block of %zu bytes for this job", J.foot.total);
     hipError_t e = take_back(b, J.off, J.foot.total);
+    if (most_workgroups(J.geom) > most_workgroups(J.least) &&
+        list_workgroups(b) + most_workgroups(J.geom) > max_wg(&b->cfg))
+        J.geom = J.least;
+    if (e == hipSuccess) e = make_list_room(b, most_workgroups(J.geom));
     if (e != hipSuccess) {
         (void)hipStreamSynchronize(b->stream);
         b->heap.release(J.off, J.foot.total);

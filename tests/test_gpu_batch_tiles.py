@@ -95,3 +95,29 @@ def test_an_arena_of_the_sum_of_the_reported_bytes_admits_every_job(jobs):
         np.testing.assert_array_equal(np.vstack(recs[i]), o_r)
         np.testing.assert_array_equal(b.spins(i), o_s)
     b.close()
+
+
+def test_tiles_do_not_overflow_the_default_work_list():
+    """3000 jobs of 2D L = 1760 are 1.09 million tiles, more than the default work list
+    of 2^20 holds; in the row class, which the same arena always had room for, 330
+    thousand strips.  Every job is the same lattice, so one oracle run checks all; the
+    last 120 are added when the others' state lies in the tiles' second copy."""
+    p, n, late = S.Params(L=1760, T=2.3, seed=9), 3000, 120
+    cfg = S.batch_config(max_jobs=n, record_capacity=8)
+    second = 2 * ((p.nsites // 2 + 255) // 256 * 256)
+    b = S.Batch(S.batch_base_bytes(cfg) + n * (S.batch_job_bytes(p, cfg) + second), max_jobs=n, record_capacity=8)
+    for _ in range(n - late):
+        assert b.add(p, sweeps=5) is not None
+    b.sweep(2)
+    for _ in range(late):
+        assert b.add(p, sweeps=5) is not None
+    b.sweep(3)
+    b.sweep(2)
+    got = b.drain()
+    o_s, o_r = run_oracle(p, 5)
+    assert len(got) == n
+    for r in got.values():
+        np.testing.assert_array_equal(r, o_r)
+    for i in (0, n // 2, n - 1):
+        np.testing.assert_array_equal(b.spins(i), o_s)
+    b.close()
