@@ -298,7 +298,8 @@ sl_status sl_record_observables(const sl_params* params, const sl_record* record
  * tiles in LDS, four sweeps per launch (2D), as walks along z (3D), or, if one
  * tile holds the lattice, a whole call in one launch, while the arena has room
  * to spare for a second copy of the lattice and tile_rows is 0 (admission does
- * not depend on it); else, or with the flags:
+ * not depend on it; a job whose second copy a new one takes goes back to its
+ * tiles or walks when room comes free); else, or with the flags:
  *   - resident: both colours fit 48 KiB; one workgroup per job runs the
  *     call's sweeps in LDS, in one launch per call for all such jobs, on a
  *     stream of the library's own that overlaps the other launches;

@@ -10,7 +10,7 @@
 // carved first-fit.  Admission by footprint is the heap allocation succeeding.
 // Tiles and walks along z need a second lattice copy, lent from the heap's free
 // ranges; where there is no room for it, or a new job takes it, a job runs in the
-// one-copy class that sl_batch_job_bytes reports.
+// one-copy class that sl_batch_job_bytes reports, until room comes free again.
 //
 // A call (sl_batch_sweep) uploads the counters and work lists from pinned
 // staging (double-buffered, so the host never waits for the previous call),
@@ -130,7 +130,8 @@ struct JobHost {
     int kind = 0;
     size_t off = 0;
     JobFoot foot{};
-    RowGeomHost geom{}, least{};  // class in use; the one the footprint is for
+    // class in use; the one the footprint is for; the one to use while there is room
+    RowGeomHost geom{}, least{}, want{};
     bool lent = false;            // copy 1 lies at off2, in a free range of the heap
     size_t off2 = 0;
     uint32_t cur = 0;  // copy holding the current state (fused jobs alternate)
@@ -201,6 +202,8 @@ struct sl_batch {
     BaseLayout base;
     std::vector<JobHost> jobs;
     FreeList heap;       // free ranges of the job heap
+    std::map<size_t, size_t> lent;  // lent second copies in free ranges: end -> start
+    bool retry;          // room has come free since jobs last went back to their wanted class
     uint8_t* h_up[2];    // pinned upload staging, one per upload set
     sl_record* h_stage;  // pinned [max_jobs * record_capacity]
     BatchFold* h_fold;   // pinned [max_jobs]
@@ -277,10 +280,7 @@ BatchJob job_entry(const sl_batch* b, uint32_t j)
 // depend on the second copies.
 bool find_second(const sl_batch* b, size_t bytes, size_t* off)
 {
-    std::map<size_t, size_t> lent;  // end -> start
-    for (const JobHost& J : b->jobs)
-        if (J.used && J.lent) lent[J.off2 + 2 * J.foot.col_bytes] = J.off2;
-    const std::map<size_t, size_t>& ranges = b->heap.map();
+    const std::map<size_t, size_t>&lent = b->lent, &ranges = b->heap.map();
     for (auto r = ranges.rbegin(); r != ranges.rend(); ++r) {
         const size_t start = r->first;
         size_t end = start + r->second;
@@ -297,6 +297,25 @@ bool find_second(const sl_batch* b, size_t bytes, size_t* off)
     return false;
 }
 
+// Device job-table entry of job j in its present class, in stream order: a start of
+// no lattice and no ring.
+hipError_t write_entry(sl_batch* b, uint32_t j)
+{
+    const BatchJob entry = job_entry(b, j);
+    StartArgs s{};
+    s.blob_dst = reinterpret_cast<uint32_t*>(d_jobs(b) + j);
+    s.blob_words = (uint32_t)(sizeof(BatchJob) / 4);
+    StartBlob blob;
+    std::memcpy(blob.w, &entry, sizeof(BatchJob));
+    return launch_start(s, b->jobs[j].kind, blob, b->stream);
+}
+
+void give_up_second(sl_batch* b, JobHost& J)
+{
+    if (J.lent) b->lent.erase(J.off2 + 2 * J.foot.col_bytes);
+    J.lent = false;
+}
+
 // Job j goes on in its least class: the state moves to its own copy, a lent one is
 // given up.
 hipError_t demote(sl_batch* b, uint32_t j)
@@ -308,15 +327,9 @@ hipError_t demote(sl_batch* b, uint32_t j)
         if (e != hipSuccess) return e;
     }
     if (J.lent) J.cur = 0;
-    J.lent = false;
+    give_up_second(b, J);
     J.geom = J.least;
-    const BatchJob entry = job_entry(b, j);
-    StartArgs s{};  // no lattice, no ring: the entry alone
-    s.blob_dst = reinterpret_cast<uint32_t*>(d_jobs(b) + j);
-    s.blob_words = (uint32_t)(sizeof(BatchJob) / 4);
-    StartBlob blob;
-    std::memcpy(blob.w, &entry, sizeof(BatchJob));
-    return launch_start(s, J.kind, blob, b->stream);
+    return write_entry(b, j);
 }
 
 // Second copies in [off, off + bytes) are given up: their jobs go on in the class
@@ -360,6 +373,46 @@ hipError_t make_list_room(sl_batch* b, uint64_t more)
         const hipError_t e = demote(b, saves[i].second);
         if (e != hipSuccess) return e;
         total -= saves[i].first;
+    }
+    return hipSuccess;
+}
+
+// A second copy for a job in its wanted class, where that needs one.
+bool lend_second(sl_batch* b, JobHost& J)
+{
+    if (J.want.copies <= J.least.copies) return true;
+    J.lent = find_second(b, 2 * J.foot.col_bytes, &J.off2);
+    if (J.lent) b->lent[J.off2 + 2 * J.foot.col_bytes] = J.off2;
+    return J.lent;
+}
+
+// Jobs that gave up their tiles or walks take them again where room has come free
+// since, in the order of their slots.
+hipError_t promote(sl_batch* b)
+{
+    if (!b->retry) return hipSuccess;
+    b->retry = false;
+    uint64_t total = list_workgroups(b);
+    size_t refused = ~(size_t)0;  // the least second copy that found no room
+    for (uint32_t j = 0; j < b->jobs.size(); ++j) {
+        JobHost& J = b->jobs[j];
+        if (!J.used || !J.remaining || J.geom.variant == J.want.variant) continue;
+        const uint64_t now = total - most_workgroups(J.geom) + most_workgroups(J.want);
+        const size_t second = 2 * J.foot.col_bytes;
+        if (most_workgroups(J.want) > most_workgroups(J.geom) && now > max_wg(&b->cfg)) continue;
+        if (J.want.copies > J.least.copies && second >= refused) continue;
+        if (!lend_second(b, J)) {
+            refused = second;
+            continue;
+        }
+        J.geom = J.want;  // J.cur: 0 in a class of one copy, else either way
+        total = now;
+        const hipError_t e = write_entry(b, j);
+        if (e != hipSuccess) {
+            give_up_second(b, J);
+            J.geom = J.least;
+            return e;
+        }
     }
     return hipSuccess;
 }
@@ -548,6 +601,7 @@ sl_status sl_batch_create(const sl_batch_config* cfg, void* device_arena, size_t
     b->h_stage = nullptr;
     b->h_fold = nullptr;
     b->calls = 0;
+    b->retry = false;
     hipError_t e = hipSuccess;
     for (int k = 0; k < 2 && e == hipSuccess; ++k)
         e = hipHostMalloc(reinterpret_cast<void**>(&b->h_up[k]), base.u.bytes, hipHostMallocDefault);
@@ -578,8 +632,9 @@ sl_status sl_batch_add(sl_batch* b, const sl_params* params, uint64_t sweeps, ui
     if (!b) return fail(SL_E_INVALID, "NULL batch");
     if (!job_id) return fail(SL_E_INVALID, "job_id is NULL");
     JobHost J;
-    sl_status st = prepare_job(&b->cfg, params, &J.params, &J.foot, &J.geom, &J.least, J.table, &J.table_n);
+    sl_status st = prepare_job(&b->cfg, params, &J.params, &J.foot, &J.want, &J.least, J.table, &J.table_n);
     if (st != SL_OK) return st;
+    J.geom = J.want;
     if (sweeps > (1ull << 32) - J.params.t0)  // validate() keeps t0 < 2^32
         return fail(SL_E_OVERFLOW, "t0 + sweeps would pass 2^32");
     uint32_t j = 0;
@@ -597,10 +652,7 @@ sl_status sl_batch_add(sl_batch* b, const sl_params* params, uint64_t sweeps, ui
         b->heap.release(J.off, J.foot.total);
         return hip_fail(e, "batch add");
     }
-    if (J.geom.copies > J.least.copies) {
-        J.lent = find_second(b, 2 * J.foot.col_bytes, &J.off2);
-        if (!J.lent) J.geom = J.least;
-    }
+    if (J.geom.variant == J.want.variant && !lend_second(b, J)) J.geom = J.least;
     J.used = true;
     J.kind = kind_of(&J.params);
     J.t = J.params.t0;
@@ -622,6 +674,7 @@ sl_status sl_batch_add(sl_batch* b, const sl_params* params, uint64_t sweeps, ui
     if (e != hipSuccess) {
         (void)hipStreamSynchronize(b->stream);
         b->heap.release(J.off, J.foot.total);
+        give_up_second(b, b->jobs[j]);
         b->jobs[j] = JobHost();
         return hip_fail(e, "batch add");
     }
@@ -648,11 +701,13 @@ sl_status sl_batch_sweep(sl_batch* b, uint64_t n)
         n_eff = std::max(n_eff, budget[j]);
     }
     if (n_eff == 0) return SL_OK;
+    hipError_t e = promote(b);
+    if (e != hipSuccess) return hip_fail(e, "batch: job entries");
 
     // this call's upload set; wait until the launches that read it last (two
     // calls ago) have been enqueued past its upload
     const int k = (int)(b->calls & 1u);
-    hipError_t e = hipEventSynchronize(b->ev_up[k]);
+    e = hipEventSynchronize(b->ev_up[k]);
     if (e != hipSuccess) return hip_fail(e, "batch: wait for staging");
     const UploadLayout& u = b->base.u;
     uint8_t* hu = b->h_up[k];
@@ -913,7 +968,9 @@ sl_status sl_batch_remove(sl_batch* b, uint32_t job_id)
     if (e != hipSuccess) return hip_fail(e, "batch remove");
     JobHost& J = b->jobs[job_id];
     b->heap.release(J.off, J.foot.total);
+    give_up_second(b, J);
     J = JobHost();
+    b->retry = true;
     return SL_OK;
 }
 

@@ -121,3 +121,31 @@ def test_tiles_do_not_overflow_the_default_work_list():
     for i in (0, n // 2, n - 1):
         np.testing.assert_array_equal(b.spins(i), o_s)
     b.close()
+
+
+@pytest.mark.parametrize("p", [S.Params(dim=3, L=72, T=4.6, seed=3), S.Params(L=936, two_s=2, T=1.6, seed=4)])
+def test_a_second_copy_is_lent_again_when_room_comes_free(p):
+    """A job whose second copy a new job took writes one again once that job is gone:
+    a lattice copy of the free arena space, marked before, is then overwritten."""
+    cfg = S.batch_config(max_jobs=2, record_capacity=16)
+    base, one = S.batch_base_bytes(cfg), S.batch_job_bytes(p, cfg)
+    b = S.Batch(base + 2 * one, max_jobs=2, record_capacity=16)
+    i = b.add(p, sweeps=14)
+    b.sweep(3)
+    k = b.add(p, sweeps=14)
+    b.sweep(2)
+    b.arena.cpu()  # nothing runs from here on
+    assert k is not None
+    b.remove(k)
+    free = b.arena[base + one:]
+    free.fill_(0x55)
+    b.sweep(1)
+    assert int((free != 0x55).sum()) >= 0.9 * p.nsites
+    b.sweep(3)
+    k = b.add(p, sweeps=14)  # taken once more, while it may hold the state
+    b.sweep(5)
+    for j, n in ((i, 14), (k, 5)):
+        o_s, o_r = run_oracle(p, n)
+        np.testing.assert_array_equal(S.records_to_array(b.measure(j)), o_r)
+        np.testing.assert_array_equal(b.spins(j), o_s)
+    b.close()
