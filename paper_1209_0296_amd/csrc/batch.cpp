@@ -173,6 +173,11 @@ int class_kind(const JobHost& J)
     return J.params.model == SL_NE_COUPLED ? kBatchKindNeCoupled : J.kind;
 }
 
+struct Lent {
+    size_t start;
+    uint32_t job;
+};
+
 struct GraphEntry {
     uint64_t key;  // sweeps * 2 + upload set
     uint32_t grid[kBatchFamilies];
@@ -202,8 +207,10 @@ struct sl_batch {
     BaseLayout base;
     std::vector<JobHost> jobs;
     FreeList heap;       // free ranges of the job heap
-    std::map<size_t, size_t> lent;  // lent second copies in free ranges: end -> start
+    std::map<size_t, Lent> lent;  // lent second copies in free ranges, by their end
+    uint64_t list_most;  // workgroups of every job's class in a call, at most
     bool retry;          // room has come free since jobs last went back to their wanted class
+    bool refused;        // a job found no room since the last call
     uint8_t* h_up[2];    // pinned upload staging, one per upload set
     sl_record* h_stage;  // pinned [max_jobs * record_capacity]
     BatchFold* h_fold;   // pinned [max_jobs]
@@ -280,14 +287,15 @@ BatchJob job_entry(const sl_batch* b, uint32_t j)
 // depend on the second copies.
 bool find_second(const sl_batch* b, size_t bytes, size_t* off)
 {
-    const std::map<size_t, size_t>&lent = b->lent, &ranges = b->heap.map();
+    const std::map<size_t, Lent>& lent = b->lent;
+    const std::map<size_t, size_t>& ranges = b->heap.map();
     for (auto r = ranges.rbegin(); r != ranges.rend(); ++r) {
         const size_t start = r->first;
         size_t end = start + r->second;
-        for (auto l = lent.rbegin(); l != lent.rend(); ++l) {
-            if (l->first > end || l->second < start) continue;  // of another range
-            if (end - l->first >= bytes) break;
-            end = l->second;
+        for (auto l = lent.upper_bound(end); l != lent.begin();) {
+            --l;
+            if (l->first <= start || end - l->first >= bytes) break;  // of another range, or a gap
+            end = l->second.start;
         }
         if (end - start >= bytes) {
             *off = end - bytes;
@@ -295,6 +303,13 @@ bool find_second(const sl_batch* b, size_t bytes, size_t* off)
         }
     }
     return false;
+}
+
+// The class that job J, one of the batch's, runs in from here on.
+void set_class(sl_batch* b, JobHost& J, const RowGeomHost& geom)
+{
+    b->list_most = b->list_most - most_workgroups(J.geom) + most_workgroups(geom);
+    J.geom = geom;
 }
 
 // Device job-table entry of job j in its present class, in stream order: a start of
@@ -316,42 +331,40 @@ void give_up_second(sl_batch* b, JobHost& J)
     J.lent = false;
 }
 
-// Job j goes on in its least class: the state moves to its own copy, a lent one is
-// given up.
+// Job j goes on in its least class: the state moves to the first copy, a second one
+// apart from it is given up.
 hipError_t demote(sl_batch* b, uint32_t j)
 {
     JobHost& J = b->jobs[j];
-    if (J.lent && J.cur == 1) {
+    const bool apart = J.lent;  // copy 1
+    if (apart && J.cur == 1) {
         const hipError_t e = hipMemcpyAsync(col_of(b, J, 0, 0), col_of(b, J, 1, 0), 2 * J.foot.col_bytes,
                                             hipMemcpyDeviceToDevice, b->stream);
         if (e != hipSuccess) return e;
     }
-    if (J.lent) J.cur = 0;
+    if (apart) J.cur = 0;
     give_up_second(b, J);
-    J.geom = J.least;
+    set_class(b, J, J.least);
     return write_entry(b, j);
 }
 
-// Second copies in [off, off + bytes) are given up: their jobs go on in the class
-// that needs one.
+// Lent second copies in [off, off + bytes): their jobs.
+std::vector<uint32_t> lent_in(const sl_batch* b, size_t off, size_t bytes)
+{
+    std::vector<uint32_t> out;
+    for (auto l = b->lent.upper_bound(off); l != b->lent.end() && l->second.start < off + bytes; ++l)
+        out.push_back(l->second.job);
+    return out;
+}
+
+// These are given up: their jobs go on in the class that needs one.
 hipError_t take_back(sl_batch* b, size_t off, size_t bytes)
 {
-    for (uint32_t j = 0; j < b->jobs.size(); ++j) {
-        const JobHost& J = b->jobs[j];
-        if (!J.used || !J.lent || J.off2 >= off + bytes || J.off2 + 2 * J.foot.col_bytes <= off) continue;
+    for (uint32_t j : lent_in(b, off, bytes)) {
         const hipError_t e = demote(b, j);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
-}
-
-// Workgroups of every job's class in a call, at most.
-uint64_t list_workgroups(const sl_batch* b)
-{
-    uint64_t total = 0;
-    for (const JobHost& J : b->jobs)
-        if (J.used) total += most_workgroups(J.geom);
-    return total;
 }
 
 // Tiles of 2D rows that a row class takes in few strips need more workgroups than
@@ -360,8 +373,8 @@ uint64_t list_workgroups(const sl_batch* b)
 // those that save most first.
 hipError_t make_list_room(sl_batch* b, uint64_t more)
 {
-    uint64_t total = list_workgroups(b) + more;
-    if (total <= max_wg(&b->cfg)) return hipSuccess;
+    const uint64_t most = max_wg(&b->cfg);
+    if (b->list_most + more <= most) return hipSuccess;
     std::vector<std::pair<uint64_t, uint32_t>> saves;
     for (uint32_t j = 0; j < b->jobs.size(); ++j) {
         const JobHost& J = b->jobs[j];
@@ -369,48 +382,48 @@ hipError_t make_list_room(sl_batch* b, uint64_t more)
             saves.emplace_back(most_workgroups(J.geom) - most_workgroups(J.least), j);
     }
     std::sort(saves.rbegin(), saves.rend());
-    for (size_t i = 0; i < saves.size() && total > max_wg(&b->cfg); ++i) {
+    for (size_t i = 0; i < saves.size() && b->list_most + more > most; ++i) {
         const hipError_t e = demote(b, saves[i].second);
         if (e != hipSuccess) return e;
-        total -= saves[i].first;
     }
     return hipSuccess;
 }
 
 // A second copy for a job in its wanted class, where that needs one.
-bool lend_second(sl_batch* b, JobHost& J)
+bool lend_second(sl_batch* b, uint32_t j, JobHost& J)
 {
     if (J.want.copies <= J.least.copies) return true;
     J.lent = find_second(b, 2 * J.foot.col_bytes, &J.off2);
-    if (J.lent) b->lent[J.off2 + 2 * J.foot.col_bytes] = J.off2;
+    if (J.lent) b->lent[J.off2 + 2 * J.foot.col_bytes] = Lent{J.off2, j};
     return J.lent;
 }
 
 // Jobs that gave up their tiles or walks take them again where room has come free
-// since, in the order of their slots.
+// since, in the order of their slots.  Not while jobs are refused for want of room:
+// the next one would take the copies back at once.
 hipError_t promote(sl_batch* b)
 {
-    if (!b->retry) return hipSuccess;
+    const bool refused = b->refused;
+    b->refused = false;
+    if (!b->retry || refused) return hipSuccess;
     b->retry = false;
-    uint64_t total = list_workgroups(b);
-    size_t refused = ~(size_t)0;  // the least second copy that found no room
+    size_t none = ~(size_t)0;  // the least second copy that found no room
     for (uint32_t j = 0; j < b->jobs.size(); ++j) {
         JobHost& J = b->jobs[j];
         if (!J.used || !J.remaining || J.geom.variant == J.want.variant) continue;
-        const uint64_t now = total - most_workgroups(J.geom) + most_workgroups(J.want);
+        const uint64_t now = most_workgroups(J.geom), then = most_workgroups(J.want);
         const size_t second = 2 * J.foot.col_bytes;
-        if (most_workgroups(J.want) > most_workgroups(J.geom) && now > max_wg(&b->cfg)) continue;
-        if (J.want.copies > J.least.copies && second >= refused) continue;
-        if (!lend_second(b, J)) {
-            refused = second;
+        if (then > now && b->list_most - now + then > max_wg(&b->cfg)) continue;
+        if (J.want.copies > J.least.copies && second >= none) continue;
+        if (!lend_second(b, j, J)) {
+            none = second;
             continue;
         }
-        J.geom = J.want;  // J.cur: 0 in a class of one copy, else either way
-        total = now;
+        set_class(b, J, J.want);  // J.cur: 0 in a class of one copy, else either way
         const hipError_t e = write_entry(b, j);
         if (e != hipSuccess) {
             give_up_second(b, J);
-            J.geom = J.least;
+            set_class(b, J, J.least);
             return e;
         }
     }
@@ -601,7 +614,8 @@ sl_status sl_batch_create(const sl_batch_config* cfg, void* device_arena, size_t
     b->h_stage = nullptr;
     b->h_fold = nullptr;
     b->calls = 0;
-    b->retry = false;
+    b->list_most = 0;
+    b->retry = b->refused = false;
     hipError_t e = hipSuccess;
     for (int k = 0; k < 2 && e == hipSuccess; ++k)
         e = hipHostMalloc(reinterpret_cast<void**>(&b->h_up[k]), base.u.bytes, hipHostMallocDefault);
@@ -640,19 +654,20 @@ sl_status sl_batch_add(sl_batch* b, const sl_params* params, uint64_t sweeps, ui
     uint32_t j = 0;
     while (j < b->jobs.size() && b->jobs[j].used) ++j;
     if (j == b->jobs.size()) return fail(SL_E_STATE, "job table full (%u jobs)", b->cfg.max_jobs);
-    if (!b->heap.alloc(J.foot.total, &J.off))
+    if (!b->heap.alloc(J.foot.total, &J.off)) {
+        b->refused = true;
         return fail(SL_E_BUFFER, "arena has no free block of %zu bytes for this job", J.foot.total);
+    }
+    const bool list_full = b->list_most + most_workgroups(J.want) > max_wg(&b->cfg);
+    if (list_full && most_workgroups(J.want) > most_workgroups(J.least)) J.geom = J.least;
     hipError_t e = take_back(b, J.off, J.foot.total);
-    if (most_workgroups(J.geom) > most_workgroups(J.least) &&
-        list_workgroups(b) + most_workgroups(J.geom) > max_wg(&b->cfg))
-        J.geom = J.least;
     if (e == hipSuccess) e = make_list_room(b, most_workgroups(J.geom));
     if (e != hipSuccess) {
         (void)hipStreamSynchronize(b->stream);
         b->heap.release(J.off, J.foot.total);
         return hip_fail(e, "batch add");
     }
-    if (J.geom.variant == J.want.variant && !lend_second(b, J)) J.geom = J.least;
+    if (J.geom.variant == J.want.variant && !lend_second(b, j, J)) J.geom = J.least;
     J.used = true;
     J.kind = kind_of(&J.params);
     J.t = J.params.t0;
@@ -660,6 +675,7 @@ sl_status sl_batch_add(sl_batch* b, const sl_params* params, uint64_t sweeps, ui
     J.remaining = sweeps;
     J.cur = 0;
     b->jobs[j] = J;
+    b->list_most += most_workgroups(J.geom);
 
     // device job-table entry, written by the start kernel
     static_assert(sizeof(BatchJob) <= sizeof(StartBlob), "a job entry travels in the start kernel's arguments");
@@ -675,6 +691,7 @@ sl_status sl_batch_add(sl_batch* b, const sl_params* params, uint64_t sweeps, ui
         (void)hipStreamSynchronize(b->stream);
         b->heap.release(J.off, J.foot.total);
         give_up_second(b, b->jobs[j]);
+        b->list_most -= most_workgroups(J.geom);
         b->jobs[j] = JobHost();
         return hip_fail(e, "batch add");
     }
@@ -969,6 +986,7 @@ sl_status sl_batch_remove(sl_batch* b, uint32_t job_id)
     JobHost& J = b->jobs[job_id];
     b->heap.release(J.off, J.foot.total);
     give_up_second(b, J);
+    b->list_most -= most_workgroups(J.geom);
     J = JobHost();
     b->retry = true;
     return SL_OK;
