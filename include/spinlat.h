@@ -350,6 +350,13 @@ sl_status sl_batch_create(const sl_batch_config* cfg, void* device_arena, size_t
  * fits (e.g. L % 8 != 0); SL_E_OVERFLOW: t0 + sweeps would pass 2^32. */
 sl_status sl_batch_add(sl_batch* b, const sl_params* params, uint64_t sweeps, uint32_t* job_id);
 
+/* As sl_batch_add, for a caller that queues its jobs and wants them done soonest:
+ * SL_E_BUFFER also where the job, or one already there, would have to do without
+ * the second lattice copy of its tiles or walks, unless the batch is empty.  The
+ * job's second copy then belongs to it until it is removed, and later jobs of
+ * either call do not get that space. */
+sl_status sl_batch_add_keeping(sl_batch* b, const sl_params* params, uint64_t sweeps, uint32_t* job_id);
+
 /* Enqueue up to n sweeps of every job that has sweeps left and room in its
  * record ring; jobs stop individually.  Asynchronous: the per-call counters and
  * work lists go up from double-buffered pinned staging (the host waits only if

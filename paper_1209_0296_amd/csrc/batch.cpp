@@ -133,6 +133,7 @@ struct JobHost {
     // class in use; the one the footprint is for; the one to use while there is room
     RowGeomHost geom{}, least{}, want{};
     bool lent = false;            // copy 1 lies at off2, in a free range of the heap
+    bool kept = false;            // copy 1 lies at off2, in a block of its own
     size_t off2 = 0;
     uint32_t cur = 0;  // copy holding the current state (fused jobs alternate)
     uint64_t t = 0, remaining = 0, pending = 0, first_t = 0, done = 0;
@@ -236,7 +237,7 @@ Geom geom_of(const sl_params* p, uint64_t nh)
 
 uint8_t* col_of(const sl_batch* b, const JobHost& J, uint32_t copy, uint32_t colour)
 {
-    if (J.lent && copy == 1) return b->arena + J.off2 + colour * J.foot.col_bytes;
+    if ((J.lent || J.kept) && copy == 1) return b->arena + J.off2 + colour * J.foot.col_bytes;
     return b->arena + J.off + (2 * copy + colour) * J.foot.col_bytes;
 }
 
@@ -328,7 +329,8 @@ hipError_t write_entry(sl_batch* b, uint32_t j)
 void give_up_second(sl_batch* b, JobHost& J)
 {
     if (J.lent) b->lent.erase(J.off2 + 2 * J.foot.col_bytes);
-    J.lent = false;
+    if (J.kept) b->heap.release(J.off2, 2 * J.foot.col_bytes);
+    J.lent = J.kept = false;
 }
 
 // Job j goes on in its least class: the state moves to the first copy, a second one
@@ -336,7 +338,7 @@ void give_up_second(sl_batch* b, JobHost& J)
 hipError_t demote(sl_batch* b, uint32_t j)
 {
     JobHost& J = b->jobs[j];
-    const bool apart = J.lent;  // copy 1
+    const bool apart = J.lent || J.kept;  // copy 1
     if (apart && J.cur == 1) {
         const hipError_t e = hipMemcpyAsync(col_of(b, J, 0, 0), col_of(b, J, 1, 0), 2 * J.foot.col_bytes,
                                             hipMemcpyDeviceToDevice, b->stream);
@@ -553,6 +555,85 @@ sl_status graph_for(sl_batch* b, int k, uint64_t n, const uint32_t (&grid)[kBatc
     return SL_OK;
 }
 
+// sl_batch_add, or (keep) sl_batch_add_keeping.
+sl_status add_job(sl_batch* b, const sl_params* params, uint64_t sweeps, bool keep, uint32_t* job_id)
+{
+    if (!b) return fail(SL_E_INVALID, "NULL batch");
+    if (!job_id) return fail(SL_E_INVALID, "job_id is NULL");
+    JobHost J;
+    sl_status st = prepare_job(&b->cfg, params, &J.params, &J.foot, &J.want, &J.least, J.table, &J.table_n);
+    if (st != SL_OK) return st;
+    J.geom = J.want;
+    if (sweeps > (1ull << 32) - J.params.t0)  // validate() keeps t0 < 2^32
+        return fail(SL_E_OVERFLOW, "t0 + sweeps would pass 2^32");
+    uint32_t j = 0;
+    while (j < b->jobs.size() && b->jobs[j].used) ++j;
+    if (j == b->jobs.size()) return fail(SL_E_STATE, "job table full (%u jobs)", b->cfg.max_jobs);
+    if (!b->heap.alloc(J.foot.total, &J.off)) {
+        b->refused = true;
+        return fail(SL_E_BUFFER, "arena has no free block of %zu bytes for this job", J.foot.total);
+    }
+    const bool list_full = b->list_most + most_workgroups(J.want) > max_wg(&b->cfg);
+    if (list_full && most_workgroups(J.want) > most_workgroups(J.least)) J.geom = J.least;
+    if (keep) {
+        // with other jobs in the arena, only beside every copy that they and it want
+        const size_t second = 2 * J.foot.col_bytes;
+        const bool need = J.want.copies > J.least.copies;
+        const bool others = std::any_of(b->jobs.begin(), b->jobs.end(), [](const JobHost& o) { return o.used; });
+        bool room = !list_full && lent_in(b, J.off, J.foot.total).empty();
+        if (room && need) {
+            J.kept = b->heap.alloc(second, &J.off2);
+            room = J.kept && lent_in(b, J.off2, second).empty();
+        }
+        if (!room && others) {
+            if (J.kept) b->heap.release(J.off2, second);
+            b->heap.release(J.off, J.foot.total);
+            b->refused = true;
+            return fail(SL_E_BUFFER, "arena has no room for this job beside the jobs' second lattice copies");
+        }
+        if (need && !J.kept) J.geom = J.least;
+    }
+    hipError_t e = take_back(b, J.off, J.foot.total);
+    if (e == hipSuccess) e = make_list_room(b, most_workgroups(J.geom));
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(b->stream);
+        give_up_second(b, J);
+        b->heap.release(J.off, J.foot.total);
+        return hip_fail(e, "batch add");
+    }
+    if (!keep && J.geom.variant == J.want.variant && !lend_second(b, j, J)) J.geom = J.least;
+    J.used = true;
+    J.kind = kind_of(&J.params);
+    J.t = J.params.t0;
+    J.first_t = J.params.t0;
+    J.remaining = sweeps;
+    J.cur = 0;
+    b->jobs[j] = J;
+    b->list_most += most_workgroups(J.geom);
+
+    // device job-table entry, written by the start kernel
+    static_assert(sizeof(BatchJob) <= sizeof(StartBlob), "a job entry travels in the start kernel's arguments");
+    const BatchJob entry = job_entry(b, j);
+    SweepArgs a = job_args(b, j);
+    const uint64_t bern = thr_from_prob(J.params.c);
+    e = start_lattice(a, &J.params, J.kind, bern, ring_of(b, j), (uint64_t)b->cfg.record_capacity * kSlotWords,
+                      d_jobs(b) + j, &entry, sizeof(BatchJob), b->stream);
+    // record r_0: observables of the initial state
+    a.acc = ring_of(b, j);
+    if (e == hipSuccess) e = launch_observe(a, J.kind, b->stream);
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(b->stream);
+        b->heap.release(J.off, J.foot.total);
+        give_up_second(b, b->jobs[j]);
+        b->list_most -= most_workgroups(J.geom);
+        b->jobs[j] = JobHost();
+        return hip_fail(e, "batch add");
+    }
+    b->jobs[j].pending = 1;
+    *job_id = j;
+    return SL_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -643,61 +724,12 @@ sl_status sl_batch_create(const sl_batch_config* cfg, void* device_arena, size_t
 
 sl_status sl_batch_add(sl_batch* b, const sl_params* params, uint64_t sweeps, uint32_t* job_id)
 {
-    if (!b) return fail(SL_E_INVALID, "NULL batch");
-    if (!job_id) return fail(SL_E_INVALID, "job_id is NULL");
-    JobHost J;
-    sl_status st = prepare_job(&b->cfg, params, &J.params, &J.foot, &J.want, &J.least, J.table, &J.table_n);
-    if (st != SL_OK) return st;
-    J.geom = J.want;
-    if (sweeps > (1ull << 32) - J.params.t0)  // validate() keeps t0 < 2^32
-        return fail(SL_E_OVERFLOW, "t0 + sweeps would pass 2^32");
-    uint32_t j = 0;
-    while (j < b->jobs.size() && b->jobs[j].used) ++j;
-    if (j == b->jobs.size()) return fail(SL_E_STATE, "job table full (%u jobs)", b->cfg.max_jobs);
-    if (!b->heap.alloc(J.foot.total, &J.off)) {
-        b->refused = true;
-        return fail(SL_E_BUFFER, "arena has no free block of %zu bytes for this job", J.foot.total);
-    }
-    const bool list_full = b->list_most + most_workgroups(J.want) > max_wg(&b->cfg);
-    if (list_full && most_workgroups(J.want) > most_workgroups(J.least)) J.geom = J.least;
-    hipError_t e = take_back(b, J.off, J.foot.total);
-    if (e == hipSuccess) e = make_list_room(b, most_workgroups(J.geom));
-    if (e != hipSuccess) {
-        (void)hipStreamSynchronize(b->stream);
-        b->heap.release(J.off, J.foot.total);
-        return hip_fail(e, "batch add");
-    }
-    if (J.geom.variant == J.want.variant && !lend_second(b, j, J)) J.geom = J.least;
-    J.used = true;
-    J.kind = kind_of(&J.params);
-    J.t = J.params.t0;
-    J.first_t = J.params.t0;
-    J.remaining = sweeps;
-    J.cur = 0;
-    b->jobs[j] = J;
-    b->list_most += most_workgroups(J.geom);
+    return add_job(b, params, sweeps, false, job_id);
+}
 
-    // device job-table entry, written by the start kernel
-    static_assert(sizeof(BatchJob) <= sizeof(StartBlob), "a job entry travels in the start kernel's arguments");
-    const BatchJob entry = job_entry(b, j);
-    SweepArgs a = job_args(b, j);
-    const uint64_t bern = thr_from_prob(J.params.c);
-    e = start_lattice(a, &J.params, J.kind, bern, ring_of(b, j), (uint64_t)b->cfg.record_capacity * kSlotWords,
-                      d_jobs(b) + j, &entry, sizeof(BatchJob), b->stream);
-    // record r_0: observables of the initial state
-    a.acc = ring_of(b, j);
-    if (e == hipSuccess) e = launch_observe(a, J.kind, b->stream);
-    if (e != hipSuccess) {
-        (void)hipStreamSynchronize(b->stream);
-        b->heap.release(J.off, J.foot.total);
-        give_up_second(b, b->jobs[j]);
-        b->list_most -= most_workgroups(J.geom);
-        b->jobs[j] = JobHost();
-        return hip_fail(e, "batch add");
-    }
-    b->jobs[j].pending = 1;
-    *job_id = j;
-    return SL_OK;
+sl_status sl_batch_add_keeping(sl_batch* b, const sl_params* params, uint64_t sweeps, uint32_t* job_id)
+{
+    return add_job(b, params, sweeps, true, job_id);
 }
 
 sl_status sl_batch_sweep(sl_batch* b, uint64_t n)

@@ -35,6 +35,7 @@ EXPORTS = (
     "sl_batch_add", "sl_batch_sweep", "sl_batch_job_status", "sl_batch_measure",
     "sl_batch_copy_spins", "sl_batch_remove", "sl_batch_destroy", "sl_batch_drain",
     "sl_record_statistics", "sl_overlap", "sl_autocorrelation", "sl_sweep_static",
+    "sl_batch_add_keeping",
 )
 
 
@@ -123,6 +124,7 @@ def lib():
     L.sl_batch_create.argtypes = [BC, ctypes.c_void_p, sz, ctypes.c_void_p,
                                   ctypes.POINTER(ctypes.c_void_p)]
     L.sl_batch_add.argtypes = [B, P, ctypes.c_uint64, ctypes.POINTER(ctypes.c_uint32)]
+    L.sl_batch_add_keeping.argtypes = L.sl_batch_add.argtypes
     L.sl_batch_sweep.argtypes = [B, ctypes.c_uint64]
     u64p = ctypes.POINTER(ctypes.c_uint64)
     L.sl_batch_job_status.argtypes = [B, ctypes.c_uint32, u64p, u64p, u64p]
@@ -382,18 +384,21 @@ class Batch:
 
     ``add`` admits a job if its footprint fits the free arena space (returns
     None otherwise), ``sweep(n)`` runs up to n sweeps of every job with sweeps
-    left, ``measure(job)`` drains a job's records.
+    left, ``measure(job)`` drains a job's records.  With ``keep_copies`` a job also
+    waits for room for the second lattice copy that its fastest kernels need, and
+    takes none from the jobs that are there.
     """
 
     def __init__(self, arena_bytes: int, max_jobs: int = 1024, record_capacity: int = 256,
                  tile_rows: int = 0, device="cuda", stream=None, max_workgroups: int = 0,
-                 flags: int = 0):
+                 flags: int = 0, keep_copies: bool = False):
         import torch
 
         self._torch = torch
         self.device = torch.device(device)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
         self.cfg = batch_config(max_jobs, record_capacity, tile_rows, max_workgroups, flags)
+        self._add = lib().sl_batch_add_keeping if keep_copies else lib().sl_batch_add
         self.arena = torch.empty(int(arena_bytes), dtype=torch.uint8, device=self.device)
         self._init_refs = {}
         h = ctypes.c_void_p()
@@ -414,7 +419,7 @@ class Batch:
             ptr = t.data_ptr()
         cp = p.c_struct(ptr)
         jid = ctypes.c_uint32()
-        st = lib().sl_batch_add(self._h, ctypes.byref(cp), _count(sweeps), ctypes.byref(jid))
+        st = self._add(self._h, ctypes.byref(cp), _count(sweeps), ctypes.byref(jid))
         if st in (3, 5):  # SL_E_BUFFER: no arena room; SL_E_STATE: job table full
             return None
         _check(st)

@@ -44,3 +44,41 @@ def test_served_results_equal_alone_runs():
     # admission really was limited by the arena: some job waited in the queue
     waits = [outcomes[r.id].admitted - r.arrival for r in reqs]
     assert max(waits) > 0.0
+
+
+def test_a_server_job_waits_for_the_second_copies_of_the_others():
+    """Room for one lattice beside its second copy, but not for another lattice as
+    well: the server's next job waits, where sl_batch_add admits it by its footprint."""
+    p = S.Params(dim=3, L=72, T=4.6, seed=3)
+    cfg = S.batch_config(max_jobs=4, record_capacity=17)
+    arena = S.batch_base_bytes(cfg) + 2 * S.batch_job_bytes(p, cfg)
+    srv = Server(arena, max_jobs=4, chunk=16)
+    b = srv.batch
+    i = b.add(p, 9)
+    assert i is not None and b.add(p, 9) is None
+    b.sweep(4)
+    assert b.add(p, 9) is None
+    b.sweep(5)
+    o_s, o_r = run_oracle(p, 9)
+    np.testing.assert_array_equal(S.records_to_array(b.measure(i)), o_r)
+    np.testing.assert_array_equal(b.spins(i), o_s)
+    b.remove(i)
+    assert b.add(p, 9) is not None
+    srv.close()
+    plain = S.Batch(arena, max_jobs=4, record_capacity=17)
+    assert plain.add(p, 9) is not None and plain.add(p, 9) is not None
+    plain.close()
+
+
+def test_a_server_whose_arena_holds_one_copy_of_a_job_runs_it():
+    """An empty arena of exactly the footprint: the job runs in the class that needs
+    no second copy."""
+    p = S.Params(dim=3, L=72, T=4.6, seed=4)
+    cfg = S.batch_config(max_jobs=4, record_capacity=17)
+    srv = Server(S.batch_base_bytes(cfg) + S.batch_job_bytes(p, cfg), max_jobs=4, chunk=16)
+    reqs = [Request(i, 0.0, p, 20) for i in range(2)]
+    outcomes, _ = srv.run(reqs, realtime=False)
+    srv.close()
+    _, o_r = run_oracle(p, 20)
+    for r in reqs:
+        np.testing.assert_array_equal(outcomes[r.id].records, o_r)
