@@ -7,9 +7,9 @@ and model (its own seed and device buffer; the caller's lattice is never
 touched) with HIP events around `sweeps` sweeps after a warm-up, and returns
 the fastest together with the timings.  Candidates: the library's own choice
 (which alone runs several sweeps per launch on tiles, and 3D sweeps as walks
-along z), the resident mode, the direct kernel, the whole-row half and fused kernels over strip heights and
-words per lane, and the column-window kernels; shapes a schedule does not fit
-are skipped.
+along z), the resident mode, the direct kernel, the whole-row half and fused
+kernels over strip heights and words per lane, and the column-window kernels;
+shapes a schedule does not fit are skipped.
 
     best, table = autotune(Params(L=2048, T=2.269))
     lat = Lattice(params); lat.set_launch(*best)
