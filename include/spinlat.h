@@ -155,7 +155,7 @@ typedef enum sl_mode {
     SL_MODE_AUTO = 0,         /* library's choice for the shape; where that is faster it
                                  runs several sweeps per launch on tiles in LDS, or 3D
                                  sweeps as walks along z, instead of the schedule that
-                                 sl_get_launch names */
+                                 sl_get_launch names (reserved tells) */
     SL_MODE_SIMPLE = 1,       /* one thread per 4 same-colour sites, direct global loads,
                                  two launches per sweep */
     SL_MODE_HALF = 2,         /* row-group streaming, one colour in place per launch,
@@ -185,7 +185,11 @@ typedef struct sl_launch {
                             workgroup (0: default) */
     int32_t tile_words;  /* HALF/FUSED/HALF_ROWS: 4-byte words per lane, 1, 2 or 4 (0:
                             default); must be 0 for the window modes */
-    int32_t reserved;
+    int32_t reserved;    /* sl_get_launch: the sweeps per launch of the tiles (walks along
+                            z: 1) that the default runs instead of the schedule above, 0
+                            if it or a chosen schedule runs as named.  sl_set_launch: what
+                            sl_get_launch reported, not 0, restores that default; any
+                            other value is ignored */
 } sl_launch;
 
 /* Bytes of device memory the lattice needs (Alg. I steps 1-2: the lattice

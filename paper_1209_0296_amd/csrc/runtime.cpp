@@ -250,6 +250,20 @@ sl_launch auto_launch(const sl_lattice* h, TilePlan* tile, PlaneGeom* plane)
     return l;
 }
 
+// What sl_launch::reserved reports of a default (include/spinlat.h).
+int32_t plan_mark(const TilePlan& tile, const PlaneGeom& plane) { return tile.k ? (int32_t)tile.k : plane.L ? 1 : 0; }
+
+// Is l the default as sl_get_launch reports it while that runs tiles or walks?
+bool reported_default(const sl_lattice* h, const sl_launch& l)
+{
+    if (l.reserved == 0 || is_sub_lattice(h->params.model)) return false;
+    TilePlan tile;
+    PlaneGeom plane;
+    const sl_launch d = auto_launch(h, &tile, &plane);
+    return l.mode == d.mode && l.tile_rows == d.tile_rows && l.tile_words == d.tile_words &&
+           l.reserved == plan_mark(tile, plane);
+}
+
 // The resident schedule runs as one tile if the lattice and its table allow it.
 TilePlan resident_tile(const sl_lattice* h)
 {
@@ -604,6 +618,7 @@ sl_status sl_create_lattice(const sl_params* params, void* device_buf, size_t by
     h->cur = 0;
     h->table_n = build_table(params, h->table);
     h->launch = auto_launch(h, &h->tile, &h->plane);
+    h->chosen = true;
     h->stage = nullptr;
     hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&h->stage),
                                  params->record_capacity * sizeof(sl_record), hipHostMallocDefault);
@@ -640,12 +655,14 @@ sl_status sl_set_launch(sl_lattice* h, const sl_launch* launch)
     sl_launch l = *launch;
     TilePlan tile{};
     PlaneGeom plane{};
-    const bool chosen = l.mode == SL_MODE_AUTO && !is_sub_lattice(h->params.model);
+    const bool chosen = (l.mode == SL_MODE_AUTO && !is_sub_lattice(h->params.model)) || reported_default(h, l);
     if (chosen) l = auto_launch(h, &tile, &plane);
+    l.reserved = 0;
     sl_status st = check_launch(h, &l);
     if (st != SL_OK) return st;
     if (!chosen && l.mode == SL_MODE_RESIDENT) tile = resident_tile(h);
     h->launch = l;
+    h->chosen = chosen;
     h->tile = tile;
     h->plane = plane;
     return SL_OK;
@@ -655,6 +672,7 @@ sl_status sl_get_launch(const sl_lattice* h, sl_launch* launch)
 {
     if (!h || !launch) return fail(SL_E_INVALID, "NULL argument");
     *launch = h->launch;
+    launch->reserved = h->chosen ? plan_mark(h->tile, h->plane) : 0;
     return SL_OK;
 }
 

@@ -24,6 +24,7 @@ struct sl_lattice {
     uint64_t first_t;  // t of the oldest unread record
     int cur;           // copy of the lattice holding the current state
     sl_launch launch;
+    bool chosen;       // launch, tile and plane are the default's
     spinlat::TilePlan tile;  // k != 0: sweeps run as tile launches (the default schedule only)
     spinlat::PlaneGeom plane;  // L != 0: 3D sweeps run as walks along z (the default schedule only)
     uint64_t table[spinlat::kMaxLut];

@@ -215,6 +215,17 @@ RECORD_DTYPE = np.dtype([("t", np.uint64), ("bond_sum", np.int64), ("mag", np.in
                          ("accepted", np.int64), ("unflipped", np.int64)])
 
 
+class DefaultMode(int):
+    """Mode of the schedule that ``Lattice.get_launch`` names while the default runs
+    tiles or walks along z instead: ``sweeps_per_launch`` of those.  Set back, it
+    restores that default; the plain number chooses the schedule it names."""
+
+    def __new__(cls, mode: int, sweeps_per_launch: int):
+        self = super().__new__(cls, mode)
+        self.sweeps_per_launch = sweeps_per_launch
+        return self
+
+
 class Lattice:
     """One lattice resident in HBM, advanced by ``sweep`` and read by ``measure``.
 
@@ -249,12 +260,14 @@ class Lattice:
 
     # -- schedule -----------------------------------------------------------
     def set_launch(self, mode: int, tile_rows: int = 0, tile_words: int = 0) -> None:
-        _check(lib().sl_set_launch(self._h, ctypes.byref(CLaunch(mode, tile_rows, tile_words, 0))))
+        plan = getattr(mode, "sweeps_per_launch", 0)
+        _check(lib().sl_set_launch(self._h, ctypes.byref(CLaunch(mode, tile_rows, tile_words, plan))))
 
     def get_launch(self):
         l = CLaunch()
         _check(lib().sl_get_launch(self._h, ctypes.byref(l)))
-        return (l.mode, l.tile_rows, l.tile_words)
+        mode = DefaultMode(l.mode, l.reserved) if l.reserved else l.mode
+        return (mode, l.tile_rows, l.tile_words)
 
     # -- the hot path -------------------------------------------------------
     def sweep(self, n: int) -> None:

@@ -84,3 +84,29 @@ def test_tiles_between_other_schedules():
 def test_short_calls_between_tile_launches(L, kind):
     """Calls of one (or two) sweeps run on whole rows, longer ones on tiles."""
     _same(S.Params(L=L, seed=L + 5, record_capacity=16, **KINDS[kind]), [1, 3, 1, 2] if L < 4000 else [2, 3, 1])
+
+
+@pytest.mark.parametrize("kw,sweeps_per_launch", [
+    (dict(L=512, T=2.3), 12), (dict(dim=3, L=64, T=4.5), 3), (dict(dim=3, L=136, T=4.5), 1), (dict(L=64, T=2.3), 4096),
+    (dict(model=S.NORTH_EAST, L=1536, c=0.1), None)])
+def test_the_reported_schedule_set_back_changes_nothing(kw, sweeps_per_launch):
+    """set_launch(*get_launch()) keeps the tiles or walks that run beside the named
+    schedule; naming that schedule in plain numbers runs it."""
+    lat = S.Lattice(S.Params(seed=5, record_capacity=64, **kw))
+    first = lat.get_launch()
+    assert first[0].sweeps_per_launch == sweeps_per_launch or sweeps_per_launch is None
+    lat.set_launch(*first)
+    again = lat.get_launch()
+    assert again == first and again[0].sweeps_per_launch == first[0].sweeps_per_launch
+    lat.set_launch(*[int(v) for v in first])
+    named = lat.get_launch()
+    assert named == first and not hasattr(named[0], "sweeps_per_launch")
+    lat.set_launch(S.MODE_SIMPLE)
+    lat.set_launch(*first)
+    assert lat.get_launch()[0].sweeps_per_launch == first[0].sweeps_per_launch
+    lat.sweep(9)
+    got_r, got_s = S.records_to_array(lat.measure()), lat.spins()
+    lat.close()
+    ref_s, ref_r = run_oracle(S.Params(seed=5, **kw), 9)
+    np.testing.assert_array_equal(got_r, ref_r)
+    np.testing.assert_array_equal(got_s, ref_s)
