@@ -35,6 +35,7 @@
 #include "../../include/spinlat.h"
 #include "batch_internal.h"
 #include "host_common.h"
+#include "plane_plan.h"
 #include "spinlat_internal.h"
 
 using namespace spinlat;
@@ -474,14 +475,14 @@ sl_status prepare_job(const sl_batch_config* cfg, const sl_params* params, sl_pa
     *foot = job_foot(p, cfg->record_capacity, least->copies);
     // tiles and walks along z, unless the caller asked for a strip height or for
     // fewer workgroups than they take; nor rows that fill the waves of the other
-    // classes: 3D L = 256 (us per sweep of 8 jobs, rows against walks: spin-1/2 93.9 and
-    // 97.2, spin-1 135 and 161), and 2D walks in a batch that can fill the chip (64 jobs
+    // classes: 3D row groups, and 2D walks in a batch that can fill the chip (64 jobs
     // of L = 2048, 64 lanes, walks against tiles: spin-1/2 174 and 188, spin-1 246 and
     // 284, NE 186 and 195; of L = 1536, 48 lanes, 122 and 114; 8 jobs of L = 2048 32 and
     // 26)
     const bool fills = p->dim == 2 && p->L >= 1792 && least->variant == kBvWalkD4 &&
                        (uint64_t)cfg->max_jobs * nh > (1ull << 26);
-    if (fills || (p->dim == 3 && p->L == 256) || !(p->model == SL_NORTH_EAST || lut32) ||
+    const bool rows = least->variant == kBvRowsD4 && rows_beat_plane(g, kind_of(p), 8192);
+    if (fills || rows || !(p->model == SL_NORTH_EAST || lut32) ||
         !batch_tiled_geom(g, !(cfg->flags & SL_BATCH_NO_RESIDENT),
                           !(cfg->flags & SL_BATCH_NO_FUSED) && cfg->tile_rows == 0, *geom) ||
         (cfg->max_workgroups && most_workgroups(*geom) > most_workgroups(*least)))

@@ -138,9 +138,12 @@ bool lut32_ok(const sl_lattice* h)
 //   - 3D: half-sweeps by independent row groups with 4 words per lane (fewest
 //     waves; L = 128: 7.7 against 10.0 with 1), also when 4 does not divide the
 //     row (Ising rows may be ragged: L = 136: 8.7 against 13.0 with 1 word);
-//     blocks of 4 waves, spin-1/2 16 at L = 256, where two of them fill a CU
-//     (16.1 against 16.4 with 8 and 17.0 with 4), and 8 above (512: 81 against
-//     87 with 4 or 16); spin-1 at 256: 22.1 with 4, 22.3 with 8.
+//     blocks of 4 waves (spin-1 at 256: 22.1 against 22.2 with 8 and 24.8 with
+//     16), spin-1/2 from L = 256 of 8 (264: 22.0 against 23.1 with 4 and 23.8
+//     with 16; 512: 83 against 89 and 86), but of 16 where these are one round
+//     that nearly fills the chip, two to a CU (256, 512 blocks: 16.4 against
+//     16.8 with 8 and 17.4 with 4; 248, 481: 18.7, 18.9, 19.9; 240, 450: 18.4,
+//     18.8, 19.5; but 224, 349 blocks: 15.3, 14.0, 14.4).
 // Other widths are tried in order when a row does not fit, and
 // shapes the whole-row kernels cannot take fall back to the window kernels.
 constexpr uint64_t kResidentAuto = 16 * 1024;
@@ -165,7 +168,9 @@ sl_launch row_launch(const sl_lattice* h)
     sl_launch l{};
     if (h->params.dim == 3) {
         const int Ds[3] = {4, 2, 1};
-        const int waves = L >= 256 && half_spin ? (L == 256 ? 16 : 8) : 4;
+        const uint32_t lanes = ((uint32_t)L / 8 + 3) / 4, per = lanes <= 64 ? 64 / lanes : 1;
+        const uint32_t blocks = ((uint32_t)L * L / per + 15) / 16;  // of 16 waves with D = 4
+        const int waves = !half_spin ? 4 : blocks <= 512 && blocks > 448 ? 16 : L >= 256 ? 8 : 4;
         for (int D : Ds)
             if (rows_supported(g, h->kind, waves, D, lut32_ok(h))) {
                 l.mode = SL_MODE_HALF_ROWS;
@@ -226,11 +231,11 @@ sl_launch row_launch(const sl_lattice* h)
 // 41.9 and 51.5) unless North-East moves draw rarely (8192, c = 0.1: 48.0 and
 // 11.9).  3D lattices above L = 128, where a tile's
 // halo costs more than the launches, walk along z with both colours per launch
-// (plane_device.hpp; spin-1/2 L = 136: 9.8 against 6.8; 232: 19.6 and 14.8;
-// 264: 23.4 and 18.1; spin-1 200: 17.4 and 16.0), but not L = 256, whose rows
-// fill the row groups' waves (spin-1/2 16.1 against 16.9, spin-1 22.1 and
-// 24.8), nor from L = 512 (81 against 82).  Zero thresholds need the kernels
-// with 64-bit tables.
+// (plane_device.hpp; spin-1/2 L = 136: 10.5 against 6.9; 232: 18.3 and 14.8;
+// 264: 22.0 and 17.9; spin-1 200: 17.3 and 15.7), but not where the rows fill
+// the row groups' waves (rows_beat_plane), nor from L = 512, where neither is
+// the better one throughout (spin-1/2 520: 126 and 97, 576: 129 and 129, 640:
+// 165 and 174).  Zero thresholds need the kernels with 64-bit tables.
 sl_launch auto_launch(const sl_lattice* h, TilePlan* tile, PlaneGeom* plane)
 {
     *tile = TilePlan{};
@@ -241,7 +246,8 @@ sl_launch auto_launch(const sl_lattice* h, TilePlan* tile, PlaneGeom* plane)
     if ((ising || coupled) && !lut32_ok(h)) return l;
     const Geom g = args_of(h).g;
     if (h->params.dim == 3 && h->params.L > 128) {
-        if (h->params.L < 512 && h->params.L != 256 && !plane_plan(g, h->kind, *plane)) *plane = PlaneGeom{};
+        if (h->params.L < 512 && !rows_beat_plane(g, h->kind, 4096) && !plane_plan(g, h->kind, *plane))
+            *plane = PlaneGeom{};
         return l;
     }
     const bool sparse = h->params.model == SL_NORTH_EAST && h->table[1] >= (1ull << 32);
@@ -436,12 +442,17 @@ sl_status enqueue_sweeps(sl_lattice* h, uint64_t n)
     if (is_sub_lattice(h->params.model)) return sweep_ne_sub(h, n);
     SweepArgs a = args_of(h);
     // One sweep alone does not pay for a tile's halo where whole rows run it in one
-    // launch (us, rows against tiles: spin-1/2 L = 1536 16.6 and 17.5, 4096 26.1 and
-    // 34.0, 6144 45.8 and 55.8), nor do two of spin-1/2 around L = 4096 (41.4 and 43.6;
-    // 2048 24.7 and 21.0, 6144 81 and 78)
-    const int L = h->params.L;
-    const bool few = n == 1 || (n == 2 && h->kind == KIND_ISING_HALF && L >= 4096 && L < 6144);
-    const bool rows = few && !h->tile.bits && h->launch.mode == SL_MODE_FUSED && L >= 1536;
+    // launch (us a call among others, rows against tiles: spin-1/2 L = 1536 6.2 and 7.0,
+    // 4096 14.2 and 23.0, 6144 34 and 45), nor do two of spin-1/2 whose rows, two words
+    // a lane, are one round of waves of at least half the chip's 8192 (4096 28 and 32,
+    // 5120 47.0 and 47.5; not 3072, 2304 waves 22 and 21, nor 6144, 9216 waves 69 and
+    // 67, nor with one word a lane 4608 44 and 40, 5632 60 and 57)
+    bool rows = false;
+    if (n <= 2 && !h->tile.bits && h->launch.mode == SL_MODE_FUSED && h->params.L >= 1536) {
+        const uint32_t L = (uint32_t)h->params.L, words = (uint32_t)h->launch.tile_words;
+        const uint32_t waves = L / (uint32_t)h->launch.tile_rows * (L / 8 / words / 64);
+        rows = n == 1 || (h->kind == KIND_ISING_HALF && words >= 2 && waves >= 4096 && waves <= 8192);
+    }
     if (h->tile.k && !rows) {
         // equal launches of at most k sweeps
         const uint64_t launches = (n + h->tile.k - 1) / h->tile.k;

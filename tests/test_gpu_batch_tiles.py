@@ -149,3 +149,15 @@ def test_a_second_copy_is_lent_again_when_room_comes_free(p):
         np.testing.assert_array_equal(S.records_to_array(b.measure(j)), o_r)
         np.testing.assert_array_equal(b.spins(j), o_s)
     b.close()
+
+
+@pytest.mark.parametrize("p", [S.Params(dim=3, L=288, two_s=2, T=3.1, seed=3), S.Params(dim=3, L=288, T=4.5, seed=4)])
+def test_large_3d_jobs_on_row_groups_or_walks(p):
+    """Spin-1 rows of 63 of a wave's lanes keep the row groups, spin-1/2 ones walk."""
+    b = S.Batch(256 << 20, max_jobs=2, record_capacity=8)
+    i = b.add(p, sweeps=2)
+    b.sweep(2)
+    o_s, o_r = run_oracle(p, 2)
+    np.testing.assert_array_equal(S.records_to_array(b.measure(i)), o_r)
+    np.testing.assert_array_equal(b.spins(i), o_s)
+    b.close()

@@ -110,3 +110,17 @@ def test_the_reported_schedule_set_back_changes_nothing(kw, sweeps_per_launch):
     ref_s, ref_r = run_oracle(S.Params(seed=5, **kw), 9)
     np.testing.assert_array_equal(got_r, ref_r)
     np.testing.assert_array_equal(got_s, ref_s)
+
+
+@pytest.mark.parametrize("two_s,L,walks", [(1, 248, True), (1, 256, False), (1, 264, True), (1, 288, True),
+                                           (2, 160, True), (2, 192, True), (2, 224, False), (2, 248, True),
+                                           (2, 256, False), (2, 288, False), (2, 416, True)])
+def test_3d_lattices_whose_rows_fill_their_waves_keep_the_row_groups(two_s, L, walks):
+    """The choice follows the lanes of a wave that the rows fill and the waves of a
+    launch, on both sides of the line; whichever runs, the lattice is the same."""
+    sp = S.Params(dim=3, L=L, two_s=two_s, T=4.5 if two_s == 1 else 3.1, seed=L, record_capacity=8)
+    lat = S.Lattice(sp)
+    assert hasattr(lat.get_launch()[0], "sweeps_per_launch") == walks
+    lat.close()
+    if L in (224, 256, 288):
+        _same(sp, [2])
