@@ -161,3 +161,24 @@ def test_large_3d_jobs_on_row_groups_or_walks(p):
     np.testing.assert_array_equal(S.records_to_array(b.measure(i)), o_r)
     np.testing.assert_array_equal(b.spins(i), o_s)
     b.close()
+
+
+@pytest.mark.parametrize("flags", [0, S.BATCH_NO_FUSED, S.BATCH_NO_RESIDENT])
+def test_spin_one_jobs_with_zero_thresholds(flags):
+    """Tables with thresholds of zero keep the row classes: fused rows, walks (without
+    the fused class) and 3D row groups, of every width, beside ordinary jobs."""
+    jobs = [S.Params(dim=dim, L=L, two_s=2, T=0.2, h=0.05, seed=L) for dim, L in
+            ((2, 64), (2, 520), (2, 528), (2, 544), (2, 1000), (3, 32), (3, 56), (3, 72), (3, 64))]
+    jobs += [S.Params(L=264, two_s=2, T=1.7, seed=1), S.Params(dim=3, L=40, two_s=2, T=3.1, seed=2)]
+    assert 0 in S.threshold_table(jobs[0]) and 0 in S.threshold_table(jobs[5])
+    b = S.Batch(64 << 20, max_jobs=len(jobs), record_capacity=16, flags=flags)
+    ids = [b.add(p, sweeps=7) for p in jobs]
+    for n in (3, 4):
+        b.sweep(n)
+    got = b.drain()
+    for i, p in zip(ids, jobs):
+        print(f"case zero thresholds flags={flags} dim={p.dim} L={p.L} T={p.T}", flush=True)
+        o_s, o_r = run_oracle(p, 7)
+        np.testing.assert_array_equal(got[i], o_r)
+        np.testing.assert_array_equal(b.spins(i), o_s)
+    b.close()

@@ -124,3 +124,17 @@ def test_3d_lattices_whose_rows_fill_their_waves_keep_the_row_groups(two_s, L, w
     lat.close()
     if L in (224, 256, 288):
         _same(sp, [2])
+
+
+@pytest.mark.parametrize("two_s,L", [(1, 296), (1, 344), (1, 504), (2, 248), (2, 344), (2, 496)])
+def test_walks_along_z_with_two_words_a_thread(two_s, L):
+    """The larger walks hold two words of a plane per thread; ragged last columns in
+    both directions, up to the last size that walks."""
+    sp = S.Params(dim=3, L=L, two_s=two_s, T=4.5 if two_s == 1 else 3.1, h=0.1, seed=L, record_capacity=8)
+    _same(sp, [1, 1] if L < 400 else [1])
+
+
+@pytest.mark.parametrize("kw", [dict(T=2.269), dict(two_s=2, T=1.7)])
+def test_tiles_of_large_rows_that_fit_no_row_kernel(kw):
+    """2D L = 8200: a launch of four sweeps and one of one."""
+    _same(S.Params(L=8200, seed=3, record_capacity=8, **kw), [4, 1])
