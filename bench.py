@@ -67,21 +67,26 @@ def _profile_entry(workload):
     return entry
 
 
-def measured_traffic(workload):
-    """HBM bytes per launch (of several sweeps: a sweep's share) from the committed
-    FETCH_SIZE/WRITE_SIZE profile."""
+def _per_launch(entry, key, sweeps_per_launch):
+    """A profile's counter for a launch: profiles of launches of several sweeps hold a
+    sweep's share."""
+    return entry[key] * (sweeps_per_launch if entry.get("sweeps_per_dispatch", 1) > 1 else 1)
+
+
+def measured_traffic(workload, sweeps_per_launch=1):
+    """HBM bytes per launch from the committed FETCH_SIZE/WRITE_SIZE profile."""
     entry = _profile_entry(workload)
-    return entry["bytes_per_launch"] if entry else None
+    return _per_launch(entry, "bytes_per_launch", sweeps_per_launch) if entry else None
 
 
-def valu_fraction(workload, per_launch_s):
+def valu_fraction(workload, per_launch_s, sweeps_per_launch=1):
     """Issued VALU instructions per launch (SQ_INSTS_VALU of the committed
     profile) over what the chip issues in the measured launch time: 256 CUs x
     4 SIMDs, one wave64 instruction per SIMD every 4 cycles at 2.4 GHz."""
     entry = _profile_entry(workload)
     if not entry or "valu_insts_per_dispatch" not in entry:
         return None
-    insts = entry["valu_insts_per_dispatch"]
+    insts = _per_launch(entry, "valu_insts_per_dispatch", sweeps_per_launch)
     return {"insts_per_launch": insts, "peak_insts_per_s": VALU_WAVE_INSTS_PER_S,
             "frac": insts / (per_launch_s * VALU_WAVE_INSTS_PER_S)}
 
@@ -137,9 +142,12 @@ def time_workload(S, torch, name, cfg, steps, warmup, T=None, prewarm_s=0.0):
         # which between a call's launches is two bits a site
         launches_per_sweep = 2 if p.model == S.NE_SUBLATTICE else 4
         bytes_per_launch = p.nsites // 2
+    elif hasattr(mode[0], "sweeps_per_launch"):
+        # tiles (walks along z: one sweep) that run beside the named schedule: a launch
+        # reads and writes the lattice once
+        launches_per_sweep = -(-steps // mode[0].sweeps_per_launch) / steps
+        bytes_per_launch = ALGO_BYTES_PER_ATTEMPT * p.nsites
     else:
-        # by the schedule that get_launch names; the default runs several sweeps per
-        # launch where that is faster, and a "launch" is then a sweep's share of one
         launches_per_sweep = 1 if mode[0] == S.MODE_FUSED else 2
         bytes_per_launch = ALGO_BYTES_PER_ATTEMPT * p.nsites / launches_per_sweep
     per_launch_s = sweep_ms / 1e3 / (steps * launches_per_sweep)
@@ -148,7 +156,8 @@ def time_workload(S, torch, name, cfg, steps, warmup, T=None, prewarm_s=0.0):
         "workload": name, "attempts_per_s": attempts / wall, "wall_s": wall,
         "ms_per_step": wall * 1e3 / steps, "sweep_kernels_ms_per_step": sweep_ms / steps,
         "launch": {"mode": mode[0], "tile_rows": mode[1], "tile_words": mode[2],
-                   "launches_per_sweep": launches_per_sweep},
+                   "launches_per_sweep": launches_per_sweep,
+                   "sweeps_per_launch": 1.0 / launches_per_sweep},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None,
                      "per_launch_us": per_launch_s * 1e6, "algo_bytes_per_launch": bytes_per_launch},
@@ -362,14 +371,15 @@ def main():
             print(f"# {key}: {r['attempts_per_s']:.4g} attempts/s, {r['ms_per_step']:.4f} ms/sweep",
                   file=sys.stderr, flush=True)
             per_launch_s = r["roofline"]["per_launch_us"] * 1e-6
+            sweeps = r["launch"]["sweeps_per_launch"]
             secondary.append({k: r[k] for k in ("workload", "attempts_per_s", "ms_per_step",
                                                  "sweep_kernels_ms_per_step", "launch")}
                              | {"roofline_frac": r["roofline"]["frac"],
                                 "per_launch_us": r["roofline"]["per_launch_us"],
                                 "algo_bytes_per_launch": r["roofline"]["algo_bytes_per_launch"],
                                 # committed counters, while the kernel sources match them
-                                "traffic": measured_traffic(key),
-                                "valu": valu_fraction(key, per_launch_s)})
+                                "traffic": measured_traffic(key, sweeps),
+                                "valu": valu_fraction(key, per_launch_s, sweeps)})
     # the served and CPU-baseline sections report an exception in the line
     # instead of losing the headline measurement taken above
     served_res = None
