@@ -303,7 +303,8 @@ sl_status sl_record_observables(const sl_params* params, const sl_record* record
  * tile holds the lattice, a whole call in one launch, while the arena has room
  * to spare for a second copy of the lattice and tile_rows is 0 (admission does
  * not depend on it; a job whose second copy a new one takes goes back to its
- * tiles or walks when room comes free); else, or with the flags:
+ * tiles or walks when room comes free).  Calls of few sweeps run large 2D jobs on
+ * rows where that is faster.  Else, or with the flags:
  *   - resident: both colours fit 48 KiB; one workgroup per job runs the
  *     call's sweeps in LDS, in one launch per call for all such jobs, on a
  *     stream of the library's own that overlaps the other launches;
@@ -313,11 +314,11 @@ sl_status sl_record_observables(const sl_params* params, const sl_record* record
  *   - 3D jobs that fit one wave likewise: half-sweeps by row groups;
  *   - the rest: half-sweep column windows (coupled NE jobs must fit a row
  *     class or LDS, SL_E_UNSUPPORTED otherwise).
- * The non-resident jobs of a call share launches by kernel family: one per
- * sweep for the fused jobs, one per colour for the row groups and for the
- * other half-sweep classes.  They are captured once per shape into HIP graphs
- * and replayed; the row-group family runs on another stream of the library's
- * own, beside the other families.  Every stream the library uses is joined
+ * The non-resident jobs of a call share launches by kernel family: one per four
+ * sweeps for the tiles, one per sweep for the walks along z and the fused jobs, one
+ * per colour for the row groups and for the other half-sweep classes.  They are
+ * captured once per shape into HIP graphs and replayed; the 3D families run on
+ * another stream of the library's own, beside the others.  Every stream the library uses is joined
  * back into the caller's stream within each sl_batch_sweep call.
  * ------------------------------------------------------------------------- */
 typedef struct sl_batch sl_batch;

@@ -144,21 +144,10 @@ struct JobHost {
 
 bool resident_job(const JobHost& J) { return J.geom.variant == kBvResident || J.geom.variant == kBvWhole; }
 
-// Launches that `sweeps` sweeps of a job with two copies take: each leaves the
-// state in the other copy.
-uint64_t copy_flips(const JobHost& J, uint64_t sweeps)
+// Kernel kind of a job's class: the model kind, with coupled NE jobs apart.
+int class_kind(const JobHost& J)
 {
-    if (J.geom.variant == kBvTile) return family_launches(4, sweeps);
-    return J.geom.copies == 2 ? sweeps : 0;
-}
-
-// Planes of a column of the walks along z, for a call whose jobs have `planes`
-// planes of columns in all: about 768 workgroups (three per CU), 4 to 32 planes
-// (a column recomputes two colour-0 planes).
-uint32_t plane_depth(uint64_t planes)
-{
-    const uint64_t d = (planes + 767) / 768;
-    return (uint32_t)(d < 4 ? 4 : d > 32 ? 32 : d);
+    return J.params.model == SL_NE_COUPLED ? kBatchKindNeCoupled : J.kind;
 }
 
 // Workgroups of a job in a call, at most.
@@ -169,10 +158,51 @@ uint64_t most_workgroups(const RowGeomHost& g)
     return (g.nitems + per - 1) / per;
 }
 
-// Kernel kind of a job's class: the model kind, with coupled NE jobs apart.
-int class_kind(const JobHost& J)
+// Launches that `sweeps` sweeps in class g take if each leaves the state in the
+// other of two copies.
+uint64_t copy_flips(const RowGeomHost& g, uint64_t sweeps)
 {
-    return J.params.model == SL_NE_COUPLED ? kBatchKindNeCoupled : J.kind;
+    if (g.variant == kBvTile) return family_launches(4, sweeps);
+    return g.copies == 2 ? sweeps : 0;
+}
+
+// Classes of whole 2D rows.
+bool row_class(uint32_t variant)
+{
+    return variant <= kBvWalkD1 || (variant >= kBvFusedD4 && variant <= kBvFusedD1);
+}
+
+// Can a job on tiles run a call in its row class, at no more workgroups?
+bool has_rows(const JobHost& J)
+{
+    return J.geom.variant == kBvTile && row_class(J.least.variant) &&
+           most_workgroups(J.least) <= most_workgroups(J.geom);
+}
+
+// Does a job on tiles run a call of n sweeps on its rows, when such jobs have
+// `sites` sites in all?  A tile's halo and start are paid per launch of up to four
+// sweeps, so where the chip is full, rows are faster for few sweeps, and for spin-1/2
+// whenever the last launch has fewer (us a call, rows against tiles: 16 jobs of L = 1024,
+// 2^24 sites: spin-1/2 n = 1 40 and 45, 2 54 and 53; of L = 1536 1 59 and 84, 2 94 and 102, 3
+// 132 and 125; 64 of L = 1024: spin-1/2 1 85 and 117, 2 132 and 148, 3 179 and 189, 5 275 and
+// 308, 64 3172 and 3086; spin-1 1 116 and 137, 2 198 and 197, 3 279 and 266; North-East 1 93
+// and 122, 2 152 and 158, 3 211 and 201).
+bool runs_on_rows(const JobHost& J, uint64_t n, uint64_t sites)
+{
+    const bool half = class_kind(J) == KIND_ISING_HALF;
+    if (n == 1) return sites >= (1ull << 24);
+    if (class_kind(J) == KIND_ISING_ONE) return false;
+    if (n == 2) return sites >= (half ? 1ull << 25 : 1ull << 26);
+    return half && n % kBatchTileSweeps != 0 && n < 32 && sites >= (1ull << 26);
+}
+
+// Planes of a column of the walks along z, for a call whose jobs have `planes`
+// planes of columns in all: about 768 workgroups (three per CU), 4 to 32 planes
+// (a column recomputes two colour-0 planes).
+uint32_t plane_depth(uint64_t planes)
+{
+    const uint64_t d = (planes + 767) / 768;
+    return (uint32_t)(d < 4 ? 4 : d > 32 ? 32 : d);
 }
 
 struct Lent {
@@ -278,6 +308,8 @@ BatchJob job_entry(const sl_batch* b, uint32_t j)
     entry.dim = (uint32_t)J.params.dim;
     entry.table_n = (uint32_t)J.table_n;
     std::memcpy(entry.rg_words, J.geom.bytes, sizeof(entry.rg_words));
+    std::memcpy(entry.row_words, J.least.bytes, sizeof(entry.row_words));
+    entry.row_cls = batch_class(class_kind(J), J.params.dim, J.least.variant);
     std::memcpy(entry.table, J.table, J.table_n * sizeof(uint64_t));
     return entry;
 }
@@ -772,16 +804,22 @@ sl_status sl_batch_sweep(sl_batch* b, uint64_t n)
     uint32_t count[kBatchFamilies] = {}, offset[kBatchFamilies] = {};
     std::vector<std::pair<uint64_t, uint32_t>> order;  // {family, weight, class; job}
     order.reserve(top);
+    uint64_t sites = 0;  // of the jobs that could run on rows instead of tiles
+    for (uint32_t j = 0; j < top; ++j)
+        if (budget[j] && has_rows(b->jobs[j])) sites += 2 * b->jobs[j].foot.nh;
+    std::vector<bool> on_rows(top, false);
     for (uint32_t j = 0; j < top; ++j) {
         const JobHost& J = b->jobs[j];
         if (!J.used || !budget[j] || resident_job(J)) continue;
+        on_rows[j] = has_rows(J) && runs_on_rows(J, budget[j], sites);
+        const RowGeomHost& g = on_rows[j] ? J.least : J.geom;
         const uint32_t kind = (uint32_t)class_kind(J);
         // tiles and columns: the heaviest workgroups first
-        const bool tiled = J.geom.variant == kBvTile || J.geom.variant == kBvPlane;
-        const uint64_t weight = tiled ? J.geom.words * (kind == (uint32_t)KIND_ISING_ONE ? 2 : 1) : 0;
-        order.emplace_back(((uint64_t)batch_family(J.geom.variant, kind) << 48) + ((0xFFFFFFull - weight) << 16) +
-                               batch_class((int)kind, J.params.dim, J.geom.variant), j);
-        if (J.geom.variant == kBvPlane) planes += J.geom.nitems;
+        const bool tiled = g.variant == kBvTile || g.variant == kBvPlane;
+        const uint64_t weight = tiled ? g.words * (kind == (uint32_t)KIND_ISING_ONE ? 2 : 1) : 0;
+        order.emplace_back(((uint64_t)batch_family(g.variant, kind) << 48) + ((0xFFFFFFull - weight) << 16) +
+                               batch_class((int)kind, J.params.dim, g.variant), j);
+        if (g.variant == kBvPlane) planes += g.nitems;
     }
     std::sort(order.begin(), order.end());
     const uint32_t depth = plane_depth(planes);
@@ -792,10 +830,11 @@ sl_status sl_batch_sweep(sl_batch* b, uint64_t n)
             const uint32_t j = order[at].second;
             const JobHost& J = b->jobs[j];
             const uint32_t L = (uint32_t)J.params.L, nz = (L + depth - 1) / depth, hz = (L + nz - 1) / nz;
-            const bool walk = J.geom.variant == kBvPlane;
-            const uint32_t per = walk ? hz : J.geom.items_per_wg;
-            const uint32_t nty = walk ? J.geom.nitems / L : 0;
-            const uint32_t kwg = walk ? nty * ((L + hz - 1) / hz) : (J.geom.nitems + per - 1) / per;
+            const RowGeomHost& g = on_rows[j] ? J.least : J.geom;
+            const bool walk = g.variant == kBvPlane;
+            const uint32_t per = walk ? hz : g.items_per_wg, job = on_rows[j] ? j | kOnRows : j;
+            const uint32_t nty = walk ? g.nitems / L : 0;
+            const uint32_t kwg = walk ? nty * ((L + hz - 1) / hz) : (g.nitems + per - 1) / per;
             if (nwg + kwg > max_wg(&b->cfg))
                 return fail(SL_E_STATE, "work list full (%llu workgroups); raise max_workgroups",
                             (unsigned long long)max_wg(&b->cfg));
@@ -804,7 +843,7 @@ sl_status sl_batch_sweep(sl_batch* b, uint64_t n)
                     for (uint32_t ty = 0; ty < nty; ++ty)
                         h_wgs[nwg++] = BatchWG{j, ty + (z0 << 8) + (std::min(hz, L - z0) << 20)};
             } else {
-                for (uint32_t w = 0; w < kwg; ++w) h_wgs[nwg++] = BatchWG{j, w * per};
+                for (uint32_t w = 0; w < kwg; ++w) h_wgs[nwg++] = BatchWG{job, w * per};
             }
         }
         count[fam] = (uint32_t)nwg - offset[fam];
@@ -909,7 +948,7 @@ sl_status sl_batch_sweep(sl_batch* b, uint64_t n)
         J.pending += budget[j];
         J.remaining -= budget[j];
         J.done += budget[j];
-        J.cur ^= (uint32_t)(copy_flips(J, budget[j]) & 1u);
+        J.cur ^= (uint32_t)(copy_flips(on_rows[j] ? J.least : J.geom, budget[j]) & 1u);
     }
     return SL_OK;
 }

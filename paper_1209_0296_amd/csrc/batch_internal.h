@@ -29,11 +29,15 @@ struct BatchJob {
     uint32_t copies;           // 1, or 2 for fused jobs
     uint32_t dim, table_n;
     uint32_t rg_words[24];     // geometry of the job's kernel (RowGeom, StreamGeom, TileGeom, PlaneGeom)
+    uint32_t row_words[15];    // RowGeom of a job on tiles, for its calls on rows
+    uint32_t row_cls;          // as cls, for those
     uint64_t table[kTableMax]; // threshold table (NE: up, down)
 };
 
+constexpr uint32_t kOnRows = 0x80000000u;  // of BatchWG::job: the job's rows in this call
+
 struct BatchWG {
-    uint32_t job;        // index into the job table
+    uint32_t job;        // index into the job table, with kOnRows
     uint32_t item_base;  // first item (strip, plane or row set) of this workgroup, its tile,
                          // or its column: y tile + (first plane << 8) + (planes << 20)
 };

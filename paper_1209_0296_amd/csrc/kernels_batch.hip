@@ -48,11 +48,12 @@ using namespace rowk;
 
 namespace {
 
-__device__ __forceinline__ SweepArgs job_sweep_args(const BatchJob& J, const uint32_t* dj, uint32_t colour,
-                                                    uint32_t step)
+// copy: the lattice copy with the state (only jobs with two leave copy 0).
+__device__ __forceinline__ SweepArgs job_sweep_args(const BatchJob& J, const uint32_t* dj, uint32_t copy,
+                                                    uint32_t colour, uint32_t step)
 {
     SweepArgs a{};
-    const bool second = J.copies == 2 && ((dj[3] + step) & 1u);
+    const bool second = (copy & 1u) != 0;
     a.col[0] = second ? J.col[1][0] : J.col[0][0];
     a.col[1] = second ? J.col[1][1] : J.col[0][1];
     a.key0 = J.key0;
@@ -63,14 +64,14 @@ __device__ __forceinline__ SweepArgs job_sweep_args(const BatchJob& J, const uin
 }
 
 template <int KIND, int DIM, int D>
-__device__ __forceinline__ void batch_walk_body(const BatchJob& J, const uint32_t* dj, const BatchWG w, uint32_t colour,
+__device__ __forceinline__ void batch_walk_body(const BatchJob& J, const uint32_t* geom, const uint32_t* dj, const BatchWG w, uint32_t colour,
                                                 uint32_t step, RowLuts& lut, uint32_t (&xch)[2][16][2])
 {
     uint64_t thr_up, thr_down;
     build_row_luts<KIND, DIM>(lut, J.table, thr_up, thr_down);
     __syncthreads();
-    const SweepArgs a = job_sweep_args(J, dj, colour, step);
-    const RowGeom rg = *reinterpret_cast<const RowGeom*>(J.rg_words);
+    const SweepArgs a = job_sweep_args(J, dj, dj[3], colour, step);
+    const RowGeom rg = *reinterpret_cast<const RowGeom*>(geom);
     Obs o = {};
     const Lanes ln = lanes_of(rg, false);
     const uint32_t item = ln.slot < rg.slots ? w.item_base + ln.wave * rg.slots + ln.slot : 0xFFFFFFFFu;
@@ -85,11 +86,11 @@ __device__ __forceinline__ void batch_walk_body(const BatchJob& J, const uint32_
 }
 
 template <int KIND, int DIM, int D>
-__device__ __forceinline__ void batch_rows_body(const BatchJob& J, const uint32_t* dj, const BatchWG w, uint32_t colour,
+__device__ __forceinline__ void batch_rows_body(const BatchJob& J, const uint32_t* geom, const uint32_t* dj, const BatchWG w, uint32_t colour,
                                                 uint32_t step, RowLuts& lut, LanePart& part)
 {
-    const SweepArgs a = job_sweep_args(J, dj, colour, step);
-    const RowGeom rg = *reinterpret_cast<const RowGeom*>(J.rg_words);
+    const SweepArgs a = job_sweep_args(J, dj, dj[3], colour, step);
+    const RowGeom rg = *reinterpret_cast<const RowGeom*>(geom);
     Obs o = {};
     const Lanes ln = lanes_of(rg, false);
     rows_run<KIND, DIM, D, kRagNone>(a, rg, w.item_base + ln.wave * rg.K, ln, J.table, lut, part, o);
@@ -101,17 +102,17 @@ __device__ __forceinline__ void batch_rows_body(const BatchJob& J, const uint32_
 // 2D jobs with two copies: the whole sweep, reading copy cur and writing the
 // other.
 template <int KIND, int D>
-__device__ __forceinline__ void batch_fused_body(const BatchJob& J, const uint32_t* dj, const BatchWG w, uint32_t step,
+__device__ __forceinline__ void batch_fused_body(const BatchJob& J, const uint32_t* geom, const uint32_t* dj, const BatchWG w, uint32_t step,
                                                  RowLuts& lut, uint32_t (&xch)[2][16][4])
 {
     uint64_t thr_up, thr_down;
     build_row_luts<KIND, 2>(lut, J.table, thr_up, thr_down);
     __syncthreads();
-    const SweepArgs a = job_sweep_args(J, dj, 0u, step);  // the current copy
+    const SweepArgs a = job_sweep_args(J, dj, dj[3] + step, 0u, step);  // the current copy
     const bool second = (dj[3] + step) & 1u;
     uint8_t* const N0 = second ? J.col[0][0] : J.col[1][0];  // the other copy
     uint8_t* const N1 = second ? J.col[0][1] : J.col[1][1];
-    const RowGeom rg = *reinterpret_cast<const RowGeom*>(J.rg_words);
+    const RowGeom rg = *reinterpret_cast<const RowGeom*>(geom);
     Obs o = {};
     const Lanes ln = lanes_of(rg, false);
     const uint32_t item = ln.slot < rg.slots ? w.item_base + ln.wave * rg.slots + ln.slot : 0xFFFFFFFFu;
@@ -129,14 +130,14 @@ __device__ __forceinline__ void batch_fused_body(const BatchJob& J, const uint32
 }
 
 template <int KIND, int DIM>
-__device__ __forceinline__ void batch_window_body(const BatchJob& J, const uint32_t* dj, const BatchWG w,
+__device__ __forceinline__ void batch_window_body(const BatchJob& J, const uint32_t* geom, const uint32_t* dj, const BatchWG w,
                                                   uint32_t colour, uint32_t step, streamk::Luts& lut)
 {
     uint64_t thr_up, thr_down;
     streamk::build_luts<KIND, DIM>(lut, J.table, thr_up, thr_down);
     __syncthreads();
-    const SweepArgs a = job_sweep_args(J, dj, colour, step);
-    const streamk::StreamGeom sg = *reinterpret_cast<const streamk::StreamGeom*>(J.rg_words);
+    const SweepArgs a = job_sweep_args(J, dj, dj[3], colour, step);
+    const streamk::StreamGeom sg = *reinterpret_cast<const streamk::StreamGeom*>(geom);
     streamk::Obs o = {0, 0, 0, 0};
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t item = w.item_base + (threadIdx.x >> 6) * sg.G + lane / sg.W;
@@ -159,24 +160,24 @@ union BatchLds {
 constexpr int kFamHalf = 0, kFamRows = 1, kFamFused = 2, kFamRowsOne = 3;
 
 template <int FAM, int KIND, int DIM>
-__device__ __forceinline__ void dispatch(uint32_t v, const BatchJob& J, const uint32_t* dj, const BatchWG w,
-                                         uint32_t colour, uint32_t step, BatchLds& lds, uint32_t (&xch)[2][16][4])
+__device__ __forceinline__ void dispatch(uint32_t v, const BatchJob& J, const uint32_t* geom, const uint32_t* dj,
+                                         const BatchWG w, uint32_t colour, uint32_t step, BatchLds& lds, uint32_t (&xch)[2][16][4])
 {
     if constexpr (FAM == kFamHalf) {
         uint32_t(&xch2)[2][16][2] = *reinterpret_cast<uint32_t(*)[2][16][2]>(&xch);
-        if (v == kBvWalkD4) batch_walk_body<KIND, DIM, 4>(J, dj, w, colour, step, lds.row, xch2);
-        else if (v == kBvWalkD2) batch_walk_body<KIND, DIM, 2>(J, dj, w, colour, step, lds.row, xch2);
-        else if (v == kBvWalkD1) batch_walk_body<KIND, DIM, 1>(J, dj, w, colour, step, lds.row, xch2);
+        if (v == kBvWalkD4) batch_walk_body<KIND, DIM, 4>(J, geom, dj, w, colour, step, lds.row, xch2);
+        else if (v == kBvWalkD2) batch_walk_body<KIND, DIM, 2>(J, geom, dj, w, colour, step, lds.row, xch2);
+        else if (v == kBvWalkD1) batch_walk_body<KIND, DIM, 1>(J, geom, dj, w, colour, step, lds.row, xch2);
         else if constexpr (KIND != KIND_NE_COUPLED) {
-            if (v == kBvWindow) batch_window_body<KIND, DIM>(J, dj, w, colour, step, lds.win);
+            if (v == kBvWindow) batch_window_body<KIND, DIM>(J, geom, dj, w, colour, step, lds.win);
         }
     } else if constexpr (FAM == kFamRows || FAM == kFamRowsOne) {
-        if (v == kBvRowsD4) batch_rows_body<KIND, DIM, 4>(J, dj, w, colour, step, lds.rows.lut, lds.rows.part);
-        else if (v == kBvRowsD2) batch_rows_body<KIND, DIM, 2>(J, dj, w, colour, step, lds.rows.lut, lds.rows.part);
-        else if (v == kBvRowsD1) batch_rows_body<KIND, DIM, 1>(J, dj, w, colour, step, lds.rows.lut, lds.rows.part);
+        if (v == kBvRowsD4) batch_rows_body<KIND, DIM, 4>(J, geom, dj, w, colour, step, lds.rows.lut, lds.rows.part);
+        else if (v == kBvRowsD2) batch_rows_body<KIND, DIM, 2>(J, geom, dj, w, colour, step, lds.rows.lut, lds.rows.part);
+        else if (v == kBvRowsD1) batch_rows_body<KIND, DIM, 1>(J, geom, dj, w, colour, step, lds.rows.lut, lds.rows.part);
     } else if constexpr (DIM == 2) {
-        if (v == kBvFusedD2) batch_fused_body<KIND, 2>(J, dj, w, step, lds.row, xch);
-        else if (v == kBvFusedD1) batch_fused_body<KIND, 1>(J, dj, w, step, lds.row, xch);
+        if (v == kBvFusedD2) batch_fused_body<KIND, 2>(J, geom, dj, w, step, lds.row, xch);
+        else if (v == kBvFusedD1) batch_fused_body<KIND, 1>(J, geom, dj, w, step, lds.row, xch);
     }
 }
 
@@ -196,25 +197,29 @@ __global__ void __launch_bounds__(256, FAM == kFamHalf ? 5 : 1) k_batch_family(c
     __shared__ uint32_t xch[2][16][4];
     if (blockIdx.x >= meta[2 * FAM]) return;  // whole workgroup
     const BatchWG w = wgs[meta[2 * FAM + 1] + blockIdx.x];
-    const uint32_t* dj = dyn + kDynWords * w.job;
+    const uint32_t job = w.job & ~kOnRows;
+    const uint32_t* dj = dyn + kDynWords * job;
     if (step >= dj[2]) return;  // whole workgroup: no sweep left for this job in this call
-    const BatchJob& J = jobs[w.job];
-    const uint32_t kind = J.cls >> 5, dim3d = (J.cls >> 4) & 1u, v = J.cls & 15u;
+    const BatchJob& J = jobs[job];
+    const bool on_rows = (w.job & kOnRows) != 0;
+    const uint32_t cls = on_rows ? J.row_cls : J.cls;
+    const uint32_t* geom = on_rows ? J.row_words : J.rg_words;
+    const uint32_t kind = cls >> 5, dim3d = (cls >> 4) & 1u, v = cls & 15u;
     if constexpr (FAM == kFamRowsOne) {
         // row groups of spin-1 jobs only (the row class is 3D)
-        dispatch<FAM, KIND_ISING_ONE, 3>(v, J, dj, w, colour, step, lds, xch);
+        dispatch<FAM, KIND_ISING_ONE, 3>(v, J, geom, dj, w, colour, step, lds, xch);
     } else if (kind == KIND_ISING_HALF) {
-        if (dim3d) dispatch<FAM, KIND_ISING_HALF, 3>(v, J, dj, w, colour, step, lds, xch);
-        else dispatch<FAM, KIND_ISING_HALF, 2>(v, J, dj, w, colour, step, lds, xch);
+        if (dim3d) dispatch<FAM, KIND_ISING_HALF, 3>(v, J, geom, dj, w, colour, step, lds, xch);
+        else dispatch<FAM, KIND_ISING_HALF, 2>(v, J, geom, dj, w, colour, step, lds, xch);
     } else if (kind == KIND_ISING_ONE) {
         if constexpr (FAM != kFamRows) {  // spin-1 row groups are family kFamRowsOne
-            if (dim3d) dispatch<FAM, KIND_ISING_ONE, 3>(v, J, dj, w, colour, step, lds, xch);
-            else dispatch<FAM, KIND_ISING_ONE, 2>(v, J, dj, w, colour, step, lds, xch);
+            if (dim3d) dispatch<FAM, KIND_ISING_ONE, 3>(v, J, geom, dj, w, colour, step, lds, xch);
+            else dispatch<FAM, KIND_ISING_ONE, 2>(v, J, geom, dj, w, colour, step, lds, xch);
         }
     } else if (kind == KIND_NE) {
-        dispatch<FAM, KIND_NE, 2>(v, J, dj, w, colour, step, lds, xch);
+        dispatch<FAM, KIND_NE, 2>(v, J, geom, dj, w, colour, step, lds, xch);
     } else {
-        dispatch<FAM, KIND_NE_COUPLED, 2>(v, J, dj, w, colour, step, lds, xch);
+        dispatch<FAM, KIND_NE_COUPLED, 2>(v, J, geom, dj, w, colour, step, lds, xch);
     }
 }
 
@@ -230,7 +235,7 @@ __global__ void __launch_bounds__(simplek::kResidentBlock) k_batch_resident(cons
     const uint32_t n = dj[2];
     if (n == 0) return;
     const BatchJob& J = jobs[j];
-    SweepArgs a = job_sweep_args(J, dj, 0u, 0u);
+    SweepArgs a = job_sweep_args(J, dj, 0u, 0u, 0u);
     const RowGeom rg = *reinterpret_cast<const RowGeom*>(J.rg_words);
     a.g.L = rg.L;
     a.g.Lh = rg.Lh;
@@ -267,6 +272,7 @@ __global__ void __launch_bounds__(256) k_batch_fold(const BatchFold* __restrict_
 bool batch_geom(const Geom& g, int H, bool lut32_ok, bool allow_fused, RowGeomHost& out)
 {
     out = RowGeomHost{};
+    static_assert(sizeof(RowGeom) == sizeof(BatchJob::row_words), "RowGeom storage");
     static_assert(sizeof(RowGeom) <= sizeof(out.bytes), "RowGeom storage");
     static_assert(sizeof(streamk::StreamGeom) <= sizeof(out.bytes), "StreamGeom storage");
     if (lut32_ok) {

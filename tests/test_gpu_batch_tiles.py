@@ -182,3 +182,31 @@ def test_spin_one_jobs_with_zero_thresholds(flags):
         np.testing.assert_array_equal(got[i], o_r)
         np.testing.assert_array_equal(b.spins(i), o_s)
     b.close()
+
+
+@pytest.mark.parametrize("flags", [0, S.BATCH_NO_GRAPH])
+def test_short_calls_of_large_batches_run_on_rows(flags):
+    """Calls of few sweeps over enough sites leave the tiles for the row classes (fused
+    rows and, of one copy, walks), in place in whichever copy holds the state, and
+    longer calls take the tiles again."""
+    jobs = [S.Params(L=2048, T=2.3, seed=i) for i in range(8)] + [S.Params(L=1536, T=2.1, h=0.1, seed=20)]
+    jobs += [S.Params(L=1024, T=2.3, seed=30 + i) for i in range(28)]
+    jobs += [S.Params(L=1024, two_s=2, T=1.7, seed=60), S.Params(L=1056, two_s=2, T=1.6, seed=61),
+             S.Params(model=S.NORTH_EAST, L=1024, c=0.3, seed=62), S.Params(model=S.NORTH_EAST, L=1088, c=0.2, seed=63),
+             S.Params(model=S.NE_COUPLED, L=1024, c=0.5, T=3.0, seed=64), S.Params(L=72, T=2.2, seed=65),
+             S.Params(L=1000, T=2.2, seed=66), S.Params(dim=3, L=64, T=4.5, seed=67)]
+    assert sum(p.nsites for p in jobs) > 2 ** 26
+    b = S.Batch(1 << 30, max_jobs=len(jobs), record_capacity=32, flags=flags)
+    ids = [b.add(p, sweeps=17 if i % 5 else 11) for i, p in enumerate(jobs)]
+    recs = {i: [] for i in ids}
+    for n in (1, 3, 1, 2, 4, 5, 7):
+        b.sweep(n)
+        for i, r in b.drain().items():
+            recs[i].append(r)
+    for k, (i, p) in enumerate(zip(ids, jobs)):
+        print(f"case short calls flags={flags} job {k} model={p.model} L={p.L}", flush=True)
+        n = 17 if k % 5 else 11
+        o_s, o_r = run_oracle(p, n)
+        np.testing.assert_array_equal(np.vstack(recs[i]), o_r)
+        np.testing.assert_array_equal(b.spins(i), o_s)
+    b.close()
