@@ -141,6 +141,26 @@ __device__ __forceinline__ void or_row(uint32_t* words, typename BitRows<B>::Row
     if constexpr (B == 64) atomicOr(words + 1, (uint32_t)(v >> 32));
 }
 
+// Whether the lanes of a sub-lattice put a column together by ballots, one per row
+// of a lane (few, then), or by LDS atomics.  Where a wavefront holds one sub-lattice,
+// the compiler makes an atomic on its column a loop over the lanes: 1.4 us a launch of
+// lambda = 128 (us per sweep: B = 16, L = 16 9.5, with ballots 6.3; B = 64, L = 256 23.1 and
+// 15.7).
+template <int LPT>
+constexpr bool column_by_ballot()
+{
+    return LPT >= 16;
+}
+
+// bit of every lane of this lane's sub-lattice, lane l's at bit l
+template <int LPT>
+__device__ __forceinline__ uint64_t group_ballot(bool bit)
+{
+    const uint64_t m = __builtin_amdgcn_ballot_w64(bit);
+    if constexpr (LPT == 64) return m;
+    else return (m >> (threadIdx.x / LPT * LPT)) & ((1ull << LPT) - 1u);
+}
+
 template <int B, bool BAL>
 constexpr int owner_words()
 {
@@ -237,7 +257,8 @@ __device__ __forceinline__ void load_colours(const NeSubArgs& a, BitTile<B>& t, 
     constexpr int NV = B / 2 / UNIT;
     constexpr int K = Steps::per_step;
     const uint32_t xe = x0 + B == a.L ? 0u : x0 + B;
-    if (B >= 32 && l == 0) set_row<B>(t.ecol, 0, 0);
+    constexpr bool BALLOT = column_by_ballot<LPT>();
+    if (B >= 32 && !BALLOT && l == 0) set_row<B>(t.ecol, 0, 0);
     Row ecol = 0;
 #pragma nounroll
     for (int s = 0; s < Steps::steps; ++s) {
@@ -273,13 +294,22 @@ __device__ __forceinline__ void load_colours(const NeSubArgs& a, BitTile<B>& t, 
                 }
             if (B < 32) row |= (Row)(east[i] & 1u) << (B & 31);
             if (pr <= (uint32_t)B) set_row<B>(t.rows, pr, row);
-            if (pr - 1u < (uint32_t)B) {
-                set_row<B>(t.flags, pr - 1u, flags);
-                if (B >= 32) ecol |= (Row)(east[i] & 1u) << (pr - 1u);
+            const bool own = pr - 1u < (uint32_t)B;
+            if (own) set_row<B>(t.flags, pr - 1u, flags);
+            if constexpr (B >= 32 && BALLOT) {
+                const uint64_t m = group_ballot<LPT>(own && (east[i] & 1u) != 0);
+                const uint32_t first = (uint32_t)((s * K + i) * LPT);  // pr of lane 0
+                ecol |= first == 0 ? (Row)(m >> 1) : (Row)m << min(first - 1u, (uint32_t)(B - 1));
+            } else if (B >= 32 && own) {
+                ecol |= (Row)(east[i] & 1u) << (pr - 1u);
             }
         }
     }
-    if (B >= 32) or_row<B>(t.ecol, ecol);
+    if constexpr (B >= 32 && BALLOT) {
+        if (l == 0) set_row<B>(t.ecol, 0, ecol);
+    } else if constexpr (B >= 32) {
+        or_row<B>(t.ecol, ecol);
+    }
 }
 
 // Sub-lattice (tx, ty) of bit rows.
@@ -372,19 +402,29 @@ __device__ __forceinline__ void store_bits(const NeSubArgs& a, BitTile<B>& t, ui
 {
     using Row = typename BitRows<B>::Row;
     using Bits = typename BitRows<B>::Bits;
+    constexpr bool BALLOT = column_by_ballot<LPT>();
     const BitLattice<B> dst(a.dst[0], a.dst[1], a.ntiles);
-    if (l == 0) set_row<B>(t.ecol, 0, 0);
+    if (!BALLOT && l == 0) set_row<B>(t.ecol, 0, 0);
     Row column = 0;
+    constexpr int R = (B + LPT - 1) / LPT;  // rows of a lane; LPT > B: of the first B lanes
 #pragma unroll 4
-    for (uint32_t r = l; r < (uint32_t)B; r += LPT) {
-        const Row row = row_of<B>(t.rows, r + 1);
-        dst.rows[(size_t)tau * B + r] = (Bits)row;
-        dst.flags[(size_t)tau * B + r] = (Bits)row_of<B>(t.flags, r);
-        column |= (row & 1u) << r;
+    for (int i = 0; i < R; ++i) {
+        const uint32_t r = l + (uint32_t)(i * LPT);
+        const bool own = LPT <= B || r < (uint32_t)B;
+        const Row row = row_of<B>(t.rows, (own ? r : 0u) + 1u);
+        if (own) {
+            dst.rows[(size_t)tau * B + r] = (Bits)row;
+            dst.flags[(size_t)tau * B + r] = (Bits)row_of<B>(t.flags, r);
+        }
+        if constexpr (BALLOT) column |= (Row)group_ballot<LPT>(own && (row & 1u) != 0) << (i * LPT);
+        else column |= (row & 1u) << r;
     }
-    or_row<B>(t.ecol, column);
-    asm volatile("" ::: "memory");  // all lanes' parts
-    if (l == 0) dst.column[tau] = (Bits)row_of<B>(t.ecol, 0);
+    if constexpr (!BALLOT) {
+        or_row<B>(t.ecol, column);
+        asm volatile("" ::: "memory");  // all lanes' parts
+        column = row_of<B>(t.ecol, 0);
+    }
+    if (l == 0) dst.column[tau] = (Bits)column;
 }
 
 // Wavefront sums of the per-lane counts into the records: one atomic

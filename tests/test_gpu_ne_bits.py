@@ -33,3 +33,19 @@ def test_a_threshold_of_zero(model, c):
     o_s, o_r = run_oracle(p, 4)
     np.testing.assert_array_equal(g_r, o_r)
     np.testing.assert_array_equal(g_s, o_s)
+
+
+@pytest.mark.parametrize("B,lam,balanced", [
+    (B, lam, balanced) for B in (16, 32, 64) for lam in (32, 64, 128) for balanced in (False, True)
+    if (8 if balanced else 2) * lam <= B * B])
+def test_columns_put_together_by_ballots(B, lam, balanced):
+    """16, 32 and 64 lanes a sub-lattice, more and fewer than its rows, one sub-lattice
+    to a wavefront and several: the east columns of the colour arrays and of the rows
+    that pass between a call's launches."""
+    for L in (B, 2 * B, 5 * B):
+        p = S.Params(model=S.NE_SUBLATTICE_BALANCED if balanced else S.NE_SUBLATTICE, L=L, c=0.45, seed=B + lam + L,
+                     ne_side=B, ne_lambda=lam, record_capacity=16)
+        got_s, got_r = run_gpu(p, 5, chunks=[1, 3, 1])
+        ref_s, ref_r = run_oracle(p, 5)
+        np.testing.assert_array_equal(got_r, ref_r)
+        np.testing.assert_array_equal(got_s, ref_s)
