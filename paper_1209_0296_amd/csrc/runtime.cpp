@@ -228,8 +228,8 @@ sl_launch row_launch(const sl_lattice* h)
 // 0.1: 17.2 and 3.5; 3D L = 64: 8.0 and 2.8;
 // 128: 8.7 and 5.9.  Not for lattices of L >= 8192 whose rows fit the fused
 // kernels (8192: spin-1/2 36.6 against 45.7, spin-1 68.0 and 71.9, coupled NE
-// 41.9 and 51.5) unless North-East moves draw rarely (8192, c = 0.1: 48.0 and
-// 11.9).  3D lattices above L = 128, where a tile's
+// 41.9 and 51.5; spin-1/2 with two words a lane from above 6144, 35 and 28: 7168 36.5
+// and 38) unless North-East moves draw rarely (8192, c = 0.1: 48.0 and 11.9).  3D lattices above L = 128, where a tile's
 // halo costs more than the launches, walk along z with both colours per launch
 // (plane_device.hpp; spin-1/2 L = 136: 10.5 against 6.9; 232: 18.3 and 14.8;
 // 264: 22.0 and 17.9; spin-1 200: 17.3 and 15.7), but not where the rows fill
@@ -251,7 +251,8 @@ sl_launch auto_launch(const sl_lattice* h, TilePlan* tile, PlaneGeom* plane)
         return l;
     }
     const bool sparse = h->params.model == SL_NORTH_EAST && h->table[1] >= (1ull << 32);
-    if (h->params.L >= 8192 && l.mode == SL_MODE_FUSED && !sparse) return l;
+    const bool wide = h->params.L >= 8192 || (h->params.L > 6144 && h->kind == KIND_ISING_HALF && l.tile_words >= 2);
+    if (wide && l.mode == SL_MODE_FUSED && !sparse) return l;
     *tile = tile_plan(g, h->kind, coupled, sparse);
     return l;
 }
@@ -447,8 +448,16 @@ sl_status enqueue_sweeps(sl_lattice* h, uint64_t n)
     // a lane, are one round of waves of at least half the chip's 8192 (4096 28 and 32,
     // 5120 47.0 and 47.5; not 3072, 2304 waves 22 and 21, nor 6144, 9216 waves 69 and
     // 67, nor with one word a lane 4608 44 and 40, 5632 60 and 57)
+    const bool single = h->tile.k && !h->tile.bits && h->launch.mode == SL_MODE_FUSED && h->params.L >= 1536;
+    // Nor, with more tiles than two a CU, one sweep beyond the launches of four (spin-1/2
+    // L = 4096 n = 5 76 us in launches of 3 and 2, 65 so; 9 132 and 115; 2560 39 and 37; but
+    // with fewer tiles L = 2048 n = 9 34 and 38)
+    if (single && h->params.model == SL_ISING && h->lay.nsites > (1ull << 22) && n > 1 && n % h->tile.k == 1) {
+        const sl_status st = enqueue_sweeps(h, 1);
+        return st == SL_OK ? enqueue_sweeps(h, n - 1) : st;
+    }
     bool rows = false;
-    if (n <= 2 && !h->tile.bits && h->launch.mode == SL_MODE_FUSED && h->params.L >= 1536) {
+    if (n <= 2 && single) {
         const uint32_t L = (uint32_t)h->params.L, words = (uint32_t)h->launch.tile_words;
         const uint32_t waves = L / (uint32_t)h->launch.tile_rows * (L / 8 / words / 64);
         rows = n == 1 || (h->kind == KIND_ISING_HALF && words >= 2 && waves >= 4096 && waves <= 8192);

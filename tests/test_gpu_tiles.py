@@ -138,3 +138,10 @@ def test_walks_along_z_with_two_words_a_thread(two_s, L):
 def test_tiles_of_large_rows_that_fit_no_row_kernel(kw):
     """2D L = 8200: a launch of four sweeps and one of one."""
     _same(S.Params(L=8200, seed=3, record_capacity=8, **kw), [4, 1])
+
+
+@pytest.mark.parametrize("kw", [dict(L=2304, T=2.3), dict(L=2560, two_s=2, T=1.7), dict(L=7168, T=2.3)])
+def test_one_sweep_beyond_full_launches(kw):
+    """Calls of 4 m + 1 sweeps of large lattices: one on whole rows, the rest in launches
+    of four; and the widest rows below 8192, which run on rows alone."""
+    _same(S.Params(seed=5, record_capacity=16, **kw), [5, 1, 9] if kw["L"] < 7000 else [3, 2])
