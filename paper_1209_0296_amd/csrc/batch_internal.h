@@ -22,11 +22,11 @@ constexpr uint32_t kBvTile = 14;                                   // kBatchTile
 constexpr uint32_t kBvPlane = 15;                                  // both colours per launch, walks along z (3D)
 
 struct BatchJob {
-    uint8_t* col[2][2];        // [copy][colour] colour arrays (copy 1 only for fused jobs)
+    uint8_t* col[2][2];        // [copy][colour] colour arrays (copy 1: fused rows, tiles, walks along z)
     unsigned long long* acc;   // record ring [capacity][kSub][kQ]
     uint32_t key0, key1;       // Philox key = seed
     uint32_t cls;              // kind * 32 + (dim - 2) * 16 + variant
-    uint32_t copies;           // 1, or 2 for fused jobs
+    uint32_t copies;           // 1, or 2
     uint32_t dim, table_n;
     uint32_t rg_words[24];     // geometry of the job's kernel (RowGeom, StreamGeom, TileGeom, PlaneGeom)
     uint32_t row_words[15];    // RowGeom of a job on tiles, for its calls on rows

@@ -10,7 +10,8 @@
 // those of kernels_batch_tile.hip: whole lattices in one tile, tiles, walks
 // along z.  The classes here take what those do not: tables with zero
 // thresholds, arenas without room for a second lattice copy, callers that ask
-// for a strip height or switch the fused class off):
+// for a strip height or switch the fused class off, 3D rows that fill their
+// waves, and calls of few sweeps that fill the chip with 2D jobs):
 //   - resident: the lattice (both colours) fits 48 KiB of LDS.  One launch per
 //     call runs every resident job's sweeps of the call, one workgroup per job,
 //     the whole chunk of sweeps in LDS (k_batch_resident).

@@ -5,7 +5,7 @@ server keeps every admitted lattice resident in one device arena
 (``Batch``), admits queued requests whenever a job slot is free and the arena has
 room for them with the second lattice copy that their fastest kernels need (the
 rate comes from the kernels, not from the number of resident jobs: 4096 jobs in
-2 GiB run at 754 jobs/s so, at 530 while running jobs gave their second copies up
+2 GiB run at 740 to 750 jobs/s so, at 530 while running jobs gave their second copies up
 to new ones for good), and advances all resident jobs together in
 chunks of sweeps: requests that arrive while others run join the next chunk,
 and finished jobs free their space at once.  Each job's records are the ones
